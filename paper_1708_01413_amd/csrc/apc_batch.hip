@@ -417,12 +417,18 @@ __global__ void k_batch_check(const BatchSys* sys, int32_t count, const int32_t*
 // item kinds share one LDS buffer.  Registers are capped for two workgroups
 // per CU (one otherwise: 326 against 338 us per update for the 8192^2 k = 64
 // system with the 256 systems; four steps of prefetch took 345; the k = 1
-// tile as a called function instead of inlined, 395).
+// tile as a called function instead of inlined, 395).  The FP32 contraction
+// loads two steps ahead, one with 64 right-hand sides (two spill there), and
+// 128 right-hand sides go in two column groups of 64: a group of 128 stages
+// 100 KB of V, which leaves one workgroup per CU (8192^2, k = 128 with the
+// 256 systems: 476 us per update, 397 in two groups; 425 on the FP32 matrix
+// instructions.  k = 64: 289 -> 257).
 template <int NCT>
 __global__ __launch_bounds__(256, 2) void k_batch_mixed(const BatchSys* sys, const BatchGemm* gemm,
                                                      const int4* items, int32_t nitems,
                                                      const int32_t* active) {
-  constexpr size_t kTn = sizeof(TnStage<NCT>);
+  constexpr size_t kTn = sizeof(TnStage<float, NCT>);  // the larger of the two
+  constexpr int kPf = NCT == 4 ? 1 : 2;
   constexpr size_t kRed = sizeof(float) * 4 * kBatchFusedCols;
   constexpr size_t kBytes = kTn > kRed ? kTn : kRed;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kBytes];
@@ -440,9 +446,9 @@ __global__ __launch_bounds__(256, 2) void k_batch_mixed(const BatchSys* sys, con
       // (The FP64 contraction, an anchor update's, loads one step ahead: with
       // two the kernel's union of work kinds spilled registers.)
       if (kind == kItemTn32)
-        tn_block<float, 1, NCT, 2, 1>(a, w.w, *reinterpret_cast<TnStage<NCT>*>(lds));
+        tn_block<float, 1, NCT, kPf, 1>(a, w.w, *reinterpret_cast<TnStage<float, NCT>*>(lds));
       else
-        tn_block<double, 1, NCT, 1, 0>(a, w.w, *reinterpret_cast<TnStage<NCT>*>(lds));
+        tn_block<double, 1, NCT, 1, 0>(a, w.w, *reinterpret_cast<TnStage<double, NCT>*>(lds));
       __syncthreads();
     } else {
       // Elementwise items, four consecutive entries per thread: every row
@@ -494,7 +500,6 @@ hipError_t launch_batch_mixed(int32_t grid, int32_t nct, const BatchSys* sys, co
     case 1: k_batch_mixed<1><<<grid, 256, 0, s>>>(sys, gemm, items, nitems, active); break;
     case 2: k_batch_mixed<2><<<grid, 256, 0, s>>>(sys, gemm, items, nitems, active); break;
     case 4: k_batch_mixed<4><<<grid, 256, 0, s>>>(sys, gemm, items, nitems, active); break;
-    case 8: k_batch_mixed<8><<<grid, 256, 0, s>>>(sys, gemm, items, nitems, active); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -23,8 +23,9 @@
 // K permutation: the MFMA instructions reduce over a K index that is only a
 // label.  A step's 256 bytes of a row are sixteen 16-byte chunks; lane group g
 // (lanes 16 g .. 16 g + 15) holds chunks g, 4 + g, 8 + g, 12 + g as pieces
-// p = 0..3, and piece p feeds the p-th MFMA of the step (bf16: one 16x16x32,
-// f32: four 16x16x4, f64: two 16x16x4).  In a row-major M one load instruction
+// p = 0..3, and piece p feeds the p-th product of the step (bf16: one 16x16x32;
+// f64: two 16x16x4; f32: two pieces together, split into three bf16 parts, six
+// 16x16x32, see Split3).  In a row-major M one load instruction
 // then reads 64 contiguous bytes of each of 16 rows, which measured 2-5 %
 // faster than giving each lane one contiguous 64-byte run.  V is read from LDS
 // with exactly the same (lane group, piece, element) -> K mapping, so the sum
@@ -59,7 +60,7 @@ namespace {
 
 template <typename T, int RT, int NCT, int PF, int NT, int W>
 __global__ __launch_bounds__(64 * W) void k_tn(TnArgs a) {
-  __shared__ TnStage<NCT> vs;
+  __shared__ TnStage<T, NCT> vs;
   tn_block<T, RT, NCT, PF, NT, W>(a, blockIdx.x, vs);
 }
 
@@ -137,27 +138,9 @@ hipError_t tn_pf(int rt, int pf, const TnArgs& a, hipStream_t s) {
 
 // ------------------------------------------------------------------ epilogues
 
-// out[c*ldo + r] = TQ(sum of the split partials), r < rows, c < kp.
-template <typename P, typename TQ>
-__global__ __launch_bounds__(256) void k_tn_sum_cast(const P* part, int32_t nsplit, int32_t kp,
-                                                     int64_t ldp, int64_t rows, TQ* out, int64_t ldo) {
-  const int64_t total = static_cast<int64_t>(kp) * rows;
-  const int64_t stride = static_cast<int64_t>(kp) * ldp;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    sum_cast_elem(part, nsplit, ldp, rows, stride, out, ldo, e);
-}
-
 // The (y, x_bar) update, its start, or an anchor update; see TnUpdateArgs.
-template <typename P, typename TQ>
-__global__ __launch_bounds__(256) void k_tn_update(TnUpdateArgs a) {
-  const int64_t total = static_cast<int64_t>(a.kp) * a.n;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    update_elem<P, TQ>(a, e);
-}
-
-// The same four entries per thread (every row length and stride a multiple of 4).
+// Four consecutive entries per thread (every row length and stride of a plan's
+// operands is a multiple of 256).
 template <typename P, typename TQ>
 __global__ __launch_bounds__(256) void k_tn_update4(TnUpdateArgs a) {
   const int64_t total = static_cast<int64_t>(a.kp) * a.n / 4;
@@ -166,6 +149,7 @@ __global__ __launch_bounds__(256) void k_tn_update4(TnUpdateArgs a) {
     update4<P, TQ>(a, 4 * e);
 }
 
+// out = the V operand W (row c, rows entries): the sum of the split partials.
 template <typename P, typename TQ>
 __global__ __launch_bounds__(256) void k_tn_sum_cast4(const P* part, int32_t nsplit, int32_t kp,
                                                       int64_t ldp, int64_t rows, TQ* out, int64_t ldo) {
@@ -186,13 +170,37 @@ __global__ __launch_bounds__(256) void k_tn_anchor_vec(const double* y, const do
     yref[e] = (1.0 - gamma) * y[e] + gamma * xb[e];
 }
 
-// Operand yq = TQ((1 - gamma) y + gamma x_bar) after the state was restored.
+// The V operand yq = TQ((1 - gamma) y + gamma x_bar) after the state was
+// restored, rows of n entries (stride n).
 template <typename TQ>
 __global__ __launch_bounds__(256) void k_tn_prep(const double* y, const double* xb, int64_t count,
-                                                 double gamma, TQ* yq) {
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; e < count;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    yq[e] = cvt<TQ>((1.0 - gamma) * y[e] + gamma * xb[e]);
+                                                 int64_t n, double gamma, TQ* yq) {
+  for (int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x); e < count;
+       e += 4 * static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    double yv[4], xv[4];
+    load4(y + e, yv);
+    load4(xb + e, xv);
+    TQ q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = cvt<TQ>((1.0 - gamma) * yv[u] + gamma * xv[u]);
+    const int64_t c = e / n;
+    store_operand4(yq, n, c, e - c * n, q);
+  }
+}
+
+// dst (rows x ldd V operand) = src (FP64, rows x cols, stride lds), zero past cols.
+template <typename TQ>
+__global__ __launch_bounds__(256) void k_tn_operand(const double* src, int64_t lds, int64_t rows,
+                                                    int64_t cols, TQ* dst, int64_t ldd) {
+  const int64_t count = rows * ldd;
+  for (int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x); e < count;
+       e += 4 * static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    const int64_t c = e / ldd, j = e - c * ldd;
+    TQ q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = j + u < cols ? cvt<TQ>(src[c * lds + j + u]) : TQ(0);
+    store_operand4(dst, ldd, c, j, q);
+  }
 }
 
 // One reverse step of the (y, x_bar) iteration; see TnAdjointArgs.  Each
@@ -206,20 +214,42 @@ __global__ __launch_bounds__(256) void k_tn_adjoint(TnAdjointArgs a) {
   TQ* bq = static_cast<TQ*>(a.bq);
   const double g = a.gamma, eta = a.eta;
   double sg = 0.0, se = 0.0;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+  for (int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x); e < total;
+       e += 4 * static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const int64_t c = e / a.n, j = e - c * a.n;
     const int64_t i = c * a.ldx + j;
-    const double xbh = split_sum(part, a.nsplit, stride, c * a.ldp + j) * a.inv_m;  // X b
-    const double bh = a.bh[i];
-    const double at = a.a[i] + eta * (bh - xbh);
-    sg += at * (a.xb_t[i] - a.y_t[i]);
-    se += bh * (a.xb_next[i] - a.xb_t[i]);
-    a.g0[i] += eta * bh;
-    a.a[i] = (1.0 - g) * at;
-    const double bn = (1.0 - eta) * bh + g * at;
-    a.bh[i] = bn;
-    bq[c * a.ldq + j] = cvt<TQ>(bn);
+    P zs[4];
+    load4(part + c * a.ldp + j, zs);
+    for (int sp = 1; sp < a.nsplit; ++sp) {
+      P t[4];
+      load4(part + sp * stride + c * a.ldp + j, t);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) zs[q] += t[q];
+    }
+    double av[4], bv[4], gv[4], yv[4], xv[4], nv[4];
+    load4(a.a + i, av);
+    load4(a.bh + i, bv);
+    load4(a.g0 + i, gv);
+    load4(a.y_t + i, yv);
+    load4(a.xb_t + i, xv);
+    load4(a.xb_next + i, nv);
+    TQ qv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double xbh = static_cast<double>(zs[q]) * a.inv_m;  // X b
+      const double bh = bv[q];
+      const double at = av[q] + eta * (bh - xbh);
+      sg += at * (xv[q] - yv[q]);
+      se += bh * (nv[q] - xv[q]);
+      gv[q] += eta * bh;
+      av[q] = (1.0 - g) * at;
+      bv[q] = (1.0 - eta) * bh + g * at;
+      qv[q] = cvt<TQ>(bv[q]);
+    }
+    store4(a.g0 + i, gv);
+    store4(a.a + i, av);
+    store4(a.bh + i, bv);
+    store_operand4(bq, a.ldq, c, j, qv);
   }
   __shared__ double rs[2][256];
   rs[0][threadIdx.x] = sg;
@@ -462,19 +492,11 @@ int tn_step_elems(int type) { return type == kTnF64 ? 32 : type == kTnF32 ? 64 :
 
 hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_t kp, int64_t ldp,
                               int64_t rows, void* out, int64_t ldo, hipStream_t s) {
-  // Four entries per thread where every row starts 16-byte aligned.
-  const bool four = rows % 4 == 0 && ldp % 4 == 0 && ldo % 4 == 0 && quad_ok(part) &&
-                    reinterpret_cast<uintptr_t>(out) % 16 == 0;
-  const unsigned g = grid_stride_blocks(static_cast<int64_t>(kp) * rows / (four ? 4 : 1));
-#define APC_SUM_CAST(P, TQ)                                                                      \
-  do {                                                                                           \
-    if (four)                                                                                    \
-      APC_LAUNCH((k_tn_sum_cast4<P, TQ>), dim3(g), dim3(256), 0, s, static_cast<const P*>(part), \
-                 nsplit, kp, ldp, rows, static_cast<TQ*>(out), ldo);                             \
-    else                                                                                         \
-      APC_LAUNCH((k_tn_sum_cast<P, TQ>), dim3(g), dim3(256), 0, s, static_cast<const P*>(part),  \
-                 nsplit, kp, ldp, rows, static_cast<TQ*>(out), ldo);                             \
-  } while (0)
+  if (rows % 4 || ldp % 4 || ldo % 4 || !quad_ok(part) || !quad_ok(out)) return hipErrorInvalidValue;
+  const unsigned g = grid_stride_blocks(static_cast<int64_t>(kp) * rows / 4);
+#define APC_SUM_CAST(P, TQ)                                                                    \
+  APC_LAUNCH((k_tn_sum_cast4<P, TQ>), dim3(g), dim3(256), 0, s, static_cast<const P*>(part),   \
+             nsplit, kp, ldp, rows, static_cast<TQ*>(out), ldo)
   switch (type) {
     case kTnF64: APC_SUM_CAST(double, double); break;
     case kTnF32: APC_SUM_CAST(float, float); break;
@@ -486,15 +508,12 @@ hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_
 }
 
 hipError_t launch_tn_update(int type, int part_f64, const TnUpdateArgs& a, hipStream_t s) {
-  const bool four = a.n % 4 == 0 && a.ldp % 4 == 0 && a.ldx % 4 == 0 && a.ldq % 4 == 0 &&
-                    quad_ok(a.part) && quad_ok(a.x0) && quad_ok(a.y) && quad_ok(a.xb) &&
-                    quad_ok(a.yq) && (!a.yref || (quad_ok(a.yref) && quad_ok(a.uref)));
-  const unsigned g = grid_stride_blocks(static_cast<int64_t>(a.kp) * a.n / (four ? 4 : 1));
-#define APC_UPDATE(P, TQ)                                                            \
-  do {                                                                               \
-    if (four) APC_LAUNCH((k_tn_update4<P, TQ>), dim3(g), dim3(256), 0, s, a);        \
-    else APC_LAUNCH((k_tn_update<P, TQ>), dim3(g), dim3(256), 0, s, a);              \
-  } while (0)
+  if (a.n % 4 || a.ldp % 4 || a.ldx % 4 || a.ldq % 4 || !quad_ok(a.part) || !quad_ok(a.x0) ||
+      !quad_ok(a.y) || !quad_ok(a.xb) || !quad_ok(a.yq) ||
+      (a.yref && (!quad_ok(a.yref) || !quad_ok(a.uref))))
+    return hipErrorInvalidValue;
+  const unsigned g = grid_stride_blocks(static_cast<int64_t>(a.kp) * a.n / 4);
+#define APC_UPDATE(P, TQ) APC_LAUNCH((k_tn_update4<P, TQ>), dim3(g), dim3(256), 0, s, a)
   if (part_f64) {
     switch (type) {
       case kTnF64: APC_UPDATE(double, double); break;
@@ -519,13 +538,27 @@ hipError_t launch_tn_anchor_vec(const double* y, const double* xb, int64_t count
   return hipGetLastError();
 }
 
-hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, double gamma,
-                          void* yq, hipStream_t s) {
-  const unsigned g = grid_stride_blocks(count);
+hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, int64_t n,
+                          double gamma, void* yq, hipStream_t s) {
+  if (n % tn_step_elems(type) || count % n || !quad_ok(y) || !quad_ok(xb) || !quad_ok(yq))
+    return hipErrorInvalidValue;
+  const unsigned g = grid_stride_blocks(count / 4);
   switch (type) {
-    case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, gamma, static_cast<double*>(yq)); break;
-    case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, gamma, static_cast<float*>(yq)); break;
-    case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, gamma, static_cast<__bf16*>(yq)); break;
+    case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<double*>(yq)); break;
+    case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<float*>(yq)); break;
+    case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<__bf16*>(yq)); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t rows, int64_t cols,
+                             void* dst, int64_t ldd, hipStream_t s) {
+  if (ldd % tn_step_elems(type) || cols > ldd || !quad_ok(dst)) return hipErrorInvalidValue;
+  const unsigned g = grid_stride_blocks(rows * ldd / 4);
+  switch (type) {
+    case kTnF64: k_tn_operand<double><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<double*>(dst), ldd); break;
+    case kTnF32: k_tn_operand<float><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<float*>(dst), ldd); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -578,9 +611,9 @@ hipError_t tn_pack(int type, const double* src, int64_t lds, int64_t srows, int6
 
 }  // namespace
 
-hipError_t launch_tn_pack(int type, const double* src, int64_t lds, int64_t srows, int64_t scols,
-                          int32_t transpose, void* dst, int64_t ldd, int64_t drows, hipStream_t s) {
-  return tn_pack(type, src, lds, srows, scols, transpose, dst, ldd, drows, 0, s);
+hipError_t launch_tn_pack(const double* src, int64_t lds, int64_t srows, int64_t scols,
+                          int32_t transpose, double* dst, int64_t ldd, int64_t drows, hipStream_t s) {
+  return tn_pack(kTnF64, src, lds, srows, scols, transpose, dst, ldd, drows, 0, s);
 }
 
 hipError_t launch_tn_pack_frag(int type, const double* src, int64_t lds, int64_t srows,

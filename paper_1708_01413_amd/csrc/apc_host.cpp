@@ -237,8 +237,12 @@ Layout make_layout(int64_t N, int64_t n, const int64_t* off, int32_t m, int32_t 
   // bf16: C^T in FP32 for the inner solves' starts (x_bar(0) = (1/m) C^T c).
   L.C32T = take(bf ? L.np * L.Np * 4 : 0);
   L.Apad = take(gemm ? L.Np * L.np * d : 0);
-  L.yq = take(gemm ? kp * L.np * sq : 0);
-  L.Wq = take(gemm ? kp * L.Np * sq : 0);
+  const int tq = prec == APC_F64 ? kTnF64 : prec == APC_F32 ? kTnF32 : kTnBF16;
+  L.yq = take(gemm ? tn_operand_bytes(tq, kp, L.np) : 0);
+  // (An FP32 iteration's W shares the FP64 W's slice below: an update forms
+  // one or the other and reads it right after.)
+  const bool own_wq = gemm && prec != APC_F32;
+  L.Wq = take(own_wq ? tn_operand_bytes(tq, kp, L.Np) : 0);
   L.tnpart = take(gemm ? static_cast<int64_t>(kTnMaxSplit) * kp * std::max(L.Np, L.np) * d : 0);
   L.xbar = take((gemm ? kp * L.np : kq * L.ldc) * d);
   L.x0 = take(gemm ? kp * L.np * d : 0);
@@ -252,6 +256,7 @@ Layout make_layout(int64_t N, int64_t n, const int64_t* off, int32_t m, int32_t 
   L.yref = take(anc ? kp * L.np * d : 0);
   L.uref = take(anc ? kp * L.np * d : 0);
   L.W64 = take(anc ? kp * L.Np * d : 0);
+  if (!own_wq) L.Wq = L.W64;
   L.Rb = take(gemm ? kp * N * d : 0);
   L.cw = take(bf ? kp * N * d : 0);
   L.ssq = take(sumsq_parts() * d);
@@ -845,7 +850,7 @@ apc_status update_gemm(apc_plan_s* P, hipEvent_t* ev, int* kinds, int* nev) {
 apc_status start_gemm(apc_plan_s* P, const double* c_rhs) {
   const Layout& L = P->L;
   const int t = x0_type(P);
-  HIP_TRY(launch_tn_pack(t, c_rhs, P->N, P->kp, P->N, 0, P->ws + L.c64p, L.Np, P->kp, P->stream));
+  HIP_TRY(launch_tn_operand(t, c_rhs, P->N, P->kp, P->N, P->ws + L.c64p, L.Np, P->stream));
   HIP_TRY(launch_tn(t, P->tnX0.rt, P->tnX0.pf, x0_args(P), P->stream));
   HIP_TRY(launch_tn_update(P->tq, t == kTnF64, update_args(P, P->tnX0, 1), P->stream));
   P->since_start = 0;
@@ -928,7 +933,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
   std::vector<TnChoice> cand;
   const int rts[3] = {1, 2, 4};
   for (int rt : rts) {
-    if (type == kTnF64 && rt == 4) continue;
+    if (type != kTnBF16 && rt == 4) continue;  // registers (FP32: spills, never the fastest)
     if (base.rows % (64 * rt)) continue;
     for (int ns : splits) {
       if (blocks(rt, ns) < 64 && !(rt == 1 && ns == 8)) continue;
@@ -1591,9 +1596,8 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
       optimum(lo, hi, &P->gamma, &P->eta, &P->rho);
     }
     HIP_TRY(launch_tn_pack_frag(kTnF64, P->A, P->lda, N, n, 0, P->ws + L.Apad, np, Np, st));
-    const int64_t sq = P->tq == kTnF64 ? 8 : P->tq == kTnF32 ? 4 : 2;
-    HIP_TRY(launch_fill_u32(P->at<unsigned>(L.yq), P->kp * np * sq / 4, 0u, st));
-    HIP_TRY(launch_fill_u32(P->at<unsigned>(L.Wq), P->kp * Np * sq / 4, 0u, st));
+    HIP_TRY(launch_fill_u32(P->at<unsigned>(L.yq), tn_operand_bytes(P->tq, P->kp, np) / 4, 0u, st));
+    HIP_TRY(launch_fill_u32(P->at<unsigned>(L.Wq), tn_operand_bytes(P->tq, P->kp, Np) / 4, 0u, st));
     HIP_TRY(launch_fill_u32(P->at<unsigned>(L.c64p), 2 * P->kp * Np, 0u, st));
     HIP_TRY(launch_fill_u32(P->at<unsigned>(L.xbar), 2 * P->kp * np, 0u, st));
     HIP_TRY(launch_fill_u32(P->at<unsigned>(L.Rb), 2 * P->kp * N, 0u, st));
@@ -2263,7 +2267,7 @@ apc_status restart_impl(apc_plan_s* P, const double* B, int64_t ldb) {
     double* cb = P->at<double>(L.cb);
     double* ca = P->at<double>(L.ca);
     // RHS-major copy of B (columns k..kp zero), then the two inverse factors.
-    HIP_TRY(launch_tn_pack(kTnF64, B, ldb, P->N, P->k, 1, cb, P->N, P->kp, st));
+    HIP_TRY(launch_tn_pack(B, ldb, P->N, P->k, 1, cb, P->N, P->kp, st));
     HIP_TRY(launch_linv_apply(P->doff(), P->at<int64_t>(L.goff), P->m, P->pmax,
                               P->at<double>(L.Linv), cb, P->N, ca, P->N, P->kp, 0, 1.0, st));
     if (P->qr_passes == 2) {
@@ -2297,14 +2301,13 @@ apc_status restart_impl(apc_plan_s* P, const double* B, int64_t ldb) {
 
 // Slices of the caller's backward workspace.
 struct BwdLayout {
-  size_t ck, seg, a, bh, g0, bq, red, total;
+  size_t ck, seg, a, bh, g0, red, total;
 };
 
 BwdLayout bwd_layout(const apc_plan_s* P, int32_t T, int32_t ckpt) {
   BwdLayout B{};
   const int64_t st = static_cast<int64_t>(P->kp) * P->L.np * 8;  // one FP64 state vector set
   const int64_t nck = T > 0 ? (T + ckpt - 1) / ckpt : 0;
-  const int64_t sq = P->tq == kTnF64 ? 8 : 4;
   size_t cur = 0;
   auto take = [&](int64_t bytes) {
     const size_t at = cur;
@@ -2316,7 +2319,6 @@ BwdLayout bwd_layout(const apc_plan_s* P, int32_t T, int32_t ckpt) {
   B.a = take(st);
   B.bh = take(st);
   B.g0 = take(st);
-  B.bq = take(static_cast<int64_t>(P->kp) * P->L.np * sq);
   B.red = take(2 * static_cast<int64_t>(tn_adjoint_blocks()) * 8);
   B.total = cur;
   return B;
@@ -2336,7 +2338,8 @@ apc_status restore_state(apc_plan_s* P, const double* y, const double* xb) {
   const Layout& L = P->L;
   ST_TRY(copy_state(P, P->at<double>(L.ys), P->xbar(), y, xb));
   HIP_TRY(launch_tn_prep(P->tq, P->at<double>(L.ys), P->xbar(),
-                         static_cast<int64_t>(P->kp) * L.np, P->gamma, P->ws + L.yq, P->stream));
+                         static_cast<int64_t>(P->kp) * L.np, L.np, P->gamma, P->ws + L.yq,
+                         P->stream));
   P->since_start = 0;
   return APC_OK;
 }
@@ -2379,7 +2382,9 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
   double* a = reinterpret_cast<double*>(bw + BL.a);
   double* bh = reinterpret_cast<double*>(bw + BL.bh);
   double* g0 = reinterpret_cast<double*>(bw + BL.g0);
-  void* bq = bw + BL.bq;
+  // The adjoint's operand takes the start's slice: the forward's start is over
+  // once the first update runs.
+  void* bq = P->ws + L.c64p;
   double* red = reinterpret_cast<double*>(bw + BL.red);
   double* ys = P->at<double>(L.ys);
   double* xb = P->xbar();
@@ -2397,8 +2402,8 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(a), 2 * cnt, 0u, st));
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(g0), 2 * cnt, 0u, st));
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(red), 4 * tn_adjoint_blocks(), 0u, st));
-  HIP_TRY(launch_tn_pack(kTnF64, dXbar, ldd, P->n, P->k, 1, bh, L.np, P->kp, st));
-  HIP_TRY(launch_tn_prep(P->tq, a, bh, cnt, 1.0, bq, st));  // bq = TQ(bh)
+  HIP_TRY(launch_tn_pack(dXbar, ldd, P->n, P->k, 1, bh, L.np, P->kp, st));
+  HIP_TRY(launch_tn_prep(P->tq, a, bh, cnt, L.np, 1.0, bq, st));  // bq = TQ(bh)
 
   void* part = P->ws + L.tnpart;
   for (int64_t sgi = nck - 1; sgi >= 0; --sgi) {
@@ -2576,7 +2581,7 @@ BatchGemm batch_gemm_desc(apc_plan_s* P) {
   // The batch kernel runs one 16-row tile per wave in four-wave workgroups.
   for (int q = 0; q < 4; ++q) {
     G.tn[q].waves = 4;
-    G.tn_blocks[q] = static_cast<int32_t>((G.tn[q].rows / 64) * (P->kp / (16 * std::min(8, P->kp / 16))) *
+    G.tn_blocks[q] = static_cast<int32_t>((G.tn[q].rows / 64) * (P->kp / (16 * std::min(4, P->kp / 16))) *
                                           G.tn[q].nsplit);
   }
   G.sum_part = part;
@@ -2861,7 +2866,7 @@ apc_status apc_batch_create(apc_batch* out, const apc_plan* plans, int32_t count
     B->itemsL0 = reinterpret_cast<int4*>(B->ws + L.L0);
     B->nL0 = static_cast<int32_t>(it.L0.size());
     const apc_plan_s* G0 = plans[it.gemm_sys[0]];
-    B->nct = std::min(8, G0->kp / 16);
+    B->nct = std::min(4, G0->kp / 16);  // 128 right-hand sides: two column groups of 64
     B->anchor_every = G0->anchor_every;
     B->since = G0->since_start;
   }

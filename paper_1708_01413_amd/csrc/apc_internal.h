@@ -397,7 +397,9 @@ constexpr int kTnMaxSplit = 8;    // split-K factors the partial buffer holds
 // a row), kp is 16, 32, 64 or a multiple of 128, M and V rows are 16-byte
 // aligned and zero wherever they extend past the data.
 // M: rows x K in the fragment-packed layout written by launch_tn_pack_frag
-// (ldm = K); V: kp rows of K, stride ldv.
+// (ldm = K); V: kp rows of K entries, stride ldv (a multiple of the step): row-
+// major in bf16 and FP64, split into three bf16 parts in FP32 (TnOperand in
+// apc_tn.h; written by the epilogues and launch_tn_operand).
 struct TnArgs {
   const void* M;
   int64_t ldm;
@@ -418,7 +420,8 @@ struct TnArgs {
 // covers 16 * waves * rt rows.
 hipError_t launch_tn(int type, int rt, int pf, const TnArgs& a, hipStream_t s);
 int tn_step_elems(int type);
-// out[c*ldo + r] = TQ(sum over the nsplit partials in split order), r < rows, c < kp.
+// out = the V operand TQ(sum over the nsplit partials in split order): row c,
+// entries r < rows (stride ldo), c < kp.
 hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_t kp, int64_t ldp,
                               int64_t rows, void* out, int64_t ldo, hipStream_t s);
 // One update of APC in the (y, x_bar) form, over c < kp, j < n (state FP64 with
@@ -454,10 +457,18 @@ struct TnUpdateArgs {
 hipError_t launch_tn_anchor_vec(const double* y, const double* xb, int64_t count, double gamma,
                                 double* yref, hipStream_t s);
 hipError_t launch_tn_update(int type, int part_f64, const TnUpdateArgs& a, hipStream_t s);
-// yq = TQ((1 - gamma) y + gamma x_bar), count entries (the pass-A operand for a
-// restored state).
-hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, double gamma,
-                          void* yq, hipStream_t s);
+// yq = TQ((1 - gamma) y + gamma x_bar), count entries in rows of n (the pass-A
+// operand for a restored state).
+hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, int64_t n,
+                          double gamma, void* yq, hipStream_t s);
+// dst = the V operand (rows of ldd entries, type FP64 or FP32) of src (FP64,
+// rows x cols, stride lds), zero past cols.
+hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t rows, int64_t cols,
+                             void* dst, int64_t ldd, hipStream_t s);
+// Bytes of a V operand of `rows` rows of ld entries.
+inline int64_t tn_operand_bytes(int type, int64_t rows, int64_t ld) {
+  return rows * ld * (type == kTnF64 ? 8 : type == kTnF32 ? 6 : 2);
+}
 
 // One reverse step of the (y, x_bar) iteration (FP64 adjoints a = dL/dy(t+1),
 // bh = dL/dx_bar(t+1); z = the summed partials of C^T C b_q, so X bh = z / m):
@@ -567,7 +578,7 @@ enum BatchItemKind {
   kItemSum64 = 5, kItemUpd32 = 6, kItemUpd64 = 7, kItemAnchorVec = 8
 };
 constexpr int kBatchChunk = 2048;  // elements per split-sum / update / y_ref item
-// nct = kp / 16 of the k-RHS plans (1, 2, 4 or 8).
+// nct: 16-column tiles per column group of the k-RHS plans (1, 2 or 4).
 hipError_t launch_batch_mixed(int32_t grid, int32_t nct, const BatchSys* sys, const BatchGemm* gemm,
                               const int4* items, int32_t nitems, const int32_t* active,
                               hipStream_t s);
@@ -590,11 +601,11 @@ hipError_t launch_batch_check(const BatchSys* sys, int32_t count, const int32_t*
 hipError_t launch_tn_resid(const double* part, int32_t nsplit, int32_t kp, int64_t ldp, int64_t N,
                            int32_t k, const double* B, int64_t ldb, double* R, int64_t ldr,
                            hipStream_t s);
-// dst (drows x ldd, element type of `type`) = src, or src^T when transpose,
-// zero outside the FP64 source (srows x scols, stride lds).
-hipError_t launch_tn_pack(int type, const double* src, int64_t lds, int64_t srows, int64_t scols,
-                          int32_t transpose, void* dst, int64_t ldd, int64_t drows, hipStream_t s);
-// The same into the fragment-packed layout of k_tn's M operand (rows x K,
+// dst (drows x ldd, FP64) = src, or src^T when transpose, zero outside the
+// FP64 source (srows x scols, stride lds).
+hipError_t launch_tn_pack(const double* src, int64_t lds, int64_t srows, int64_t scols,
+                          int32_t transpose, double* dst, int64_t ldd, int64_t drows, hipStream_t s);
+// The same, in the element type of `type`, into the fragment-packed layout of k_tn's M operand (rows x K,
 // rows % 16 == 0, K a multiple of tn_step_elems(type)).
 hipError_t launch_tn_pack_frag(int type, const double* src, int64_t lds, int64_t srows,
                                int64_t scols, int32_t transpose, void* dst, int64_t K,

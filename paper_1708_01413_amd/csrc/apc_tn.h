@@ -39,16 +39,11 @@ struct TnTraits<double> {
 };
 
 // MFMA over one 16-byte piece of A (lane's row) and B (lane's right-hand side).
-__device__ inline void mma_piece(const u32x4& a, const u32x4& b, f32x4& c, __bf16*) {
+__device__ inline void mma_bf16(const u32x4& a, const u32x4& b, f32x4& c) {
   c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                               __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-__device__ inline void mma_piece(const u32x4& a, const u32x4& b, f32x4& c, float*) {
-  const f32x4 av = __builtin_bit_cast(f32x4, a);
-  const f32x4 bv = __builtin_bit_cast(f32x4, b);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], c, 0, 0, 0);
-}
+__device__ inline void mma_piece(const u32x4& a, const u32x4& b, f32x4& c, __bf16*) { mma_bf16(a, b, c); }
 __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f64x4& c, double*) {
   const f64x2 av = __builtin_bit_cast(f64x2, a);
   const f64x2 bv = __builtin_bit_cast(f64x2, b);
@@ -56,12 +51,69 @@ __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f64x4& c, doubl
   for (int e = 0; e < 2; ++e) c = __builtin_amdgcn_mfma_f64_16x16x4f64(av[e], bv[e], c, 0, 0, 0);
 }
 
-// V staging of one workgroup: two 256-byte-per-row steps of 16 NCT rows, 16
-// pieces per row + 1 pad (conflict-free fragment reads).
-template <int NCT>
+// FP32 operands on the bf16 matrix cores.  An FP32 value is the exact sum of
+// three bf16 values: h = its upper half (truncated), m = the remainder rounded
+// to bf16, l = what is left (at most 8 significant bits, so exact).  A product
+// is then h h' + h m' + m h' + m m' + h l' + l h' in FP32 accumulation; the
+// three left out (m l', l m', l l') are together below 2^-21 of it with random
+// signs, small against the rounding of the FP32 sums they would be added to.
+// Infinities and NaN give NaN.  The FP32 matrix instructions run at 1/16 of
+// the bf16 rate, so six products take 3/8 of their time; errors against 64
+// bits measured 0.3-0.85 of theirs (fewer roundings per sum).
+struct Split3 {
+  u32x4 h, m, l;  // eight bf16 each
+};
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+__device__ inline void split_pair(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  const unsigned u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the two upper halves
+  const float r0 = x0 - __uint_as_float(u0 & 0xffff0000u);
+  const float r1 = x1 - __uint_as_float(u1 & 0xffff0000u);
+  m = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2v{r0, r1}, bf16x2v));
+  const float s0 = r0 - __uint_as_float(m << 16);
+  const float s1 = r1 - __uint_as_float(m & 0xffff0000u);
+  l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
+}
+__device__ inline Split3 split8(const u32x4& a, const u32x4& b) {
+  const f32x4 av = __builtin_bit_cast(f32x4, a), bv = __builtin_bit_cast(f32x4, b);
+  Split3 s;
+  unsigned h, m, l;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    split_pair(av[2 * e], av[2 * e + 1], h, m, l);
+    s.h[e] = h;
+    s.m[e] = m;
+    s.l[e] = l;
+    split_pair(bv[2 * e], bv[2 * e + 1], h, m, l);
+    s.h[2 + e] = h;
+    s.m[2 + e] = m;
+    s.l[2 + e] = l;
+  }
+  return s;
+}
+
+// The V operand (one row of K entries per right-hand side).  bf16 and FP64:
+// row-major, 256 bytes per row and step.  FP32: split when it is written, 384
+// bytes per row and step of 64: the h, m and l parts of the step, 128 bytes
+// each, every part in the order the lanes take it (chunk kc = 8 q + 4 h + g of
+// four entries at 32 q + 8 g + 4 h, so lane group g's eight entries of the
+// matrix product q, its pieces 2 q and 2 q + 1 of M, are 16 contiguous bytes).
+// A workgroup stages a step in wave loads of kRows rows x 16 kLanes
+// contiguous bytes (kParts of them cover a row).
+template <typename T>
+struct TnOperand {
+  static constexpr int kStepBytes = sizeof(T) == 4 ? 384 : 256;
+  static constexpr int kLanes = sizeof(T) == 4 ? 8 : 16;
+  static constexpr int kRows = 64 / kLanes;
+  static constexpr int kParts = kStepBytes / (16 * kLanes);
+};
+
+// V staging of one workgroup: two steps of 16 NCT rows, each row's 16-byte
+// chunks + 1 pad (fragment reads, 16 rows at one chunk, are conflict-free).
+template <typename T, int NCT>
 struct TnStage {
-  u32x4 v[2][NCT * 16][17];
-  __device__ u32x4 (&operator[](int b))[NCT * 16][17] { return v[b]; }
+  u32x4 v[2][NCT * 16][TnOperand<T>::kStepBytes / 16 + 1];
 };
 
 // Element offset of (row r, column c) in the fragment-packed layout of a
@@ -76,14 +128,23 @@ __host__ __device__ inline int64_t frag_index(int64_t r, int64_t c, int64_t rows
   return (ks * (rows / 16) + r / 16) * (16 * kStep) + (64 * (kc / 4) + lane) * kE + c % kE;
 }
 
+// What bounds it.  FP32, 16384^2, k = 128: 505 us per pass on the FP32 matrix
+// instructions (86 % of their rate), 343 us here (242 us on zeros: six bf16
+// products draw enough power that the clock falls to ~2 GHz; 1.07 GB of M
+// would take 165 us).  8192^2, k = 64: 75 -> 53-63 us (268 MB of M, 4.3-5.1
+// TB/s).  bf16 and FP64: HBM, and the FP64 matrix rate from 64 right-hand
+// sides on.
+//
 // Workgroup: W waves (4 or 8), wave w owns RT consecutive 16-row tiles, all
 // 16*NCT right-hand sides of its column group.  Grid: (rows / (16 W RT)) x ncg x nsplit,
 // with the split index fastest so that, dealt round-robin over the 8 XCDs, one
 // XCD works on one split (nsplit | 8) and keeps that split's V in its L2.
 template <typename T, int RT, int NCT, int PF, int NT, int W = 4>
-__device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
-  static_assert((W == 4 || W == 8) && (4 * NCT) % W == 0, "waves per workgroup");
-  constexpr int VU = 4 * NCT / W;     // V rows each thread stages per step: 4 W rows at a time
+__device__ inline void tn_block(const TnArgs& a, int bid, TnStage<T, NCT>& vs) {
+  static_assert(W == 4 || W == 8, "waves per workgroup");
+  using Op = TnOperand<T>;
+  constexpr int kUnits = NCT * 16 / Op::kRows * Op::kParts;  // wave loads per step of V
+  constexpr int VU = (kUnits + W - 1) / W;                    // of them each wave's
   using Acc = typename TnTraits<T>::Acc;
   using Part = typename TnTraits<T>::Part;
   constexpr int kE = 16 / sizeof(T);  // elements per 16-byte piece
@@ -101,7 +162,9 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
   const int64_t kend = min(a.K, kb0 + a.klen);
   const int nsteps = kend > kb0 ? static_cast<int>((kend - kb0) / kStep) : 0;
   const T* M = static_cast<const T*>(a.M);
-  const T* V = static_cast<const T*>(a.V) + static_cast<int64_t>(cg) * NCT * 16 * a.ldv + kb0;
+  const int64_t vrow = a.ldv / kStep * Op::kStepBytes;  // bytes of one V row
+  const char* V = static_cast<const char*>(a.V) + static_cast<int64_t>(cg) * NCT * 16 * vrow +
+                  kb0 / kStep * Op::kStepBytes;
   const int64_t rb = rtile * 16 * W * RT + static_cast<int64_t>(wv) * 16 * RT;
 
   // Fragment-packed M: this wave's tile t of step s starts at
@@ -112,14 +175,179 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
 #pragma unroll
   for (int t = 0; t < RT; ++t)
     mrow[t] = M + (kb0 / kStep) * sstride + (rb + 16 * t) * kStep + lane * kE;
-  const int vr = threadIdx.x >> 4, vp = threadIdx.x & 15;
-  const T* vsrc = V + static_cast<int64_t>(vr) * a.ldv + vp * kE;
+  // Wave w stages the units w, w + W, ... of a step (the last round repeats a
+  // unit where they do not divide evenly): the unit's offset is uniform, a
+  // lane adds its row's and its chunk's.
+  const int vrl = lane / Op::kLanes, vcl = lane % Op::kLanes;
+  const uint32_t vlane = static_cast<uint32_t>(vrl * vrow) + 16 * vcl;
+  const int swv = __builtin_amdgcn_readfirstlane(wv);
+  int vunit[VU];
+#pragma unroll
+  for (int u = 0; u < VU; ++u) vunit[u] = min(swv + W * u, kUnits - 1);
 
   Acc acc[RT][NCT];
 #pragma unroll
   for (int t = 0; t < RT; ++t)
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) acc[t][ct] = Acc{};
+  // Units u0 .. u0 + n - 1 of the wave's share of a step of V.
+  auto load_v = [&](u32x4* vst, int step, int u0, int n) {
+    const char* src = V + static_cast<int64_t>(step) * Op::kStepBytes;
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+      const int w = vunit[u0 + u];
+      const char* unit = src + (w / Op::kParts) * (Op::kRows * vrow) + (w % Op::kParts) * 16 * Op::kLanes;
+      vst[u] = *reinterpret_cast<const u32x4*>(unit + vlane);
+    }
+  };
+  auto store_v = [&](const u32x4* vst, int buf, int u0, int n) {
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+      const int w = vunit[u0 + u];
+      vs.v[buf][(w / Op::kParts) * Op::kRows + vrl][(w % Op::kParts) * Op::kLanes + vcl] = vst[u];
+    }
+  };
+  // A split past the end of K (from rounding its length up to whole steps)
+  // writes zero partials.
+  if constexpr (sizeof(T) == 4) {
+    if (nsteps > 0) {
+      // A step is two phases (matrix products over 32 of its 64 columns).  In
+      // phase k the raw pieces of phase k + 1 are split while the products of
+      // phase k run, and those of phase k + R are loaded into the slot that
+      // phase k's were split from: R - 1 = 2 PF + 1 phases of M in flight.
+      // The loops are unrolled by the ring (PF + 1 steps), so every slot is a
+      // compile-time constant.  In the main loop every load is issued without
+      // a branch (a load behind one makes the compiler wait for all loads in
+      // flight where the paths join); the tail loads only what exists.  With
+      // two row tiles and 128 right-hand sides (or four) the tail's branches cost
+      // spilled registers: there the main loop runs to the end and a step past
+      // the split's end reloads its last one.
+      constexpr bool kTail = RT == 1 || (RT == 2 && NCT < 8);
+      constexpr int D = PF + 1, R = 2 * D;
+      // The next step of V is staged in two halves, one per phase, where its
+      // registers are short (128 right-hand sides; VU is even there).
+      constexpr int HV = NCT >= 8 ? 2 : 1, VH = VU / HV;
+      // Where the registers allow, the small products have sums of their own,
+      // added at the end: the large sums are then rounded once per 32 columns
+      // instead of six times (the error of long sums falls by about two).
+      constexpr bool kLow = RT * NCT <= 8;
+      Acc low[kLow ? RT : 1][kLow ? NCT : 1];
+#pragma unroll
+      for (auto& r : low)
+#pragma unroll
+        for (auto& v : r) v = Acc{};
+      u32x4 raw[R][RT][2], vst[VU];
+      Split3 ms[2][RT];
+      auto load_m = [&](u32x4 (&dst)[RT][2], int step, int q) {
+        const int64_t o = static_cast<int64_t>(step) * sstride;
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            const u32x4* src = reinterpret_cast<const u32x4*>(mrow[t] + o + (2 * q + p) * 64 * kE);
+            dst[t][p] = NT ? __builtin_nontemporal_load(src) : *src;
+          }
+      };
+      const int last = nsteps - 1;
+      load_v(vst, 0, 0, VU);
+#pragma unroll
+      for (int k = 0; k < R; ++k) load_m(raw[k], min(k / 2, last), k & 1);
+      store_v(vst, 0, 0, VU);
+#pragma unroll
+      for (int t = 0; t < RT; ++t) ms[0][t] = split8(raw[0][t][0], raw[0][t][1]);
+      __syncthreads();
+      auto step_body = [&](int step, int i, bool more, bool load_ahead) {
+        const int buf = step & 1;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int k = 2 * i + q;
+          // V before M: loads complete in order, so the wait for V leaves the
+          // M loads behind it in flight.
+          if (q < HV && more) load_v(vst, kTail ? step + 1 : min(step + 1, last), q * VH, VH);
+          __builtin_amdgcn_sched_barrier(0);
+          if (load_ahead) load_m(raw[k], kTail ? step + D : min(step + D, last), q);
+          __builtin_amdgcn_sched_barrier(0);
+          u32x4 vf[2][3];
+#pragma unroll
+          for (int e = 0; e < 3; ++e) vf[0][e] = vs.v[buf][li][8 * e + 4 * q + g];
+#pragma unroll
+          for (int t = 0; t < RT; ++t)
+            ms[q ^ 1][t] = split8(raw[(k + 1) % R][t][0], raw[(k + 1) % R][t][1]);
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) {
+            if (ct + 1 < NCT) {
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                vf[(ct + 1) & 1][e] = vs.v[buf][(ct + 1) * 16 + li][8 * e + 4 * q + g];
+            }
+            // The small products first.
+            const u32x4* v = vf[ct & 1];
+            auto mul = [&](u32x4 Split3::*part, const u32x4& b, bool small) {
+#pragma unroll
+              for (int t = 0; t < RT; ++t) {
+                if constexpr (kLow) {
+                  if (small) {
+                    mma_bf16(ms[q][t].*part, b, low[t][ct]);
+                    continue;
+                  }
+                }
+                mma_bf16(ms[q][t].*part, b, acc[t][ct]);
+              }
+            };
+            mul(&Split3::l, v[0], true);
+            mul(&Split3::h, v[2], true);
+            mul(&Split3::m, v[1], true);
+            mul(&Split3::m, v[0], true);
+            mul(&Split3::h, v[1], true);
+            mul(&Split3::h, v[0], false);
+          }
+          // Interleave: the next column tile's LDS reads and a share of the
+          // next phase's splitting between the products of each tile.
+          constexpr int kValu = (42 * RT + 3 * NCT - 1) / (3 * NCT);
+          __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) {
+            if (ct + 1 < NCT) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 2 * RT, 0);  // matrix products
+              __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);  // vector instructions
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (more && (HV == 2 || q == 1)) store_v(vst, buf ^ 1, HV == 2 ? q * VH : 0, VH);
+        }
+        __syncthreads();
+      };
+      int step0 = 0;
+      if constexpr (kTail) {
+        for (; step0 + D - 1 + D < nsteps; step0 += D) {
+#pragma unroll
+          for (int i = 0; i < D; ++i) step_body(step0 + i, i, true, true);
+        }
+        for (; step0 < nsteps; step0 += D) {
+#pragma unroll
+          for (int i = 0; i < D; ++i)
+            if (step0 + i < nsteps)
+              step_body(step0 + i, i, step0 + i + 1 < nsteps, step0 + i + D < nsteps);
+        }
+      } else {
+        for (; step0 < nsteps; step0 += D) {
+#pragma unroll
+          for (int i = 0; i < D; ++i) {
+            if (i > 0 && step0 + i >= nsteps) break;
+            step_body(step0 + i, i, true, true);
+          }
+        }
+      }
+      if constexpr (kLow) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) acc[t][ct] += low[t][ct];
+      }
+    }
+  } else {
   // Ring of PF + 1 register sets for M: the loads for step s + PF are issued
   // while step s computes.  The step loop is unrolled by the ring size so that
   // every slot index is a compile-time constant.
@@ -135,22 +363,14 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
         dst[t][p] = NT ? __builtin_nontemporal_load(src) : *src;
       }
   };
-  auto load_v = [&](int step) {
-    const int64_t o = static_cast<int64_t>(step) * kStep;
-#pragma unroll
-    for (int u = 0; u < VU; ++u)
-      vst[u] = *reinterpret_cast<const u32x4*>(vsrc + static_cast<int64_t>(4 * W * u) * a.ldv + o);
-  };
-  // A split past the end of K (from rounding its length up to whole steps)
-  // writes zero partials.  Otherwise every load below is issued without a
-  // branch, so that the compiler can count the loads in flight (see the main
-  // part); a step past the split's end is replaced by its last step.
+  // Every load below is issued without a branch, so that the compiler can
+  // count the loads in flight (see the main part); a step past the split's
+  // end is replaced by its last step.
   if (nsteps > 0) {
 #pragma unroll
   for (int s0 = 0; s0 < PF; ++s0) load_m(mr[s0], min(s0, nsteps - 1));
-  load_v(0);
-#pragma unroll
-  for (int u = 0; u < VU; ++u) vs[0][vr + 4 * W * u][vp] = vst[u];
+  load_v(vst, 0, 0, VU);
+  store_v(vst, 0, 0, VU);
   __syncthreads();
   // One step: V's next step and M's step + PF are loaded, step `step` is
   // multiplied from ring slot i, V's next step goes to the other LDS buffer.
@@ -159,7 +379,7 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
   // steps in flight.
   auto body = [&](int step, int i, bool more, bool load_ahead) {
     const int buf = step & 1;
-    if (more) load_v(step + 1);
+    if (more) load_v(vst, step + 1, 0, VU);
     if (load_ahead) load_m(mr[(i + PF) % D], step + PF);
     // Keep the loads at the top of the step: moved down among the products
     // they would be waited for as soon as they are issued.
@@ -168,17 +388,14 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
     for (int p = 0; p < 4; ++p) {
       u32x4 bf[NCT];
 #pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) bf[ct] = vs[buf][ct * 16 + li][4 * p + g];
+      for (int ct = 0; ct < NCT; ++ct) bf[ct] = vs.v[buf][ct * 16 + li][4 * p + g];
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct)
           mma_piece(mr[i][t][p], bf[ct], acc[t][ct], static_cast<T*>(nullptr));
     }
-    if (more) {
-#pragma unroll
-      for (int u = 0; u < VU; ++u) vs[buf ^ 1][vr + 4 * W * u][vp] = vst[u];
-    }
+    if (more) store_v(vst, buf ^ 1, 0, VU);
     __syncthreads();
   };
   // Main part: every step of the chunk has step + PF < nsteps, so both loads
@@ -199,6 +416,7 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<NCT>& vs) {
       if (step0 + i < nsteps) body(step0 + i, i, step0 + i + 1 < nsteps, step0 + i + PF < nsteps);
   }
   }  // nsteps > 0
+  }
 
   // Result layout: f32 accumulators hold D[4 g + q][li]; f64 ones D[g + 4 q][li].
   Part* part = static_cast<Part*>(a.part);
@@ -234,16 +452,6 @@ __device__ inline double split_sum(const P* part, int32_t nsplit, int64_t split_
   return static_cast<double>(s);
 }
 
-// out[c*ldo + r] = TQ(sum of the split partials) for element e = c * rows + r.
-template <typename P, typename TQ>
-__device__ inline void sum_cast_elem(const P* part, int32_t nsplit, int64_t ldp, int64_t rows,
-                                     int64_t stride, TQ* out, int64_t ldo, int64_t e) {
-  const int64_t c = e / rows, r = e - c * rows;
-  P s = part[c * ldp + r];
-  for (int sp = 1; sp < nsplit; ++sp) s += part[sp * stride + c * ldp + r];
-  out[c * ldo + r] = static_cast<TQ>(s);
-}
-
 // Four consecutive entries as one or two 16-byte accesses (8 bytes for bf16);
 // the address is a multiple of four entries, 16-byte aligned.
 template <typename T>
@@ -276,8 +484,28 @@ __device__ inline void store4(T* p, const T (&v)[4]) {
   }
 }
 
-// sum_cast_elem for the four entries e .. e + 3 (e, rows, ldp and ldo
-// multiples of 4: the four share one right-hand side).
+// Four consecutive entries j .. j + 3 (j % 4 == 0) of row c of a V operand of
+// row length ld (a multiple of the step): row-major, or split for FP32.
+template <typename TQ>
+__device__ inline void store_operand4(TQ* base, int64_t ld, int64_t c, int64_t j, const TQ (&v)[4]) {
+  if constexpr (sizeof(TQ) == 4) {
+    unsigned h[2], m[2], l[2];
+    split_pair(v[0], v[1], h[0], m[0], l[0]);
+    split_pair(v[2], v[3], h[1], m[1], l[1]);
+    const int kc = static_cast<int>(j >> 2) & 15;
+    char* d = reinterpret_cast<char*>(base) + (c * (ld >> 6) + (j >> 6)) * 384 +
+              64 * (kc >> 3) + 16 * (kc & 3) + 8 * ((kc >> 2) & 1);
+    *reinterpret_cast<uint2*>(d) = make_uint2(h[0], h[1]);
+    *reinterpret_cast<uint2*>(d + 128) = make_uint2(m[0], m[1]);
+    *reinterpret_cast<uint2*>(d + 256) = make_uint2(l[0], l[1]);
+  } else {
+    store4(base + c * ld + j, v);
+  }
+}
+
+// W's row c, entries r .. r + 3 as a V operand: the sum of the split partials
+// in split order, for e = c * rows + r (e, rows and ldp multiples of 4: the
+// four share one right-hand side).
 template <typename P, typename TQ>
 __device__ inline void sum_cast4(const P* part, int32_t nsplit, int64_t ldp, int64_t rows,
                                  int64_t stride, TQ* out, int64_t ldo, int64_t e) {
@@ -293,53 +521,14 @@ __device__ inline void sum_cast4(const P* part, int32_t nsplit, int64_t ldp, int
   TQ o[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) o[q] = static_cast<TQ>(s[q]);
-  store4(out + c * ldo + r, o);
+  store_operand4(out, ldo, c, r, o);
 }
 
 // The (y, x_bar) update, its start, or an anchor update (see TnUpdateArgs)
-// for element e = c * n + j.
-template <typename P, typename TQ>
-__device__ inline void update_elem(const TnUpdateArgs& a, int64_t e) {
-  const int64_t stride = static_cast<int64_t>(a.kp) * a.ldp;
-  const P* part = static_cast<const P*>(a.part);
-  TQ* yq = static_cast<TQ*>(a.yq);
-  const double g = a.gamma, omg = 1.0 - a.gamma, eta = a.eta, ome = 1.0 - a.eta;
-  const int64_t c = e / a.n, j = e - c * a.n;
-  const double z = split_sum(part, a.nsplit, stride, c * a.ldp + j);
-  const int64_t i = c * a.ldx + j;
-  if (a.mode == 1) {
-    const double x0 = z * a.inv_m;
-    a.x0[i] = x0;
-    a.xb[i] = x0;
-    a.y[i] = 0.0;
-    if (a.yref) {
-      a.yref[i] = 0.0;
-      a.uref[i] = 0.0;
-    }
-    yq[c * a.ldq + j] = cvt<TQ>(g * x0);
-    return;
-  }
-  const double xb = a.xb[i];
-  // y1 = (1 - gamma) y + gamma x_bar; an anchor update reads the copy its
-  // FP64 product was formed from.
-  const double y1 = a.mode == 2 ? a.yref[i] : omg * a.y[i] + g * xb;
-  double u = z * a.inv_m;
-  double ref = 0.0;
-  if (a.mode == 2) {  // z = m X y1 in FP64: new anchor
-    a.uref[i] = u;
-    ref = y1;
-  } else if (a.yref) {  // z = m X~ (y1 - y_ref)
-    u += a.uref[i];
-    ref = a.yref[i];
-  }
-  const double xn = eta * (a.x0[i] + y1 - u) + ome * xb;
-  a.y[i] = y1;
-  a.xb[i] = xn;
-  yq[c * a.ldq + j] = cvt<TQ>(omg * y1 + g * xn - ref);
-}
-
-// update_elem for the four entries e .. e + 3 (e, n, ldp, ldx and ldq
-// multiples of 4), the same arithmetic per entry.
+// for the four entries e .. e + 3, e = c * n + j (e, n, ldp, ldx and ldq
+// multiples of 4).  y1 = (1 - gamma) y + gamma x_bar; an anchor update (mode 2,
+// z = m X y1 in FP64) reads the copy y_ref its product was formed from and
+// becomes the new anchor, an update in between has z = m X~ (y1 - y_ref).
 template <typename P, typename TQ>
 __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
   const int64_t stride = static_cast<int64_t>(a.kp) * a.ldp;
@@ -371,7 +560,7 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
       store4(a.yref + i, zero);
       store4(a.uref + i, zero);
     }
-    store4(yq + c * a.ldq + j, qv);
+    store_operand4(yq, a.ldq, c, j, qv);
     return;
   }
   double xb[4], x0[4], y[4] = {0.0, 0.0, 0.0, 0.0}, yr[4] = {0.0, 0.0, 0.0, 0.0},
@@ -408,7 +597,7 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
   if (a.mode == 2) store4(a.uref + i, uo);
   store4(a.y + i, yo);
   store4(a.xb + i, xo);
-  store4(yq + c * a.ldq + j, qv);
+  store_operand4(yq, a.ldq, c, j, qv);
 }
 
 }  // namespace

@@ -1,0 +1,82 @@
+"""FP32 products of the k-RHS form on the bf16 matrix cores (operands split into three
+bf16 parts): one plain FP32 update against the FP64 oracle."""
+
+import math
+
+import numpy as np
+import pytest
+
+from oracle import apc_oracle as O
+from paper_1708_01413_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24  # FP32 unit roundoff
+
+
+def _torch():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _one_update(S, g, e):
+    Qt, R = O.factor(S.A, S.off)
+    x = O.init_local(Qt, R, S.B, S.off)
+    x0 = O.initial_average(x)
+    return x0, O.apc_step(Qt, x, x0, g, e)[1]
+
+
+# Row lengths around the 64-column step and the 256 padding, and right-hand sides around
+# every column-tile count (16, 32, 64, 128) and a second column group.
+@pytest.mark.parametrize("N,n,k,scale", [(64, 64, 2, 1.0), (65, 63, 16, 1.0), (130, 100, 17, 1.0),
+                                         (256, 256, 32, 1.0), (300, 200, 33, 1.0),
+                                         (257, 255, 64, 1.0), (192, 192, 65, 1.0),
+                                         (300, 256, 128, 1.0), (140, 129, 130, 1.0),
+                                         (200, 200, 24, 1e-30), (200, 200, 24, 1e30)])
+def test_one_fp32_update(N, n, k, scale):
+    """The inputs' rounding (C, y and W to FP32: 3 u) and the sums' (a random walk of at
+    most K = 256 roundings per product: sqrt(K) u) bound the error of X y, which the
+    update multiplies by eta: two products give 2 u (4 + sqrt(K)) eta ||X y|| / ||x_bar||.
+    Leaving out the third part of either operand would cost about 2^-16."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    S = synth.gaussian_system(N, n, 5, k=k, seed=3 * n + k, scale=1 / math.sqrt(n), shift=2.0)
+    S.B *= scale
+    g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+    x0, ref = _one_update(S, g, e)
+    plan = apc.Plan(torch.from_numpy(S.A).cuda(), torch.from_numpy(S.B).cuda(), S.off, "f32",
+                    gamma=g, eta=e, anchor_every=0)
+    plan.iterate(1)
+    got = plan.xbar().cpu().numpy()
+    # x_bar(1) = eta (x0 + y1 - X y1) + (1 - eta) x0 with y1 = gamma x0.
+    Xy = x0 + g * x0 - (ref - (1 - e) * x0) / e
+    amp = e * np.linalg.norm(Xy) / np.linalg.norm(ref)
+    dev = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    tol = 2 * U * (4 + math.sqrt(256)) * amp
+    print(f"N={N} n={n} k={k} scale={scale}: dev {dev:.2e} tol {tol:.2e}", flush=True)
+    assert dev <= tol
+
+
+@pytest.mark.parametrize("k", [100, 128])
+def test_mixed_batch_with_two_column_groups(k):
+    """128 padded right-hand sides next to a k = 1 system, three plain FP32 updates against
+    the oracle at the FP32 bar."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    big = synth.gaussian_system(320, 300, 6, k=k, seed=k, scale=1 / math.sqrt(300), shift=2.0)
+    small = synth.gaussian_system(90, 90, 4, seed=k + 1, scale=1 / math.sqrt(90), shift=2.0)
+    plans, refs = [], []
+    for S, kw in ((big, {"anchor_every": 0}), (small, {})):
+        g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+        refs.append(O.apc_run(S.A, S.B, S.off, T=3, gamma=g, eta=e, keep_traj=True)["traj"][3])
+        plans.append(apc.Plan(torch.from_numpy(S.A).cuda(), torch.from_numpy(S.B).cuda(), S.off,
+                              "f32", gamma=g, eta=e, **kw))
+    batch = apc.Batch(plans)
+    batch.iterate(3)
+    for S, p, ref in zip((big, small), plans, refs):
+        got = p.xbar().cpu().numpy().reshape(ref.shape)
+        dev = np.linalg.norm(got - ref) / np.linalg.norm(S.xstar)
+        print(f"k={k} n={S.n}: dev {dev:.2e}", flush=True)
+        assert dev <= 1e-5
+    batch.close()
