@@ -427,7 +427,8 @@ template <int NCT>
 __global__ __launch_bounds__(256, 2) void k_batch_mixed(const BatchSys* sys, const BatchGemm* gemm,
                                                      const int4* items, int32_t nitems,
                                                      const int32_t* active) {
-  constexpr size_t kTn = sizeof(TnStage<float, NCT>);  // the larger of the two
+  using T32 = std::conditional_t<NCT == 1, float, F32x3>;  // (tn_f32_type)
+  constexpr size_t kTn = sizeof(TnStage<T32, NCT>);  // at least TnStage<double, NCT>
   constexpr int kPf = NCT == 4 ? 1 : 2;
   constexpr size_t kRed = sizeof(float) * 4 * kBatchFusedCols;
   constexpr size_t kBytes = kTn > kRed ? kTn : kRed;
@@ -446,7 +447,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_mixed(const BatchSys* sys, con
       // (The FP64 contraction, an anchor update's, loads one step ahead: with
       // two the kernel's union of work kinds spilled registers.)
       if (kind == kItemTn32)
-        tn_block<float, 1, NCT, kPf, 1>(a, w.w, *reinterpret_cast<TnStage<float, NCT>*>(lds));
+        tn_block<T32, 1, NCT, kPf, 1>(a, w.w, *reinterpret_cast<TnStage<T32, NCT>*>(lds));
       else
         tn_block<double, 1, NCT, 1, 0>(a, w.w, *reinterpret_cast<TnStage<double, NCT>*>(lds));
       __syncthreads();
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_mixed(const BatchSys* sys, con
         for (int64_t e = e0 + 4 * threadIdx.x; e < e1; e += 4 * 256) {
           if (kind == kItemSum32)
             sum_cast4(static_cast<const float*>(G.sum_part), G.sum_nsplit[0], G.sum_ldp, G.sum_rows,
-                      stride, static_cast<float*>(G.sum_out[0]), G.sum_ldo, e);
+                      stride, static_cast<T32*>(G.sum_out[0]), G.sum_ldo, e);
           else
             sum_cast4(static_cast<const double*>(G.sum_part), G.sum_nsplit[1], G.sum_ldp,
                       G.sum_rows, stride, static_cast<double*>(G.sum_out[1]), G.sum_ldo, e);
@@ -472,8 +473,8 @@ __global__ __launch_bounds__(256, 2) void k_batch_mixed(const BatchSys* sys, con
         const TnUpdateArgs& u = G.upd[kind == kItemUpd64 ? 1 : 0];
         const int64_t e1 = min(static_cast<int64_t>(u.kp) * u.n, e0 + kBatchChunk);
         for (int64_t e = e0 + 4 * threadIdx.x; e < e1; e += 4 * 256) {
-          if (kind == kItemUpd32) update4<float, float>(u, e);
-          else update4<double, float>(u, e);
+          if (kind == kItemUpd32) update4<float, T32>(u, e);
+          else update4<double, T32>(u, e);
         }
       } else if (kind == kItemAnchorVec) {
         const int64_t e1 = min(G.state_count, e0 + kBatchChunk);

@@ -58,6 +58,12 @@ namespace apc {
 
 namespace {
 
+inline bool quad_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+inline bool update_args_ok(const TnUpdateArgs& a) {
+  return a.n % 4 == 0 && a.ldx % 4 == 0 && a.ldq % 4 == 0 && quad_ok(a.x0) && quad_ok(a.y) &&
+         quad_ok(a.xb) && quad_ok(a.yq) && (!a.yref || (quad_ok(a.yref) && quad_ok(a.uref)));
+}
+
 template <typename T, int RT, int NCT, int PF, int NT, int W>
 __global__ __launch_bounds__(64 * W) void k_tn(TnArgs a) {
   __shared__ TnStage<T, NCT> vs;
@@ -70,15 +76,23 @@ hipError_t tn_nct_w(const TnArgs& a, hipStream_t s) {
   const int64_t ncg = a.kp / (16 * nct);
   const int64_t blocks = (a.rows / (16 * W * RT)) * ncg * a.nsplit;
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * W);
-  switch (nct) {
-    case 1:
-      if constexpr (W == 4) APC_LAUNCH((k_tn<T, RT, 1, PF, NT, W>), grid, block, 0, s, a);
-      else return hipErrorInvalidValue;
-      break;
-    case 2: APC_LAUNCH((k_tn<T, RT, 2, PF, NT, W>), grid, block, 0, s, a); break;
-    case 4: APC_LAUNCH((k_tn<T, RT, 4, PF, NT, W>), grid, block, 0, s, a); break;
-    case 8: APC_LAUNCH((k_tn<T, RT, 8, PF, NT, W>), grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
+  // FP32: the matrix instructions of its own with 16 right-hand sides only.
+  constexpr bool kOne = !TnOperand<T>::kSplit, kMore = !std::is_same_v<T, float>;
+  if constexpr (kOne && W == 4) {
+    if (nct == 1) {
+      APC_LAUNCH((k_tn<T, RT, 1, PF, NT, W>), grid, block, 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (kMore) {
+    switch (nct) {
+      case 2: APC_LAUNCH((k_tn<T, RT, 2, PF, NT, W>), grid, block, 0, s, a); break;
+      case 4: APC_LAUNCH((k_tn<T, RT, 4, PF, NT, W>), grid, block, 0, s, a); break;
+      case 8: APC_LAUNCH((k_tn<T, RT, 8, PF, NT, W>), grid, block, 0, s, a); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -90,7 +104,7 @@ hipError_t tn_nct_w(const TnArgs& a, hipStream_t s) {
 template <typename T, int RT, int PF, int NT>
 hipError_t tn_nct(const TnArgs& a, hipStream_t s) {
   if (a.waves == 8) {
-    if constexpr (sizeof(T) <= 4 && (RT == 1 || (RT == 2 && PF <= 2)) && NT == 1)
+    if constexpr (sizeof(T) <= 4 && !std::is_same_v<T, float> && (RT == 1 || (RT == 2 && PF <= 2)) && NT == 1)
       return tn_nct_w<T, RT, PF, NT, 8>(a, s);
     else
       return hipErrorInvalidValue;
@@ -136,6 +150,204 @@ hipError_t tn_pf(int rt, int pf, const TnArgs& a, hipStream_t s) {
   }
 }
 
+// ------------------------------------------------------------------ few rows per workgroup
+//
+// The same contraction for small operands: a workgroup owns 16 rows and 16 NCT
+// right-hand sides and its eight waves take every eighth step of K, so it
+// holds whole sums -- added in LDS in wave order -- and applies the epilogue
+// that k_tn leaves to a launch of its own: one launch per pass instead of two
+// and no partials in memory.  Nothing is shared through LDS before that: every
+// wave loads its steps of V itself, in the lanes' order, so each 16 rows read
+// all of their column group's V from L2.  That bounds it (~15 TB/s of L2
+// reads): an update of two passes takes 15.7 us at 1024^2, k = 8 (two k_tn
+// pairs: 15.9), 16.9 us at 1000^2, k = 40 (21.6), 14.8 us at 512^2, k = 128
+// (22.1), in FP64 13.7 us there (35.1); at 4096^2, k = 16 it is behind (37
+// against 33 us).  The tuner times both and takes the cheaper with its epilogue.
+// Loads go through buffer descriptors whose size is zero past a wave's last
+// step: they return zeros and fetch nothing, so the loop needs no branch
+// around a load and no tail.
+enum KsEpilogue { kKsPartial = 0, kKsOperand = 1, kKsUpdate = 2, kKsAdjoint = 3 };
+constexpr int kKsWaves = 8;
+
+__device__ inline u32x4 ks_load(const void* base, uint32_t bytes, uint32_t off) {
+  const __amdgpu_buffer_rsrc_t r =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(bytes), 0x00027000);
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(off), 0, 0));
+}
+
+template <typename T, typename TQ, int NCT, int EPI>
+__global__ __launch_bounds__(64 * kKsWaves) void k_tn_ks(TnArgs a, TnKsEpilogue ep) {
+  using Acc = typename TnTraits<T>::Acc;
+  using Part = typename TnTraits<T>::Part;
+  using Op = TnOperand<T>;
+  constexpr bool kF32 = Op::kSplit;
+  constexpr int kE = 16 / sizeof(T), kStep = 16 * kE;
+  // 16-byte pieces of a step per lane: four of M, VP of each column tile of V
+  // (consecutive 64-byte pieces of its rows, so that both halves of a cache
+  // line are asked for together); D steps in flight.
+  constexpr int VP = Op::kStepBytes / 64;
+  constexpr int D = kF32 && NCT == 2 ? 2 : 3;
+  // (rows / 16 x column groups workgroups: 32-bit arithmetic)
+  const uint32_t tiles = static_cast<uint32_t>(a.rows) / 16;
+  const uint32_t cg = blockIdx.x / tiles, rt = blockIdx.x - cg * tiles;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, g = lane >> 4;
+  const int nsteps = static_cast<int>(static_cast<uint64_t>(a.K) / kStep);
+  const int mine = wv < nsteps ? (nsteps - wv + kKsWaves - 1) / kKsWaves : 0;
+  const int64_t vrow = static_cast<int64_t>(static_cast<uint64_t>(a.ldv) / kStep) * Op::kStepBytes;
+  const char* M = static_cast<const char*>(a.M) + static_cast<int64_t>(rt) * 4096;
+  const char* V = static_cast<const char*>(a.V) + static_cast<int64_t>(cg) * NCT * 16 * vrow;
+  const uint32_t vbytes = static_cast<uint32_t>(NCT * 16 * vrow);
+  const uint32_t vlane = static_cast<uint32_t>(li * vrow) + 16 * g;
+
+  // The epilogue's four entries of this thread (the first 64 NCT threads):
+  // column ec, rows ej .. ej + 3.  Its state is loaded first, behind nothing.
+  const bool eth = threadIdx.x < 64 * NCT;
+  const int ect = (threadIdx.x >> 6) % NCT, eli = (threadIdx.x >> 2) & 15, eg = threadIdx.x & 3;
+  const int64_t ec = static_cast<int64_t>(cg) * NCT * 16 + ect * 16 + eli,
+                ej = static_cast<int64_t>(rt) * 16 + 4 * eg;
+  UpdateState us;
+  AdjointState as;
+  if constexpr (EPI == kKsOperand) asm volatile("" ::"s"(ep.out), "s"(ep.ldo));
+  if constexpr (EPI == kKsUpdate) {
+    // The arguments used after the products are read here too: read there,
+    // each would wait for a cold line of the argument buffer.
+    asm volatile("" ::"s"(ep.upd.yq), "s"(ep.upd.ldq), "s"(ep.upd.gamma), "s"(ep.upd.eta),
+                 "s"(ep.upd.inv_m), "s"(ep.upd.y));
+    update_load<true>(ep.upd, ec, ej, us);  // (threads past the first repeat their entries)
+  }
+  if constexpr (EPI == kKsAdjoint) {
+    asm volatile("" ::"s"(ep.adj.bq), "s"(ep.adj.ldq), "s"(ep.adj.gamma), "s"(ep.adj.eta),
+                 "s"(ep.adj.inv_m), "s"(ep.adj.red));
+    adjoint_load(ep.adj, ec, ej, as);
+  }
+
+  u32x4 mr[D][4], vr[D][NCT][VP];
+  auto load = [&](int slot, int i) {
+    const int step = wv + kKsWaves * i;
+    const bool in = i < mine;
+    const char* m = M + static_cast<int64_t>(step) * tiles * 4096;
+    const char* v = V + static_cast<int64_t>(step) * Op::kStepBytes;
+    const uint32_t vin = in ? vbytes - static_cast<uint32_t>(step) * Op::kStepBytes : 0;
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+      for (int e = 0; e < VP; ++e)
+        vr[slot][ct][e] = ks_load(v, vin, static_cast<uint32_t>(ct * 16 * vrow) + vlane + 64 * e);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mr[slot][e] = ks_load(m, in ? 4096 : 0, e * 1024 + lane * 16);
+  };
+  Acc acc[NCT], low[NCT];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) acc[ct] = low[ct] = Acc{};
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    load(k, k);
+    // In slot order here too: the loop's first wait counts the loads behind it.
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  for (int i0 = 0; i0 < mine; i0 += D) {
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      if constexpr (kF32) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const Split3 ms = split8(mr[k][2 * q], mr[k][2 * q + 1]);
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) {
+            // Pieces in memory order: part e's half q at 2 e + q.
+            const u32x4 vh = vr[k][ct][q], vm = vr[k][ct][2 + q], vl = vr[k][ct][4 + q];
+            mma_bf16(ms.l, vh, low[ct]);
+            mma_bf16(ms.h, vl, low[ct]);
+            mma_bf16(ms.m, vm, low[ct]);
+            mma_bf16(ms.m, vh, low[ct]);
+            mma_bf16(ms.h, vm, low[ct]);
+            mma_bf16(ms.h, vh, acc[ct]);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct)
+            mma_piece(mr[k][p], vr[k][ct][p], acc[ct], static_cast<T*>(nullptr));
+      }
+      load(k, i0 + k + D);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if constexpr (kF32) {
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) acc[ct] += low[ct];
+  }
+
+  // red[wave][column][row]: f32 accumulators hold rows 4 g + q, f64 ones g + 4 q.
+  constexpr int kRow = sizeof(Part) == 8 ? 17 : 16;
+  __shared__ __align__(16) Part red[kKsWaves][NCT * 16][kRow];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      red[wv][ct * 16 + li][sizeof(Part) == 8 ? g + 4 * q : 4 * g + q] = acc[ct][q];
+  }
+  __syncthreads();
+  Part z[4] = {Part(0), Part(0), Part(0), Part(0)};
+  if (eth) {
+#pragma unroll
+    for (int w = 0; w < kKsWaves; ++w)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) z[q] += red[w][ect * 16 + eli][4 * eg + q];
+  }
+  const double zd[4] = {static_cast<double>(z[0]), static_cast<double>(z[1]),
+                        static_cast<double>(z[2]), static_cast<double>(z[3])};
+  if constexpr (EPI == kKsPartial) {
+    if (eth) store4(static_cast<Part*>(a.part) + ec * a.ldp + ej, z);
+  } else if constexpr (EPI == kKsOperand) {
+    if (eth) {
+      TQ o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = TQ(z[q]);
+      store_operand4(static_cast<TQ*>(ep.out), ep.ldo, ec, ej, o);
+    }
+  } else if constexpr (EPI == kKsUpdate) {
+    if (eth) update_quad<TQ>(ep.upd, ec, ej, us, zd);
+  } else {
+    // dL/dgamma and dL/deta: wave sums, then the waves' in order.
+    double sg = 0.0, se = 0.0;
+    if (eth) adjoint_quad<TQ>(ep.adj, ec, ej, as, zd, sg, se);
+    __shared__ double rs[2][NCT];
+    if (wv < NCT) {
+      sg = wave_sum_dpp(sg);
+      se = wave_sum_dpp(se);
+      if (lane == 0) {
+        rs[0][wv] = sg;
+        rs[1][wv] = se;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double tg = rs[0][0], te = rs[1][0];
+#pragma unroll
+      for (int w = 1; w < NCT; ++w) {
+        tg += rs[0][w];
+        te += rs[1][w];
+      }
+      ep.adj.red[2 * blockIdx.x] += tg;
+      ep.adj.red[2 * blockIdx.x + 1] += te / ep.adj.eta;
+    }
+  }
+}
+
+template <typename T, typename TQ, int EPI>
+hipError_t tn_ks_nct(int nct, const TnArgs& a, const TnKsEpilogue& ep, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>((a.rows / 16) * (a.kp / (16 * nct)))), block(64 * kKsWaves);
+  if (nct == 1) APC_LAUNCH((k_tn_ks<T, TQ, 1, EPI>), grid, block, 0, s, a, ep);
+  else if constexpr (!std::is_same_v<T, float>) APC_LAUNCH((k_tn_ks<T, TQ, 2, EPI>), grid, block, 0, s, a, ep);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ epilogues
 
 // The (y, x_bar) update, its start, or an anchor update; see TnUpdateArgs.
@@ -159,8 +371,6 @@ __global__ __launch_bounds__(256) void k_tn_sum_cast4(const P* part, int32_t nsp
        e += static_cast<int64_t>(gridDim.x) * blockDim.x)
     sum_cast4(part, nsplit, ldp, rows, stride, out, ldo, 4 * e);
 }
-
-inline bool quad_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // y_ref = (1 - gamma) y + gamma x_bar (the vector the next update multiplies), FP64.
 __global__ __launch_bounds__(256) void k_tn_anchor_vec(const double* y, const double* xb, int64_t count,
@@ -198,7 +408,7 @@ __global__ __launch_bounds__(256) void k_tn_operand(const double* src, int64_t l
     const int64_t c = e / ldd, j = e - c * ldd;
     TQ q[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = j + u < cols ? cvt<TQ>(src[c * lds + j + u]) : TQ(0);
+    for (int u = 0; u < 4; ++u) q[u] = j + u < cols ? cvt<TQ>(src[c * lds + j + u]) : cvt<TQ>(0.0);
     store_operand4(dst, ldd, c, j, q);
   }
 }
@@ -211,13 +421,10 @@ __global__ __launch_bounds__(256) void k_tn_adjoint(TnAdjointArgs a) {
   const int64_t total = static_cast<int64_t>(a.kp) * a.n;
   const int64_t stride = static_cast<int64_t>(a.kp) * a.ldp;
   const P* part = static_cast<const P*>(a.part);
-  TQ* bq = static_cast<TQ*>(a.bq);
-  const double g = a.gamma, eta = a.eta;
   double sg = 0.0, se = 0.0;
   for (int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x); e < total;
        e += 4 * static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const int64_t c = e / a.n, j = e - c * a.n;
-    const int64_t i = c * a.ldx + j;
     P zs[4];
     load4(part + c * a.ldp + j, zs);
     for (int sp = 1; sp < a.nsplit; ++sp) {
@@ -226,30 +433,11 @@ __global__ __launch_bounds__(256) void k_tn_adjoint(TnAdjointArgs a) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) zs[q] += t[q];
     }
-    double av[4], bv[4], gv[4], yv[4], xv[4], nv[4];
-    load4(a.a + i, av);
-    load4(a.bh + i, bv);
-    load4(a.g0 + i, gv);
-    load4(a.y_t + i, yv);
-    load4(a.xb_t + i, xv);
-    load4(a.xb_next + i, nv);
-    TQ qv[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const double xbh = static_cast<double>(zs[q]) * a.inv_m;  // X b
-      const double bh = bv[q];
-      const double at = av[q] + eta * (bh - xbh);
-      sg += at * (xv[q] - yv[q]);
-      se += bh * (nv[q] - xv[q]);
-      gv[q] += eta * bh;
-      av[q] = (1.0 - g) * at;
-      bv[q] = (1.0 - eta) * bh + g * at;
-      qv[q] = cvt<TQ>(bv[q]);
-    }
-    store4(a.g0 + i, gv);
-    store4(a.a + i, av);
-    store4(a.bh + i, bv);
-    store_operand4(bq, a.ldq, c, j, qv);
+    AdjointState s;
+    adjoint_load(a, c, j, s);
+    const double z[4] = {static_cast<double>(zs[0]), static_cast<double>(zs[1]),
+                         static_cast<double>(zs[2]), static_cast<double>(zs[3])};
+    adjoint_quad<TQ>(a, c, j, s, z, sg, se);
   }
   __shared__ double rs[2][256];
   rs[0][threadIdx.x] = sg;
@@ -264,7 +452,7 @@ __global__ __launch_bounds__(256) void k_tn_adjoint(TnAdjointArgs a) {
   }
   if (threadIdx.x == 0) {
     a.red[2 * blockIdx.x] += rs[0][0];
-    a.red[2 * blockIdx.x + 1] += rs[1][0] / eta;
+    a.red[2 * blockIdx.x + 1] += rs[1][0] / a.eta;
   }
 }
 
@@ -483,12 +671,98 @@ hipError_t launch_tn(int type, int rt, int pf, const TnArgs& a, hipStream_t s) {
   switch (type) {
     case kTnF64: return tn_pf<double>(rt, pf, a, s);
     case kTnF32: return tn_pf<float>(rt, pf, a, s);
+    case kTnF32x3: return tn_pf<F32x3>(rt, pf, a, s);
     case kTnBF16: return tn_pf<__bf16>(rt, pf, a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-int tn_step_elems(int type) { return type == kTnF64 ? 32 : type == kTnF32 ? 64 : 128; }
+bool tn_ks_ok(int type, int nct, const TnArgs& a) {
+  // 16-row tiles and whole column groups; 32-bit offsets into V.
+  return (nct == 1 || (nct == 2 && type != kTnF32)) && a.kp % (16 * nct) == 0 && a.rows % 16 == 0 && a.rows > 0 &&
+         a.K % tn_step_elems(type) == 0 && a.ldv % tn_step_elems(type) == 0 &&
+         tn_operand_bytes(type, 16 * nct, a.ldv) < (int64_t(1) << 31) &&
+         (a.rows / 16) * (a.kp / 16) < (int64_t(1) << 30);
+}
+
+hipError_t launch_tn_ks(int type, int nct, const TnArgs& a, hipStream_t s) {
+  if (!tn_ks_ok(type, nct, a) || !quad_ok(a.part) || a.ldp % 4) return hipErrorInvalidValue;
+  const TnKsEpilogue ep{};
+  switch (type) {
+    case kTnF64: return tn_ks_nct<double, double, kKsPartial>(nct, a, ep, s);
+    case kTnF32: return tn_ks_nct<float, float, kKsPartial>(nct, a, ep, s);
+    case kTnF32x3: return tn_ks_nct<F32x3, F32x3, kKsPartial>(nct, a, ep, s);
+    case kTnBF16: return tn_ks_nct<__bf16, __bf16, kKsPartial>(nct, a, ep, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_tn_ks_operand(int type, int nct, const TnArgs& a, void* out, int64_t ldo,
+                                hipStream_t s) {
+  if (!tn_ks_ok(type, nct, a) || ldo % tn_step_elems(type) || ldo < a.rows || !quad_ok(out))
+    return hipErrorInvalidValue;
+  TnKsEpilogue ep{};
+  ep.out = out;
+  ep.ldo = ldo;
+  switch (type) {
+    case kTnF64: return tn_ks_nct<double, double, kKsOperand>(nct, a, ep, s);
+    case kTnF32: return tn_ks_nct<float, float, kKsOperand>(nct, a, ep, s);
+    case kTnF32x3: return tn_ks_nct<F32x3, F32x3, kKsOperand>(nct, a, ep, s);
+    case kTnBF16: return tn_ks_nct<__bf16, __bf16, kKsOperand>(nct, a, ep, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_tn_ks_update(int type, int nct, const TnArgs& a, int type_q, const TnUpdateArgs& u,
+                               hipStream_t s) {
+  if (!tn_ks_ok(type, nct, a) || !update_args_ok(u) || u.n != a.rows || u.kp != a.kp)
+    return hipErrorInvalidValue;
+  TnKsEpilogue ep{};
+  ep.upd = u;
+  switch (type) {
+    case kTnF64:
+      switch (type_q) {
+        case kTnF64: return tn_ks_nct<double, double, kKsUpdate>(nct, a, ep, s);
+        case kTnF32: return tn_ks_nct<double, float, kKsUpdate>(nct, a, ep, s);
+        case kTnF32x3: return tn_ks_nct<double, F32x3, kKsUpdate>(nct, a, ep, s);
+        case kTnBF16: return tn_ks_nct<double, __bf16, kKsUpdate>(nct, a, ep, s);
+        default: return hipErrorInvalidValue;
+      }
+    case kTnF32:
+      switch (type_q) {
+        case kTnF32: return tn_ks_nct<float, float, kKsUpdate>(nct, a, ep, s);
+        case kTnBF16: return tn_ks_nct<float, __bf16, kKsUpdate>(nct, a, ep, s);
+        default: return hipErrorInvalidValue;
+      }
+    case kTnF32x3:
+      switch (type_q) {
+        case kTnF32x3: return tn_ks_nct<F32x3, F32x3, kKsUpdate>(nct, a, ep, s);
+        case kTnBF16: return tn_ks_nct<F32x3, __bf16, kKsUpdate>(nct, a, ep, s);
+        default: return hipErrorInvalidValue;
+      }
+    case kTnBF16:
+      return type_q == kTnBF16 ? tn_ks_nct<__bf16, __bf16, kKsUpdate>(nct, a, ep, s)
+                               : hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_tn_ks_adjoint(int type, int nct, const TnArgs& a, const TnAdjointArgs& d,
+                                hipStream_t s) {
+  if (!tn_ks_ok(type, nct, a) || d.n != a.rows || d.kp != a.kp || d.ldx % 4 ||
+      (a.rows / 16) * (a.kp / (16 * nct)) > kTnAdjointBlocks)
+    return hipErrorInvalidValue;
+  TnKsEpilogue ep{};
+  ep.adj = d;
+  switch (type) {
+    case kTnF64: return tn_ks_nct<double, double, kKsAdjoint>(nct, a, ep, s);
+    case kTnF32: return tn_ks_nct<float, float, kKsAdjoint>(nct, a, ep, s);
+    case kTnF32x3: return tn_ks_nct<F32x3, F32x3, kKsAdjoint>(nct, a, ep, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+int tn_step_elems(int type) { return type == kTnF64 ? 32 : type == kTnBF16 ? 128 : 64; }
 
 hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_t kp, int64_t ldp,
                               int64_t rows, void* out, int64_t ldo, hipStream_t s) {
@@ -500,6 +774,7 @@ hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_
   switch (type) {
     case kTnF64: APC_SUM_CAST(double, double); break;
     case kTnF32: APC_SUM_CAST(float, float); break;
+    case kTnF32x3: APC_SUM_CAST(float, F32x3); break;
     case kTnBF16: APC_SUM_CAST(float, __bf16); break;
     default: return hipErrorInvalidValue;
   }
@@ -508,22 +783,21 @@ hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_
 }
 
 hipError_t launch_tn_update(int type, int part_f64, const TnUpdateArgs& a, hipStream_t s) {
-  if (a.n % 4 || a.ldp % 4 || a.ldx % 4 || a.ldq % 4 || !quad_ok(a.part) || !quad_ok(a.x0) ||
-      !quad_ok(a.y) || !quad_ok(a.xb) || !quad_ok(a.yq) ||
-      (a.yref && (!quad_ok(a.yref) || !quad_ok(a.uref))))
-    return hipErrorInvalidValue;
+  if (!update_args_ok(a) || a.ldp % 4 || !quad_ok(a.part)) return hipErrorInvalidValue;
   const unsigned g = grid_stride_blocks(static_cast<int64_t>(a.kp) * a.n / 4);
 #define APC_UPDATE(P, TQ) APC_LAUNCH((k_tn_update4<P, TQ>), dim3(g), dim3(256), 0, s, a)
   if (part_f64) {
     switch (type) {
       case kTnF64: APC_UPDATE(double, double); break;
       case kTnF32: APC_UPDATE(double, float); break;
+      case kTnF32x3: APC_UPDATE(double, F32x3); break;
       case kTnBF16: APC_UPDATE(double, __bf16); break;
       default: return hipErrorInvalidValue;
     }
   } else {
     switch (type) {
       case kTnF32: APC_UPDATE(float, float); break;
+      case kTnF32x3: APC_UPDATE(float, F32x3); break;
       case kTnBF16: APC_UPDATE(float, __bf16); break;
       default: return hipErrorInvalidValue;
     }
@@ -546,6 +820,7 @@ hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t c
   switch (type) {
     case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<double*>(yq)); break;
     case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<float*>(yq)); break;
+    case kTnF32x3: k_tn_prep<F32x3><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<F32x3*>(yq)); break;
     case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<__bf16*>(yq)); break;
     default: return hipErrorInvalidValue;
   }
@@ -559,6 +834,7 @@ hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t r
   switch (type) {
     case kTnF64: k_tn_operand<double><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<double*>(dst), ldd); break;
     case kTnF32: k_tn_operand<float><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<float*>(dst), ldd); break;
+    case kTnF32x3: k_tn_operand<F32x3><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<F32x3*>(dst), ldd); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -570,6 +846,7 @@ hipError_t launch_tn_adjoint(int type, const TnAdjointArgs& a, hipStream_t s) {
   switch (type) {
     case kTnF64: k_tn_adjoint<double, double><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;
     case kTnF32: k_tn_adjoint<float, float><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;
+    case kTnF32x3: k_tn_adjoint<float, F32x3><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -627,6 +904,8 @@ hipError_t launch_tn_pack_frag_multi(int type, const double* src, int64_t lds, i
                                      int64_t scols, int32_t transpose, void* dst, int64_t K,
                                      int64_t rows, void* d2, int type2, float* r32, int64_t ldr,
                                      int64_t r32rows, int64_t r32cols, hipStream_t s) {
+  if (type == kTnF32x3) type = kTnF32;  // M is stored the same
+  if (type2 == kTnF32x3) type2 = kTnF32;
   if (rows % 16 || K % tn_step_elems(type)) return hipErrorInvalidValue;
   if (d2 && (type2 == type || (type2 != kTnF64 && type2 != kTnF32) || K % tn_step_elems(type2)))
     return hipErrorInvalidValue;

@@ -237,7 +237,7 @@ Layout make_layout(int64_t N, int64_t n, const int64_t* off, int32_t m, int32_t 
   // bf16: C^T in FP32 for the inner solves' starts (x_bar(0) = (1/m) C^T c).
   L.C32T = take(bf ? L.np * L.Np * 4 : 0);
   L.Apad = take(gemm ? L.Np * L.np * d : 0);
-  const int tq = prec == APC_F64 ? kTnF64 : prec == APC_F32 ? kTnF32 : kTnBF16;
+  const int tq = prec == APC_F64 ? kTnF64 : prec == APC_F32 ? tn_f32_type(kp) : kTnBF16;
   L.yq = take(gemm ? tn_operand_bytes(tq, kp, L.np) : 0);
   // (An FP32 iteration's W shares the FP64 W's slice below: an update forms
   // one or the other and reads it right after.)
@@ -402,6 +402,9 @@ struct TnChoice {
   int pf = 1;      // steps of the streamed operand loaded ahead
   int nt = 1;      // non-temporal loads of the streamed operand
   int waves = 4;   // waves per workgroup (rows per workgroup = 16 waves rt)
+  int ks = 0;      // 1, 2: k_tn_ks with 16 ks right-hand sides per workgroup (16 rows, nsplit 1)
+  int plain_nsplit = 1;  // the best split of k_tn (a mixed batch's contraction tiles)
+  int rows_per_wg() const { return ks ? 16 : 16 * waves * rt; }
 };
 
 struct apc_plan_s {
@@ -711,6 +714,11 @@ TnArgs tn_args(const void* M, int64_t ldm, int64_t rows, const void* V, int64_t 
   return a;
 }
 
+// One contraction in its chosen shape, its partials left in args.part.
+hipError_t launch_choice(int type, const TnChoice& ch, const TnArgs& a, hipStream_t s) {
+  return ch.ks ? launch_tn_ks(type, ch.ks, a, s) : launch_tn(type, ch.rt, ch.pf, a, s);
+}
+
 TnArgs pass_a_args(const apc_plan_s* P) {
   const Layout& L = P->L;
   return tn_args(P->ws + L.Cq, L.np, L.Np, P->ws + L.yq, L.np, P->kp, L.np, P->tnA, P->tq,
@@ -726,7 +734,7 @@ TnArgs pass_b_args(const apc_plan_s* P) {
 // need the start to a relative 1e-7 or so (the FP64 residual of the
 // refinement corrects the rest); its operand c then sits in the same slice
 // as FP32.
-int x0_type(const apc_plan_s* P) { return P->bf16 ? kTnF32 : kTnF64; }
+int x0_type(const apc_plan_s* P) { return P->bf16 ? tn_f32_type(P->kp) : kTnF64; }
 TnArgs x0_args(const apc_plan_s* P) {
   const Layout& L = P->L;
   const void* Mt = P->tq == kTnF64 ? P->ws + L.CqT : P->bf16 ? P->ws + L.C32T : P->ws + L.C64T;
@@ -795,6 +803,39 @@ apc_status timed_done(apc_plan_s* P, hipEvent_t* ev, int e) {
   return APC_OK;
 }
 
+// Pass A and its split sum: W (a V operand of type `type`, rows of Np) from the
+// contraction a; in one launch when the shape holds whole sums.
+apc_status pass_a_w(apc_plan_s* P, int type, const TnChoice& ch, const TnArgs& a, void* W,
+                    hipEvent_t* ev = nullptr, int* kinds = nullptr, int* e = nullptr) {
+  const int64_t Np = P->L.Np;
+  time_next(P, ev, kinds, e, 0);
+  if (ch.ks) {
+    HIP_TRY(launch_tn_ks_operand(type, ch.ks, a, W, Np, P->stream));
+    return timed_done(P, ev, e ? *e : 0);
+  }
+  HIP_TRY(launch_tn(type, ch.rt, ch.pf, a, P->stream));
+  ST_TRY(timed_done(P, ev, e ? *e : 0));
+  time_next(P, ev, kinds, e, 2);
+  HIP_TRY(launch_tn_sum_cast(type, a.part, ch.nsplit, P->kp, Np, Np, W, Np, P->stream));
+  return timed_done(P, ev, e ? *e : 0);
+}
+
+// Pass B and the (y, x_bar) step (mode as TnUpdateArgs) on its sums.
+apc_status pass_b_update(apc_plan_s* P, int type, const TnChoice& ch, const TnArgs& a, int mode,
+                         hipEvent_t* ev = nullptr, int* kinds = nullptr, int* e = nullptr) {
+  const TnUpdateArgs u = update_args(P, ch, mode);
+  time_next(P, ev, kinds, e, 1);
+  if (ch.ks) {
+    HIP_TRY(launch_tn_ks_update(type, ch.ks, a, P->tq, u, P->stream));
+    return timed_done(P, ev, e ? *e : 0);
+  }
+  HIP_TRY(launch_tn(type, ch.rt, ch.pf, a, P->stream));
+  ST_TRY(timed_done(P, ev, e ? *e : 0));
+  time_next(P, ev, kinds, e, 2);
+  HIP_TRY(launch_tn_update(P->tq, type == kTnF64, u, P->stream));
+  return timed_done(P, ev, e ? *e : 0);
+}
+
 apc_status update_gemm(apc_plan_s* P, hipEvent_t* ev, int* kinds, int* nev) {
   const Layout& L = P->L;
   int e = 0;
@@ -806,37 +847,15 @@ apc_status update_gemm(apc_plan_s* P, hipEvent_t* ev, int* kinds, int* nev) {
                                  P->at<double>(L.yref), P->stream));
     TnArgs a = tn_args(P->ws + L.C64p, L.np, L.Np, P->ws + L.yref, L.np, P->kp, L.np, P->tnR,
                        kTnF64, part, L.Np);
-    time_next(P, ev, kinds, &e, 0);
-    HIP_TRY(launch_tn(kTnF64, P->tnR.rt, P->tnR.pf, a, P->stream));
-    ST_TRY(timed_done(P, ev, e));
-    time_next(P, ev, kinds, &e, 2);
-    HIP_TRY(launch_tn_sum_cast(kTnF64, part, P->tnR.nsplit, P->kp, L.Np, L.Np, P->ws + L.W64,
-                               L.Np, P->stream));
-    ST_TRY(timed_done(P, ev, e));
+    ST_TRY(pass_a_w(P, kTnF64, P->tnR, a, P->ws + L.W64, ev, kinds, &e));
     // (A bf16 plan's start shape is an FP32 one: its anchors take the residual's.)
     const TnChoice& cb = P->bf16 ? P->tnR : P->tnX0;
     TnArgs b = tn_args(P->ws + L.C64T, L.Np, L.np, P->ws + L.W64, L.Np, P->kp, L.Np, cb, kTnF64,
                        part, L.np);
-    time_next(P, ev, kinds, &e, 1);
-    HIP_TRY(launch_tn(kTnF64, cb.rt, cb.pf, b, P->stream));
-    ST_TRY(timed_done(P, ev, e));
-    time_next(P, ev, kinds, &e, 2);
-    HIP_TRY(launch_tn_update(P->tq, 1, update_args(P, cb, 2), P->stream));
-    ST_TRY(timed_done(P, ev, e));
+    ST_TRY(pass_b_update(P, kTnF64, cb, b, 2, ev, kinds, &e));
   } else {
-    time_next(P, ev, kinds, &e, 0);
-    HIP_TRY(launch_tn(P->tq, P->tnA.rt, P->tnA.pf, pass_a_args(P), P->stream));
-    ST_TRY(timed_done(P, ev, e));
-    time_next(P, ev, kinds, &e, 2);
-    HIP_TRY(launch_tn_sum_cast(P->tq, part, P->tnA.nsplit, P->kp, L.Np, L.Np, P->ws + L.Wq, L.Np,
-                               P->stream));
-    ST_TRY(timed_done(P, ev, e));
-    time_next(P, ev, kinds, &e, 1);
-    HIP_TRY(launch_tn(P->tq, P->tnB.rt, P->tnB.pf, pass_b_args(P), P->stream));
-    ST_TRY(timed_done(P, ev, e));
-    time_next(P, ev, kinds, &e, 2);
-    HIP_TRY(launch_tn_update(P->tq, P->tq == kTnF64, update_args(P, P->tnB, 0), P->stream));
-    ST_TRY(timed_done(P, ev, e));
+    ST_TRY(pass_a_w(P, P->tq, P->tnA, pass_a_args(P), P->ws + L.Wq, ev, kinds, &e));
+    ST_TRY(pass_b_update(P, P->tq, P->tnB, pass_b_args(P), 0, ev, kinds, &e));
   }
   ++P->since_start;
   if (nev) *nev = e;
@@ -851,8 +870,7 @@ apc_status start_gemm(apc_plan_s* P, const double* c_rhs) {
   const Layout& L = P->L;
   const int t = x0_type(P);
   HIP_TRY(launch_tn_operand(t, c_rhs, P->N, P->kp, P->N, P->ws + L.c64p, L.Np, P->stream));
-  HIP_TRY(launch_tn(t, P->tnX0.rt, P->tnX0.pf, x0_args(P), P->stream));
-  HIP_TRY(launch_tn_update(P->tq, t == kTnF64, update_args(P, P->tnX0, 1), P->stream));
+  ST_TRY(pass_b_update(P, t, P->tnX0, x0_args(P), 1));
   P->since_start = 0;
   return APC_OK;
 }
@@ -860,7 +878,7 @@ apc_status start_gemm(apc_plan_s* P, const double* c_rhs) {
 // R = B - A X (X: kp x np FP64, RHS-major) into R (RHS-major, stride N), k columns.
 apc_status gemm_residual(apc_plan_s* P, const double* X, double* R) {
   const Layout& L = P->L;
-  HIP_TRY(launch_tn(kTnF64, P->tnR.rt, P->tnR.pf, resid_args(P, X), P->stream));
+  HIP_TRY(launch_choice(kTnF64, P->tnR, resid_args(P, X), P->stream));
   HIP_TRY(launch_tn_resid(P->at<double>(L.tnpart), P->tnR.nsplit, P->kp, L.Np, P->N, P->k, P->B,
                           P->ldb, R, P->N, P->stream));
   return APC_OK;
@@ -896,6 +914,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
   const char* fix_ns = std::getenv("APC_TN_SPLIT");
   const char* tune = std::getenv("APC_TN_TUNE");
   if (fix_rt || fix_ns || std::getenv("APC_TN_PF") || std::getenv("APC_TN_NT") ||
+      std::getenv("APC_TN_KS") ||
       (tune && std::atoi(tune) == 0)) {
     // Fixed shape (not cached): 128 rows per workgroup, the smallest split
     // with >= 512 workgroups, unless the environment names them.
@@ -912,6 +931,14 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
     if (c.pf > 2 && (c.rt > 2 || type == kTnF64)) c.pf = 2;
     if (c.pf > 2) c.nt = 1;
     if (const char* e = std::getenv("APC_TN_NT")) c.nt = std::atoi(e) != 0;
+    c.plain_nsplit = c.nsplit;
+    if (const char* e = std::getenv("APC_TN_KS")) {
+      const int ks = std::atoi(e);
+      if (tn_ks_ok(type, ks, base)) {
+        c.ks = ks;
+        c.nsplit = 1;
+      }
+    }
     if (const char* e = std::getenv("APC_TN_WAVES"))
       if (std::atoi(e) == 8 && type != kTnF64 && (c.rt == 1 || (c.rt == 2 && c.pf <= 2)) && c.nt &&
           base.rows % (128 * c.rt) == 0)
@@ -960,7 +987,22 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
     }
   }
   if (cand.empty()) cand.push_back(TnChoice{1, 1, 0.f, 1, 1});
+  // The waves-over-K kernel, where its reads of V (each 16 rows read all of
+  // it, from L2) stay below 2 GB: about 100 us there, where k_tn is far ahead.
+  if (tn_operand_bytes(type, base.kp, base.K) * (base.rows / 16) < (int64_t(2) << 30)) {
+    for (int ks = 1; ks <= 2; ++ks)
+      if (tn_ks_ok(type, ks, base)) {
+        TnChoice c;
+        c.rt = 1;
+        c.ks = ks;
+        cand.push_back(c);
+      }
+  }
+  // It saves the epilogue's launch, which takes at least this long (4.1-5.5 us
+  // for the smallest operands).
+  constexpr float kEpilogueMs = 4.0e-3f;
   TnChoice best;
+  int plain_nsplit = 1;
   {
     // Each timed launch takes a pair of events recorded from its own dispatch.
     constexpr int kReps = 3;
@@ -971,10 +1013,10 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
     };
     auto run_scrub = [&]() -> hipError_t {
       if (!scrub) return hipSuccess;
-      return launch_tn(scrub->type, scrub->choice.rt, scrub->choice.pf, scrub->args, P->stream);
+      return launch_choice(scrub->type, scrub->choice, scrub->args, P->stream);
     };
-    float best_ms = 0.f;
-    bool have = false;
+    float best_ms = 0.f, plain_ms = 0.f;
+    bool have = false, have_plain = false;
     for (const TnChoice& c : cand) {
       TnArgs a = base;
       a.nsplit = c.nsplit;
@@ -982,12 +1024,12 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
       a.waves = c.waves;
       a.klen = round_up((a.K + c.nsplit - 1) / c.nsplit, tn_step_elems(type));
       hipError_t err = run_scrub();
-      if (err == hipSuccess) err = launch_tn(type, c.rt, c.pf, a, P->stream);  // warm-up
+      if (err == hipSuccess) err = launch_choice(type, c, a, P->stream);  // warm-up
       for (int r = 0; err == hipSuccess && r < kReps; ++r) {
         err = run_scrub();
         if (err != hipSuccess) break;
         pending_timing() = TimedLaunch{ev[2 * r], ev[2 * r + 1]};
-        err = launch_tn(type, c.rt, c.pf, a, P->stream);
+        err = launch_choice(type, c, a, P->stream);
         if (pending_timing().start) {  // not taken: record back to back (never expected)
           pending_timing() = TimedLaunch{};
           err = hipErrorInvalidValue;
@@ -1006,14 +1048,21 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
         return fail(APC_EHIP, "tuning launch failed: %s", hipGetErrorString(err));
       }
       ms /= static_cast<float>(kReps);
-      if (!have || ms < best_ms) {
+      const float cost = ms + (c.ks ? 0.f : kEpilogueMs);
+      if (!have || cost < best_ms) {
         best = c;
-        best_ms = ms;
+        best_ms = cost;
+        best.us = ms * 1e3f;
         have = true;
+      }
+      if (!c.ks && (!have_plain || ms < plain_ms)) {
+        plain_ms = ms;
+        plain_nsplit = c.nsplit;
+        have_plain = true;
       }
     }
     destroy();
-    best.us = best_ms * 1e3f;
+    best.plain_nsplit = plain_nsplit;
   }
   std::lock_guard<std::mutex> lk(mu);
   cache[key] = best;
@@ -1819,7 +1868,7 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
   P->group_blocks = group_blocks >= 0 ? group_blocks : 0;
   P->gemm = uses_gemm(k, precision);
   P->bf16 = P->prec == APC_BF16_IR;
-  P->tq = P->prec == APC_F64 ? kTnF64 : P->prec == APC_F32 ? kTnF32 : kTnBF16;
+  P->tq = P->prec == APC_F64 ? kTnF64 : P->prec == APC_F32 ? tn_f32_type(P->kp) : kTnBF16;
   // FP32 k-RHS: an FP64 anchor update every kAnchorEvery updates; the bf16 inner solver
   // is corrected by the outer refinement instead (0 = never).
   P->anchor_every = (P->gemm && P->prec == APC_F32) ? kAnchorEvery : 0;
@@ -2219,7 +2268,7 @@ apc_status apc_get_launch(apc_plan p, int32_t which, int32_t* rows_per_wg, int32
   if (which < 0 || which > 3) return fail(APC_EINVAL, "which must be 0..5");
   if (!p->gemm) return fail(APC_EUNSUPPORTED, "launch shapes are reported for the k-RHS path only");
   const TnChoice& c = which == 0 ? p->tnA : which == 1 ? p->tnB : which == 2 ? p->tnX0 : p->tnR;
-  if (rows_per_wg) *rows_per_wg = 16 * c.waves * c.rt;
+  if (rows_per_wg) *rows_per_wg = c.rows_per_wg();
   if (splits) *splits = c.nsplit;
   if (tuned_us) *tuned_us = c.us;
   return APC_OK;
@@ -2419,14 +2468,20 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
     // Reverse through it: X bh by the same two contractions as an update.
     for (int32_t t = t1 - 1; t >= t0; --t) {
       TnArgs pa = tn_args(P->ws + L.Cq, L.np, L.Np, bq, L.np, P->kp, L.np, P->tnA, P->tq, part, L.Np);
-      HIP_TRY(launch_tn(P->tq, P->tnA.rt, P->tnA.pf, pa, st));
-      HIP_TRY(launch_tn_sum_cast(P->tq, part, P->tnA.nsplit, P->kp, L.Np, L.Np, P->ws + L.Wq, L.Np, st));
-      HIP_TRY(launch_tn(P->tq, P->tnB.rt, P->tnB.pf, pass_b_args(P), st));
+      ST_TRY(pass_a_w(P, P->tq, P->tnA, pa, P->ws + L.Wq));
       const double* s_t = seg(t - t0);
       const double* s_n = seg(t - t0 + 1);
       TnAdjointArgs ad{part, P->tnB.nsplit, P->kp, L.np, L.np, a, bh, g0, s_t, s_t + cnt,
                        s_n + cnt, L.np, bq, L.np, P->gamma, P->eta, 1.0 / P->m, red};
-      HIP_TRY(launch_tn_adjoint(P->tq, ad, st));
+      // One launch when the shape holds whole sums and its workgroups fit the
+      // sums' slots.
+      const TnChoice& cb = P->tnB;
+      if (cb.ks && (L.np / 16) * (P->kp / (16 * cb.ks)) <= tn_adjoint_blocks()) {
+        HIP_TRY(launch_tn_ks_adjoint(P->tq, cb.ks, pass_b_args(P), ad, st));
+      } else {
+        HIP_TRY(launch_choice(P->tq, cb, pass_b_args(P), st));
+        HIP_TRY(launch_tn_adjoint(P->tq, ad, st));
+      }
     }
   }
   // x_bar(0) = x0 itself: its adjoint gets dL/dx_bar(0) too.
@@ -2436,8 +2491,7 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
                                     : static_cast<const void*>(P->ws + L.C64p);
   double* W64 = P->tq == kTnF64 ? P->at<double>(L.Wq) : P->at<double>(L.W64);
   TnArgs pc = tn_args(C64, L.np, L.Np, g0, L.np, P->kp, L.np, P->tnR, kTnF64, part, L.Np);
-  HIP_TRY(launch_tn(kTnF64, P->tnR.rt, P->tnR.pf, pc, st));
-  HIP_TRY(launch_tn_sum_cast(kTnF64, part, P->tnR.nsplit, P->kp, L.Np, L.Np, W64, L.Np, st));
+  ST_TRY(pass_a_w(P, kTnF64, P->tnR, pc, W64));
   double* t1b = P->at<double>(L.Rb);
   double* t2b = P->at<double>(L.cb);
   if (P->qr_passes == 2) {
@@ -2571,12 +2625,19 @@ bool batch_single_pass(const apc_plan* plans, int32_t count) {
 BatchGemm batch_gemm_desc(apc_plan_s* P) {
   const Layout& L = P->L;
   void* part = P->ws + L.tnpart;
+  // k_tn's shapes: the batch kernel has its contraction tiles only.
+  auto plain = [](TnChoice c) {
+    c.nsplit = c.plain_nsplit;
+    c.ks = 0;
+    return c;
+  };
+  const TnChoice cA = plain(P->tnA), cB = plain(P->tnB), cR = plain(P->tnR), cX = plain(P->tnX0);
   BatchGemm G{};
-  G.tn[0] = pass_a_args(P);
-  G.tn[1] = pass_b_args(P);
-  G.tn[2] = tn_args(P->ws + L.C64p, L.np, L.Np, P->ws + L.yref, L.np, P->kp, L.np, P->tnR, kTnF64,
+  G.tn[0] = tn_args(P->ws + L.Cq, L.np, L.Np, P->ws + L.yq, L.np, P->kp, L.np, cA, P->tq, part, L.Np);
+  G.tn[1] = tn_args(P->ws + L.CqT, L.Np, L.np, P->ws + L.Wq, L.Np, P->kp, L.Np, cB, P->tq, part, L.np);
+  G.tn[2] = tn_args(P->ws + L.C64p, L.np, L.Np, P->ws + L.yref, L.np, P->kp, L.np, cR, kTnF64,
                     part, L.Np);
-  G.tn[3] = tn_args(P->ws + L.C64T, L.Np, L.np, P->ws + L.W64, L.Np, P->kp, L.Np, P->tnX0, kTnF64,
+  G.tn[3] = tn_args(P->ws + L.C64T, L.Np, L.np, P->ws + L.W64, L.Np, P->kp, L.Np, cX, kTnF64,
                     part, L.np);
   // The batch kernel runs one 16-row tile per wave in four-wave workgroups.
   for (int q = 0; q < 4; ++q) {
@@ -2585,16 +2646,16 @@ BatchGemm batch_gemm_desc(apc_plan_s* P) {
                                           G.tn[q].nsplit);
   }
   G.sum_part = part;
-  G.sum_nsplit[0] = P->tnA.nsplit;
-  G.sum_nsplit[1] = P->tnR.nsplit;
+  G.sum_nsplit[0] = cA.nsplit;
+  G.sum_nsplit[1] = cR.nsplit;
   G.sum_ldp = L.Np;
   G.sum_rows = L.Np;
   G.sum_out[0] = P->ws + L.Wq;
   G.sum_out[1] = P->ws + L.W64;
   G.sum_ldo = L.Np;
   G.kp = P->kp;
-  G.upd[0] = update_args(P, P->tnB, 0);
-  G.upd[1] = update_args(P, P->tnX0, 2);
+  G.upd[0] = update_args(P, cB, 0);
+  G.upd[1] = update_args(P, cX, 2);
   G.y = P->at<double>(L.ys);
   G.xbar = P->xbar();
   G.yref = P->anchor_every > 0 ? P->at<double>(L.yref) : nullptr;
@@ -2754,7 +2815,7 @@ apc_status batch_check_plans(const apc_plan* plans, int32_t count) {
   for (int32_t s = 0; s < count; ++s) {
     const apc_plan_s* P = plans[s];
     if (!P) return fail(APC_EINVAL, "plan %d is NULL", s);
-    if (P->prec != APC_F32 || P->bf16 || (P->gemm && P->tq != kTnF32) || (!P->gemm && P->k != 1))
+    if (P->prec != APC_F32 || P->bf16 || (!P->gemm && P->k != 1))
       return fail(APC_EUNSUPPORTED, "plan %d: batches take FP32 plans (k = 1 per-block form, or the "
                   "k-RHS form with FP32 products)", s);
     if (P->gemm && P->kp > 128)

@@ -387,7 +387,10 @@ hipError_t launch_resident_f64(const ResidentArgs& a, int rpw, int cpl, hipStrea
 // k right-hand sides: streaming contractions on the matrix cores (apc_gemm.hip)
 // ---------------------------------------------------------------------------
 
-enum { kTnF64 = 0, kTnF32 = 1, kTnBF16 = 2 };
+// kTnF32x3: FP32 on the bf16 matrix cores (V operands stored split), for more
+// than 16 right-hand sides; kTnF32 (the FP32 matrix instructions) for 16.
+enum { kTnF64 = 0, kTnF32 = 1, kTnBF16 = 2, kTnF32x3 = 3 };
+inline int tn_f32_type(int32_t kp) { return kp <= 16 ? kTnF32 : kTnF32x3; }
 constexpr int kTnPad = 256;       // rows and K of every operand, zero-padded to a multiple of this
 constexpr int kTnMaxSplit = 8;    // split-K factors the partial buffer holds
 
@@ -398,8 +401,8 @@ constexpr int kTnMaxSplit = 8;    // split-K factors the partial buffer holds
 // aligned and zero wherever they extend past the data.
 // M: rows x K in the fragment-packed layout written by launch_tn_pack_frag
 // (ldm = K); V: kp rows of K entries, stride ldv (a multiple of the step): row-
-// major in bf16 and FP64, split into three bf16 parts in FP32 (TnOperand in
-// apc_tn.h; written by the epilogues and launch_tn_operand).
+// major, or split into three bf16 parts (kTnF32x3; TnOperand in apc_tn.h;
+// written by the epilogues and launch_tn_operand).
 struct TnArgs {
   const void* M;
   int64_t ldm;
@@ -461,13 +464,13 @@ hipError_t launch_tn_update(int type, int part_f64, const TnUpdateArgs& a, hipSt
 // operand for a restored state).
 hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, int64_t n,
                           double gamma, void* yq, hipStream_t s);
-// dst = the V operand (rows of ldd entries, type FP64 or FP32) of src (FP64,
+// dst = the V operand (rows of ldd entries, not bf16) of src (FP64,
 // rows x cols, stride lds), zero past cols.
 hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t rows, int64_t cols,
                              void* dst, int64_t ldd, hipStream_t s);
 // Bytes of a V operand of `rows` rows of ld entries.
 inline int64_t tn_operand_bytes(int type, int64_t rows, int64_t ld) {
-  return rows * ld * (type == kTnF64 ? 8 : type == kTnF32 ? 6 : 2);
+  return rows * ld * (type == kTnF64 ? 8 : type == kTnF32x3 ? 6 : type == kTnF32 ? 4 : 2);
 }
 
 // One reverse step of the (y, x_bar) iteration (FP64 adjoints a = dL/dy(t+1),
@@ -499,6 +502,26 @@ struct TnAdjointArgs {
 };
 constexpr int kTnAdjointBlocks = 512;
 int tn_adjoint_blocks();
+
+// The contraction with 16 rows and 16 nct (1 or 2) right-hand sides per
+// workgroup, its waves over K (a.nsplit, a.klen, a.nt and a.waves unused), and
+// its epilogue in the same launch: the partial (as nsplit = 1), the V operand
+// W (out, stride ldo), the (y, x_bar) update with operand type type_q, or the
+// reverse step (at most kTnAdjointBlocks workgroups; red as k_tn_adjoint's).
+struct TnKsEpilogue {
+  void* out;
+  int64_t ldo;
+  TnUpdateArgs upd;
+  TnAdjointArgs adj;
+};
+bool tn_ks_ok(int type, int nct, const TnArgs& a);
+hipError_t launch_tn_ks(int type, int nct, const TnArgs& a, hipStream_t s);
+hipError_t launch_tn_ks_operand(int type, int nct, const TnArgs& a, void* out, int64_t ldo,
+                                hipStream_t s);
+hipError_t launch_tn_ks_update(int type, int nct, const TnArgs& a, int type_q, const TnUpdateArgs& u,
+                               hipStream_t s);
+hipError_t launch_tn_ks_adjoint(int type, int nct, const TnArgs& a, const TnAdjointArgs& d,
+                                hipStream_t s);
 hipError_t launch_tn_adjoint(int type, const TnAdjointArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------------------

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "apc_internal.h"
 
@@ -20,8 +21,21 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
+// Element type of an FP32 contraction on the bf16 matrix cores (see Split3):
+// a float whose V operands are stored split.
+struct F32x3 {
+  float v;
+  F32x3() = default;
+  __device__ explicit F32x3(float f) : v(f) {}
+};
+
 template <typename T>
 struct TnTraits;
+template <>
+struct TnTraits<F32x3> {
+  using Acc = f32x4;
+  using Part = float;
+};
 template <>
 struct TnTraits<__bf16> {
   using Acc = f32x4;
@@ -44,6 +58,12 @@ __device__ inline void mma_bf16(const u32x4& a, const u32x4& b, f32x4& c) {
                                               __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f32x4& c, __bf16*) { mma_bf16(a, b, c); }
+__device__ inline void mma_piece(const u32x4& a, const u32x4& b, f32x4& c, float*) {
+  const f32x4 av = __builtin_bit_cast(f32x4, a);
+  const f32x4 bv = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], c, 0, 0, 0);
+}
 __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f64x4& c, double*) {
   const f64x2 av = __builtin_bit_cast(f64x2, a);
   const f64x2 bv = __builtin_bit_cast(f64x2, b);
@@ -59,7 +79,10 @@ __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f64x4& c, doubl
 // signs, small against the rounding of the FP32 sums they would be added to.
 // Infinities and NaN give NaN.  The FP32 matrix instructions run at 1/16 of
 // the bf16 rate, so six products take 3/8 of their time; errors against 64
-// bits measured 0.3-0.85 of theirs (fewer roundings per sum).
+// bits measured 0.3-0.85 of theirs (fewer roundings per sum).  With 16 right-
+// hand sides a pass is bound by reading M, not by its products, and the FP32
+// instructions stay (T = float): splitting cost 4-15 % there (5120^2: 18.1
+// against 17.3 us).
 struct Split3 {
   u32x4 h, m, l;  // eight bf16 each
 };
@@ -93,8 +116,8 @@ __device__ inline Split3 split8(const u32x4& a, const u32x4& b) {
   return s;
 }
 
-// The V operand (one row of K entries per right-hand side).  bf16 and FP64:
-// row-major, 256 bytes per row and step.  FP32: split when it is written, 384
+// The V operand (one row of K entries per right-hand side).  bf16, FP32 and
+// FP64: row-major, 256 bytes per row and step.  F32x3: split when it is written, 384
 // bytes per row and step of 64: the h, m and l parts of the step, 128 bytes
 // each, every part in the order the lanes take it (chunk kc = 8 q + 4 h + g of
 // four entries at 32 q + 8 g + 4 h, so lane group g's eight entries of the
@@ -103,8 +126,9 @@ __device__ inline Split3 split8(const u32x4& a, const u32x4& b) {
 // contiguous bytes (kParts of them cover a row).
 template <typename T>
 struct TnOperand {
-  static constexpr int kStepBytes = sizeof(T) == 4 ? 384 : 256;
-  static constexpr int kLanes = sizeof(T) == 4 ? 8 : 16;
+  static constexpr bool kSplit = std::is_same_v<T, F32x3>;
+  static constexpr int kStepBytes = kSplit ? 384 : 256;
+  static constexpr int kLanes = kSplit ? 8 : 16;
   static constexpr int kRows = 64 / kLanes;
   static constexpr int kParts = kStepBytes / (16 * kLanes);
 };
@@ -209,7 +233,7 @@ __device__ inline void tn_block(const TnArgs& a, int bid, TnStage<T, NCT>& vs) {
   };
   // A split past the end of K (from rounding its length up to whole steps)
   // writes zero partials.
-  if constexpr (sizeof(T) == 4) {
+  if constexpr (Op::kSplit) {
     if (nsteps > 0) {
       // A step is two phases (matrix products over 32 of its 64 columns).  In
       // phase k the raw pieces of phase k + 1 are split while the products of
@@ -443,6 +467,8 @@ __device__ inline double cvt<double>(double v) { return v; }
 template <>
 __device__ inline float cvt<float>(double v) { return static_cast<float>(v); }
 template <>
+__device__ inline F32x3 cvt<F32x3>(double v) { return F32x3(static_cast<float>(v)); }
+template <>
 __device__ inline __bf16 cvt<__bf16>(double v) { return static_cast<__bf16>(static_cast<float>(v)); }
 
 template <typename P>
@@ -485,13 +511,13 @@ __device__ inline void store4(T* p, const T (&v)[4]) {
 }
 
 // Four consecutive entries j .. j + 3 (j % 4 == 0) of row c of a V operand of
-// row length ld (a multiple of the step): row-major, or split for FP32.
+// row length ld (a multiple of the step): row-major, or split (F32x3).
 template <typename TQ>
 __device__ inline void store_operand4(TQ* base, int64_t ld, int64_t c, int64_t j, const TQ (&v)[4]) {
-  if constexpr (sizeof(TQ) == 4) {
+  if constexpr (TnOperand<TQ>::kSplit) {
     unsigned h[2], m[2], l[2];
-    split_pair(v[0], v[1], h[0], m[0], l[0]);
-    split_pair(v[2], v[3], h[1], m[1], l[1]);
+    split_pair(v[0].v, v[1].v, h[0], m[0], l[0]);
+    split_pair(v[2].v, v[3].v, h[1], m[1], l[1]);
     const int kc = static_cast<int>(j >> 2) & 15;
     char* d = reinterpret_cast<char*>(base) + (c * (ld >> 6) + (j >> 6)) * 384 +
               64 * (kc >> 3) + 16 * (kc & 3) + 8 * ((kc >> 2) & 1);
@@ -520,37 +546,46 @@ __device__ inline void sum_cast4(const P* part, int32_t nsplit, int64_t ldp, int
   }
   TQ o[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) o[q] = static_cast<TQ>(s[q]);
+  for (int q = 0; q < 4; ++q) o[q] = TQ(s[q]);
   store_operand4(out, ldo, c, r, o);
 }
 
 // The (y, x_bar) update, its start, or an anchor update (see TnUpdateArgs)
-// for the four entries e .. e + 3, e = c * n + j (e, n, ldp, ldx and ldq
-// multiples of 4).  y1 = (1 - gamma) y + gamma x_bar; an anchor update (mode 2,
-// z = m X y1 in FP64) reads the copy y_ref its product was formed from and
-// becomes the new anchor, an update in between has z = m X~ (y1 - y_ref).
-template <typename P, typename TQ>
-__device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
-  const int64_t stride = static_cast<int64_t>(a.kp) * a.ldp;
-  const P* part = static_cast<const P*>(a.part);
+// for the four entries (c, j .. j + 3), j and the strides multiples of 4, from
+// their summed products z.  y1 = (1 - gamma) y + gamma x_bar; an anchor update
+// (mode 2, z = m X y1 in FP64) reads the copy y_ref its product was formed
+// from and becomes the new anchor, an update in between has
+// z = m X~ (y1 - y_ref).  The state is loaded apart from its use, so that a
+// contraction can load it before its products.
+struct UpdateState {
+  double xb[4], x0[4], y[4], yr[4], ur[4];  // y: y_ref in an anchor update
+};
+// kAll: load every field without a branch (absent anchors read y instead, and
+// are not used), so that the loads can stay in flight.
+template <bool kAll>
+__device__ inline void update_load(const TnUpdateArgs& a, int64_t c, int64_t j, UpdateState& s) {
+  const int64_t i = c * a.ldx + j;
+  const double* y = a.mode == 2 ? a.yref : a.y;
+  load4(a.xb + i, s.xb);
+  load4(a.x0 + i, s.x0);
+  load4(y + i, s.y);
+  if (kAll || (a.mode == 0 && a.yref)) {
+    load4((kAll && !a.yref ? y : a.yref) + i, s.yr);
+    load4((kAll && !a.uref ? y : a.uref) + i, s.ur);
+  }
+}
+template <typename TQ>
+__device__ inline void update_quad(const TnUpdateArgs& a, int64_t c, int64_t j, const UpdateState& s,
+                                   const double (&z)[4]) {
   TQ* yq = static_cast<TQ*>(a.yq);
   const double g = a.gamma, omg = 1.0 - a.gamma, eta = a.eta, ome = 1.0 - a.eta;
-  const int64_t c = e / a.n, j = e - c * a.n;
-  P zs[4];
-  load4(part + c * a.ldp + j, zs);
-  for (int sp = 1; sp < a.nsplit; ++sp) {
-    P t[4];
-    load4(part + sp * stride + c * a.ldp + j, t);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) zs[q] += t[q];
-  }
   const int64_t i = c * a.ldx + j;
   TQ qv[4];
   if (a.mode == 1) {
     double x0[4], zero[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      x0[q] = static_cast<double>(zs[q]) * a.inv_m;
+      x0[q] = z[q] * a.inv_m;
       qv[q] = cvt<TQ>(g * x0[q]);
     }
     store4(a.x0 + i, x0);
@@ -563,33 +598,20 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
     store_operand4(yq, a.ldq, c, j, qv);
     return;
   }
-  double xb[4], x0[4], y[4] = {0.0, 0.0, 0.0, 0.0}, yr[4] = {0.0, 0.0, 0.0, 0.0},
-         ur[4] = {0.0, 0.0, 0.0, 0.0};
-  load4(a.xb + i, xb);
-  load4(a.x0 + i, x0);
-  if (a.mode == 2) {
-    load4(a.yref + i, yr);
-  } else {
-    load4(a.y + i, y);
-    if (a.yref) {
-      load4(a.yref + i, yr);
-      load4(a.uref + i, ur);
-    }
-  }
   double yo[4], xo[4], uo[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const double y1 = a.mode == 2 ? yr[q] : omg * y[q] + g * xb[q];
-    double u = static_cast<double>(zs[q]) * a.inv_m;
+    const double y1 = a.mode == 2 ? s.y[q] : omg * s.y[q] + g * s.xb[q];
+    double u = z[q] * a.inv_m;
     double ref = 0.0;
     if (a.mode == 2) {
       uo[q] = u;
       ref = y1;
     } else if (a.yref) {
-      u += ur[q];
-      ref = yr[q];
+      u += s.ur[q];
+      ref = s.yr[q];
     }
-    const double xn = eta * (x0[q] + y1 - u) + ome * xb[q];
+    const double xn = eta * (s.x0[q] + y1 - u) + ome * s.xb[q];
     yo[q] = y1;
     xo[q] = xn;
     qv[q] = cvt<TQ>(omg * y1 + g * xn - ref);
@@ -598,6 +620,65 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
   store4(a.y + i, yo);
   store4(a.xb + i, xo);
   store_operand4(yq, a.ldq, c, j, qv);
+}
+
+// The same for e = c * n + j, from the split partials (n and ldp multiples of 4).
+template <typename P, typename TQ>
+__device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
+  const int64_t stride = static_cast<int64_t>(a.kp) * a.ldp;
+  const P* part = static_cast<const P*>(a.part);
+  const int64_t c = e / a.n, j = e - c * a.n;
+  P zs[4];
+  load4(part + c * a.ldp + j, zs);
+  for (int sp = 1; sp < a.nsplit; ++sp) {
+    P t[4];
+    load4(part + sp * stride + c * a.ldp + j, t);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) zs[q] += t[q];
+  }
+  UpdateState s;
+  update_load<false>(a, c, j, s);
+  const double z[4] = {static_cast<double>(zs[0]), static_cast<double>(zs[1]),
+                       static_cast<double>(zs[2]), static_cast<double>(zs[3])};
+  update_quad<TQ>(a, c, j, s, z);
+}
+
+// One reverse step of the (y, x_bar) iteration (see TnAdjointArgs) for the
+// four entries (c, j .. j + 3) from their summed products z; adds their shares
+// of the dL/dgamma and dL/deta sums.
+struct AdjointState {
+  double a[4], bh[4], g0[4], y[4], xb[4], xn[4];
+};
+__device__ inline void adjoint_load(const TnAdjointArgs& a, int64_t c, int64_t j, AdjointState& s) {
+  const int64_t i = c * a.ldx + j;
+  load4(a.a + i, s.a);
+  load4(a.bh + i, s.bh);
+  load4(a.g0 + i, s.g0);
+  load4(a.y_t + i, s.y);
+  load4(a.xb_t + i, s.xb);
+  load4(a.xb_next + i, s.xn);
+}
+template <typename TQ>
+__device__ inline void adjoint_quad(const TnAdjointArgs& a, int64_t c, int64_t j, AdjointState& s,
+                                    const double (&z)[4], double& sg, double& se) {
+  const int64_t i = c * a.ldx + j;
+  TQ qv[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double xbh = z[q] * a.inv_m;  // X b
+    const double bh = s.bh[q];
+    const double at = s.a[q] + a.eta * (bh - xbh);
+    sg += at * (s.xb[q] - s.y[q]);
+    se += bh * (s.xn[q] - s.xb[q]);
+    s.g0[q] += a.eta * bh;
+    s.a[q] = (1.0 - a.gamma) * at;
+    s.bh[q] = (1.0 - a.eta) * bh + a.gamma * at;
+    qv[q] = cvt<TQ>(s.bh[q]);
+  }
+  store4(a.g0 + i, s.g0);
+  store4(a.a + i, s.a);
+  store4(a.bh + i, s.bh);
+  store_operand4(static_cast<TQ*>(a.bq), a.ldq, c, j, qv);
 }
 
 }  // namespace

@@ -1,0 +1,82 @@
+"""The contraction whose waves split K and that applies its epilogue itself (forced with
+APC_TN_KS, 16 or 32 right-hand sides per workgroup): every epilogue and element type, on
+sizes with one row tile, with fewer steps of K than waves and with ragged ends."""
+
+import math
+
+import numpy as np
+import pytest
+
+from oracle import apc_oracle as O
+from paper_1708_01413_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _system(N, n, k, seed):
+    S = synth.gaussian_system(N, n, 5, k=k, seed=seed, scale=1 / math.sqrt(n), shift=2.0)
+    torch = _torch()
+    return S, torch.from_numpy(S.A).cuda(), torch.from_numpy(S.B).cuda()
+
+
+SIZES = [(64, 64, 2), (300, 200, 33), (513, 260, 17)]
+
+
+@pytest.mark.parametrize("ks", ["1", "2"])
+@pytest.mark.parametrize("N,n,k", SIZES)
+def test_trajectories(N, n, k, ks, monkeypatch):
+    """18 updates (two anchors): FP64 to 1e-10 and anchored FP32 to 1e-5 of the oracle, and
+    the rebuilt residual monitor's value to 1e-9 of the solution's own."""
+    from paper_1708_01413_amd import apc
+    S, A, b = _system(N, n, k, 7 * n + k)
+    g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+    ref = O.apc_run(S.A, S.B, S.off, T=18, gamma=g, eta=e, keep_traj=True)["traj"][18]
+    monkeypatch.setenv("APC_TN_KS", ks)
+    for prec, tol in (("f64", 1e-10), ("f32", 1e-5)):
+        plan = apc.Plan(A, b, S.off, prec, gamma=g, eta=e)
+        if k > 16 or ks == "1":
+            assert plan.launch_shapes()["pass_a"]["rows_per_wg"] == 16
+        plan.iterate(18)
+        got = plan.xbar().cpu().numpy()
+        dev = np.linalg.norm(got - ref) / np.linalg.norm(S.xstar)
+        res = np.linalg.norm(S.B - S.A @ got) / np.linalg.norm(S.B)
+        print(f"{prec} N={N} n={n} k={k} ks={ks}: dev {dev:.2e}", flush=True)
+        assert dev <= tol
+        assert abs(plan.residual() - res) <= 1e-9 * res + 1e-14
+
+
+@pytest.mark.parametrize("ks", ["1", "2"])
+def test_adjoint(ks, monkeypatch):
+    """dL/dB to 1e-10 and dL/dgamma, dL/deta to 1e-9 of the oracle's adjoint (FP64)."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    S, A, b = _system(300, 200, 33, 5)
+    g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+    dx = np.random.default_rng(1).standard_normal((S.n, S.k))
+    rB, rg, re = O.apc_adjoint(S.A, S.B, S.off, 9, g, e, dx)
+    monkeypatch.setenv("APC_TN_KS", ks)
+    plan = apc.Plan(A, b, S.off, "f64", gamma=g, eta=e)
+    dB, dg, de = plan.backward(torch.from_numpy(dx).cuda(), 9, 4)
+    dev = np.linalg.norm(dB.cpu().numpy() - rB) / np.linalg.norm(rB)
+    print(f"ks={ks}: dB {dev:.2e} dgamma {abs(dg - rg) / abs(rg):.2e} deta {abs(de - re) / abs(re):.2e}")
+    assert dev <= 1e-10
+    assert abs(dg - rg) <= 1e-9 * abs(rg) and abs(de - re) <= 1e-9 * abs(re)
+
+
+@pytest.mark.parametrize("anchor", [0, 4])
+def test_bf16_refinement(anchor, monkeypatch):
+    """bf16 inner solves (with and without FP64 anchors) refined to the FP64 solution."""
+    from paper_1708_01413_amd import apc
+    S, A, b = _system(256, 256, 40, 9)
+    monkeypatch.setenv("APC_TN_KS", "2")
+    plan = apc.Plan(A, b, S.off, "bf16_ir", anchor_every=anchor)
+    x, _, rr, st = plan.solve(1e-12, 2000)
+    dev = np.linalg.norm(x.cpu().numpy() - S.xstar) / np.linalg.norm(S.xstar)
+    print(f"anchor={anchor}: relres {rr:.2e} dev {dev:.2e}")
+    assert st == 0 and dev <= 1e-10
