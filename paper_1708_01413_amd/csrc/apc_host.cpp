@@ -565,12 +565,12 @@ apc_status fused_combine(apc_plan_s* P, double alpha, double beta) {
   if (P->prec == APC_F32) {
     FusedCombineArgs<float> a{P->at<float>(L.fpart), L.ldc, P->tf(3), P->x(), ld, P->m, P->n,
                               P->gamma, alpha, beta, P->xbar(), P->at<float>(L.dv), ld,
-                              P->fused_tpb};
+                              P->fused_tpb, P->ntiles_f};
     HIP_TRY(launch_fused_combine_f32(a, P->stream));
   } else {
     FusedCombineArgs<double> a{P->at<double>(L.fpart), L.ldc, P->tf(3), P->x(), ld, P->m, P->n,
                                P->gamma, alpha, beta, P->xbar(), P->at<double>(L.dv), ld,
-                               P->fused_tpb};
+                               P->fused_tpb, P->ntiles_f};
     HIP_TRY(launch_fused_combine_f64(a, P->stream));
   }
   return APC_OK;

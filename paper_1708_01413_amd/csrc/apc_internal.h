@@ -348,6 +348,7 @@ struct FusedCombineArgs {
   TD* d;
   int64_t ldd;
   int32_t tpb = 0;            // > 0: every block has exactly tpb tiles (1, 2, 4 or 8)
+  int32_t ntiles = 0;         // tiles of all blocks
 };
 hipError_t launch_fused_combine_f32(const FusedCombineArgs<float>& a, hipStream_t s);
 hipError_t launch_fused_combine_f64(const FusedCombineArgs<double>& a, hipStream_t s);

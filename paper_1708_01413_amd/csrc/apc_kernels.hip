@@ -520,8 +520,9 @@ __global__ __launch_bounds__(kThreads) void k_fused(FusedArgs<TQ, TA> a) {
 // SIMD at 16384 x 8192 (5.8 -> 5.3 us there; 8 columns, with 32-byte pieces
 // of the partial rows per load, took 9.1).  TPB > 0: every block has exactly
 // TPB tiles (tile t of block i is i TPB + t), so a block's partials are
-// loaded together; TPB = 0 reads the tile ranges.  Both sum a block's
-// partials in tile order.
+// loaded together; TPB = 0 reads the tile ranges, for more tiles than
+// k_fused_combine_staged's LDS holds.  Both sum a block's partials in tile
+// order.
 constexpr int kCombineCols = 16;
 template <typename TD, int TPB>
 __global__ __launch_bounds__(256) void k_fused_combine(FusedCombineArgs<TD> a) {
@@ -615,6 +616,94 @@ __global__ __launch_bounds__(256) void k_fused_combine(FusedCombineArgs<TD> a) {
         if (i < a.m) a.d[static_cast<int64_t>(i) * a.ldd + j] = static_cast<TD>(v - xi[q]);
       }
     }
+  }
+}
+
+// The same when blocks have different (or many) tiles: all partial rows of the
+// workgroup's columns go to LDS first, sixteen lanes per column with eight
+// rows' loads in flight each, and a block's sum is taken from there, in tile
+// order.  Bound by the latency of one round of loads, then by the bytes of the
+// partial rows, x and d.  Read block by block instead, each block's tile range
+// was waited for and then its rows one by one: in FP32 11.8 -> 6.1 us at
+// 4000 x 2000 with 40 uneven blocks, 15.3 -> 8.1 at 6181 x 3535 with 49,
+// 19.3 -> 11.6 at 12000 x 6005 with 137; in FP64 6.0 -> 4.2 at 1500 x 1200
+// with 11.  LDS: ntiles x 16 partials and m + 1 tile starts.
+template <typename TD>
+__global__ __launch_bounds__(256) void k_fused_combine_staged(FusedCombineArgs<TD> a) {
+  constexpr int U = 4, CL = kCombineCols, BL = 256 / kCombineCols, TU = 8;
+  extern __shared__ __align__(16) unsigned char staged[];
+  TD* ps = reinterpret_cast<TD*>(staged);  // [ntiles][CL]
+  int32_t* first = reinterpret_cast<int32_t*>(ps + static_cast<int64_t>(a.ntiles) * CL);
+  __shared__ double part[BL][CL];
+  __shared__ double xb[CL];
+  const int lane = threadIdx.x % CL;
+  const int bl = threadIdx.x / CL;
+  const int64_t j = static_cast<int64_t>(blockIdx.x) * CL + lane;
+  const bool ok = j < a.n;
+  const int64_t jc = ok ? j : a.n - 1;
+  double* x = a.x;
+  const double xo = a.xbar[jc];
+  // The first two rounds' x_i, in flight with the partial rows; their new
+  // values stay in registers for the differences.
+  double keep[2][U];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int i = bl + BL * (U * r + q);
+      keep[r][q] = x[static_cast<int64_t>(min(i, a.m - 1)) * a.ldx + jc];
+    }
+  for (int i = threadIdx.x; i <= a.m; i += 256) first[i] = a.tile_first[i];
+  for (int t0 = bl; t0 < a.ntiles; t0 += BL * TU) {
+    TD v[TU];
+#pragma unroll
+    for (int k = 0; k < TU; ++k)
+      v[k] = a.part[static_cast<int64_t>(min(t0 + BL * k, a.ntiles - 1)) * a.ldp + jc];
+#pragma unroll
+    for (int k = 0; k < TU; ++k)
+      if (t0 + BL * k < a.ntiles) ps[(t0 + BL * k) * CL + lane] = v[k];
+  }
+  __syncthreads();
+  double s = 0.0;
+  auto step = [&](int i, double xi) {
+    double u = 0.0;
+    for (int t = first[i]; t < first[i + 1]; ++t) u += static_cast<double>(ps[t * CL + lane]);
+    const double xn = xi + a.gamma * ((xo - xi) - u);
+    if (ok) x[static_cast<int64_t>(i) * a.ldx + j] = xn;
+    s += xn;
+    return xn;
+  };
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int i = bl + BL * (U * r + q);
+      if (i < a.m) keep[r][q] = step(i, keep[r][q]);
+    }
+  for (int i = bl + 2 * BL * U; i < a.m; i += BL) step(i, x[static_cast<int64_t>(i) * a.ldx + jc]);
+  part[bl][lane] = s;
+  __syncthreads();
+  if (bl == 0 && ok) {
+    double tot = part[0][lane];
+#pragma unroll
+    for (int b = 1; b < BL; ++b) tot += part[b][lane];  // block-lane order
+    const double v = a.beta == 0.0 ? a.alpha * tot : a.alpha * tot + a.beta * xo;
+    a.xbar[j] = v;
+    xb[lane] = v;
+  }
+  __syncthreads();
+  if (ok) {
+    const double v = xb[lane];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        const int i = bl + BL * (U * r + q);
+        if (i < a.m) a.d[static_cast<int64_t>(i) * a.ldd + j] = static_cast<TD>(v - keep[r][q]);
+      }
+    for (int i = bl + 2 * BL * U; i < a.m; i += BL)
+      a.d[static_cast<int64_t>(i) * a.ldd + j] =
+          static_cast<TD>(v - x[static_cast<int64_t>(i) * a.ldx + j]);
   }
 }
 
@@ -1812,7 +1901,16 @@ static hipError_t fused_combine_impl(const FusedCombineArgs<TD>& a, hipStream_t 
     case 2: APC_LAUNCH((k_fused_combine<TD, 2>), grid, dim3(256), 0, s, a); break;
     case 4: APC_LAUNCH((k_fused_combine<TD, 4>), grid, dim3(256), 0, s, a); break;
     case 8: APC_LAUNCH((k_fused_combine<TD, 8>), grid, dim3(256), 0, s, a); break;
-    default: APC_LAUNCH((k_fused_combine<TD, 0>), grid, dim3(256), 0, s, a); break;
+    default: {
+      // Staged up to what one workgroup's LDS holds without a larger limit
+      // (the kernel's static part is 2.2 KB): 479 FP64 or 957 FP32 tiles.
+      const size_t lds = static_cast<size_t>(a.ntiles) * kCombineCols * sizeof(TD) +
+                         (static_cast<size_t>(a.m) + 1) * 4;
+      if (lds <= 60 * 1024)
+        APC_LAUNCH((k_fused_combine_staged<TD>), grid, dim3(256), lds, s, a);
+      else
+        APC_LAUNCH((k_fused_combine<TD, 0>), grid, dim3(256), 0, s, a);
+    }
   }
   return hipGetLastError();
 }

@@ -1,0 +1,42 @@
+"""Single right-hand side with blocks of different heights: the combine that stages every
+partial row in LDS, and the one without for more tiles than LDS holds."""
+
+import numpy as np
+import pytest
+
+from oracle import apc_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+def _blocks(m, lo, hi, seed):
+    p = np.random.default_rng(seed).integers(lo, hi + 1, m)
+    p[0], p[-1] = lo, hi
+    return np.concatenate([[0], np.cumsum(p)]).astype(np.int64)
+
+
+# m, smallest and largest block, n: one tile per block and two; a ragged last column group;
+# more blocks than the sums kept in registers; FP64 tiles past what LDS holds (FP32 within).
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-10), ("f32", 1e-5)])
+@pytest.mark.parametrize("m,lo,hi,n", [(3, 1, 40, 41), (17, 5, 33, 257), (131, 1, 20, 513),
+                                       (500, 1, 3, 170)])
+def test_trajectory(m, lo, hi, n, prec, tol):
+    """20 updates against the oracle's."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    off = _blocks(m, lo, hi, 10 * m + n)
+    rng = np.random.default_rng(m)
+    A = rng.standard_normal((off[-1], n)) / np.sqrt(n)
+    xs = rng.standard_normal((n, 1))
+    B = A @ xs
+    g, e = 1.2, 1.1
+    ref = O.apc_run(A, B, off, T=20, gamma=g, eta=e, keep_traj=True)["traj"][20]
+    plan = apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), off, prec,
+                    gamma=g, eta=e)
+    assert plan.resident_shape() or plan.single_pass_shape()
+    plan.iterate_timed(20)
+    got = plan.xbar().cpu().numpy().reshape(n, 1)
+    dev = np.linalg.norm(got - ref) / np.linalg.norm(xs)
+    print(f"{prec} m={m} n={n}: dev {dev:.2e}", flush=True)
+    assert dev <= tol
