@@ -440,6 +440,7 @@ struct apc_plan_s {
   int32_t passa_nt = 1;                // k = 1 pass A: non-temporal loads of C
   bool fused = false;                  // k = 1: both halves of eq. (2a) in one pass over C
   int32_t fused_rows = 0, fused_g = 0, ntiles_f = 0;
+  bool fused_once = false;             // tiles short enough for k_fused_once
   int64_t ntiles_tr = 0;               // triangular-product row tiles over all blocks
   int32_t fused_tpb = 0;               // > 0: every block has this many single-pass tiles
   bool resident = false;               // k = 1 FP64: T updates in one launch (k_resident)
@@ -547,11 +548,13 @@ apc_status fused_pass(apc_plan_s* P) {
     FusedArgs<float, float> a{P->at<float>(L.C32), L.ldc, P->n, P->tf(0), P->tf(1), P->tf(2),
                               P->ntiles_f, P->at<float>(L.dv), P->state_ld(),
                               P->at<float>(L.fpart), L.ldc, remap};
+    a.once = P->fused_once;
     HIP_TRY(launch_fused_f32(a, P->fused_g, P->stream));
   } else {
     FusedArgs<double, double> a{P->C64(), L.ldc, P->n, P->tf(0), P->tf(1), P->tf(2),
                                 P->ntiles_f, P->at<double>(L.dv), P->state_ld(),
                                 P->at<double>(L.fpart), L.ldc, remap};
+    a.once = P->fused_once;
     HIP_TRY(launch_fused_f64(a, P->fused_g, P->stream));
   }
   return APC_OK;
@@ -629,6 +632,7 @@ apc_status orthogonality_defect(apc_plan_s* P, const double* C, double* defect, 
     for (int app = 0; app < 2; ++app) {
       FusedArgs<double, double> a{C, L.ldc, P->n, P->tf(0), P->tf(1), P->tf(2), P->ntiles_f,
                                   app == 0 ? zd : U, app == 0 ? 0 : L.ldc, part, L.ldc, remap};
+      a.once = P->fused_once;
       HIP_TRY(launch_fused_f64(a, g, st));
       HIP_TRY(launch_block_sum(part, L.ldc, P->tf(3), P->m, L.ldc, app == 0 ? U : V, L.ldc, st));
     }
@@ -1202,6 +1206,7 @@ apc_status normal_matvec(apc_plan_s* P, const NormalOp& op, const double* v, dou
       if (!v32_ready) HIP_TRY(launch_cast_f32(v, v32, L.ldc, P->stream));
       FusedArgs<float, float> a{static_cast<const float*>(op.C), L.ldc, P->n, P->tf(0), P->tf(1),
                                 P->tf(2), P->ntiles_f, v32, 0, part32, L.ldc, remap};
+      a.once = P->fused_once;
       HIP_TRY(launch_fused_f32(a, P->fused_g, P->stream));
       if (defer) {
         *defer = DeferredSum{part32, true, L.ldc, P->ntiles_f, op.scale};
@@ -1212,6 +1217,7 @@ apc_status normal_matvec(apc_plan_s* P, const NormalOp& op, const double* v, dou
     } else {
       FusedArgs<double, double> a{static_cast<const double*>(op.C), L.ldc, P->n, P->tf(0),
                                   P->tf(1), P->tf(2), P->ntiles_f, v, 0, part, L.ldc, remap};
+      a.once = P->fused_once;
       HIP_TRY(launch_fused_f64(a, cpt64 >= 16 ? 1 : 2, P->stream));
     }
     if (defer) {
@@ -1820,6 +1826,10 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
   P->fused = fused;
   P->fused_rows = fused_rows;
   P->fused_g = fused_g;
+  // Tiles of 16 rows (fewer than 8192 rows in all): whole in registers where
+  // rows are narrow enough, unless the looping kernel's groups are asked for.
+  P->fused_once = fused_rows > 0 && fused_rows <= kFusedOnceRows &&
+                  std::getenv("APC_FUSED_G") == nullptr;
   P->ntiles_f = static_cast<int32_t>(T.f_row0.size());
   P->ntiles_tr = T.toff.back();
   {
@@ -3268,11 +3278,13 @@ apc_status hbm_update(apc_hbm_s* H) {
       FusedArgs<float, double> a{static_cast<const float*>(H->C), L.ldc, P->n, P->tf(0),
                                  P->tf(1), P->tf(2), P->ntiles_f, H->x, 0, part, L.ldc, remap,
                                  H->d};
+      a.once = P->fused_once;
       HIP_TRY(launch_fused_f32x64(a, 1, P->stream));
     } else {
       FusedArgs<double, double> a{static_cast<const double*>(H->C), L.ldc, P->n, P->tf(0),
                                   P->tf(1), P->tf(2), P->ntiles_f, H->x, 0, part, L.ldc, remap,
                                   H->d};
+      a.once = P->fused_once;
       HIP_TRY(launch_fused_f64(a, cpt64 >= 16 ? 1 : 2, P->stream));
     }
     HIP_TRY(launch_fused_sum(part, L.ldc, P->ntiles_f, L.ldc, 1.0, H->Y, P->stream));

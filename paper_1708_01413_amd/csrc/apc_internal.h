@@ -114,6 +114,44 @@ __device__ inline double swap_add16(double& a, double& b) {
   return na + nb;
 }
 
+// The same for FP32.
+__device__ inline float swap_add32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float swap_add16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int CTRL>
+__device__ inline double dpp_add(double v, double send) { return v + dpp_f64<CTRL>(send); }
+template <int CTRL>
+__device__ inline float dpp_add(float v, float send) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), CTRL, 0xf, 0xf, false));
+}
+
+__device__ inline double lane_value(double v, int l) { return lane_f64(v, l); }
+__device__ inline float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// Sixteen rows the same way, the sum of row l / 4 left in lane l.
+template <typename T>
+__device__ inline T row_sum16(T (&v)[16], int lane) {
+  T h[8], g[4], f[2];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) h[k] = swap_add32(v[k], v[k + 8]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) g[k] = swap_add16(h[k], h[k + 4]);
+  const bool up8 = (lane & 8) != 0, up4 = (lane & 4) != 0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    f[k] = dpp_add<0x128>(up8 ? g[k + 2] : g[k], up8 ? g[k] : g[k + 2]);  // row_ror:8
+  T r = dpp_add<0x141>(up4 ? f[1] : f[0], up4 ? f[0] : f[1]);              // row_half_mirror
+  r = dpp_add<0xB1>(r, r);   // quad_perm(1, 0, 3, 2)
+  return dpp_add<0x4E>(r, r);  // quad_perm(2, 3, 0, 1)
+}
+
 template <int R>
 __device__ inline void row_sums(double (&v)[R], double (&w)[R], int lane) {
   static_assert(R == 1 || R == 2 || R == 4 || R == 8, "rows per wave");
@@ -294,7 +332,10 @@ struct FusedArgs {
   int64_t ldp;
   int32_t xcd_remap;          // 1: give each XCD a contiguous range of tiles
   const TA* wsub = nullptr;   // optional: w_r = C[r][:] . d_blk - wsub[r] (global row r)
+  bool once = false;          // no tile has more than kFusedOnceRows rows: k_fused_once may run
 };
+constexpr int kFusedOnceRows = 16;      // rows and 16-byte chunks per row of a tile held whole
+constexpr int kFusedOnceChunks = 1024;
 // cpt for a row width: the smallest of 1, 2, 4, 8, 16 that covers it (0 when
 // none does).  A launcher accepts g in 1, 2, 4 when fused_shape_ok: the two
 // register groups, d_blk and the partial sum fit 256 registers per thread

@@ -513,6 +513,86 @@ __global__ __launch_bounds__(kThreads) void k_fused(FusedArgs<TQ, TA> a) {
       store_run<TA, W>(out + c * kThreads * W, acc[c]);
 }
 
+// 16 bytes at byte offset off of a buffer of the given size; past it, zeros.
+template <typename T, int W>
+__device__ inline void buffer_load_run(const T* base, uint32_t bytes, uint32_t off, T (&o)[W]) {
+  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, static_cast<int>(bytes),
+                                                   0x00027000);
+  const u32x4_t v = __builtin_bit_cast(
+      u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(off), 0, 0));
+  __builtin_memcpy(&o, &v, 16);
+}
+
+// k_fused for tiles of at most 16 rows of at most 16 KiB, the small problems:
+// thread t owns the 16-byte chunk t of every row and all rows' loads are in
+// flight at once, so the tile costs one memory round trip and one barrier.
+// Bound by that latency (4.2 us with the launch, for any size up to about
+// 24 MB of C), above it by the rate of the cache that holds C.  In k_fused the
+// same tiles are eight steps of two rows, a barrier and a wait each.  Per
+// launch, k_fused -> this: FP64 9.3 -> 4.3 us at 1500 x 1200, 10.4 -> 7.1 at
+// 3000 x 1500, 15.7 -> 15.4 at 4000 x 2000; FP32 8.6 -> 4.3 at 3000 x 1500,
+// 9.8 -> 7.4 at 4000 x 2000, 18.2 -> 16.4 at 6181 x 3535.  The loads are plain
+// ones: C stays in the caches between launches, and non-temporal loads took
+// 4.9, 8.2 and 19.2 us at the last three.  Rows past the tile and threads past
+// column n read zeros (the buffer's size ends at the tile's last row).
+template <typename TQ, typename TA>
+__global__ __launch_bounds__(kFusedOnceChunks) void k_fused_once(FusedArgs<TQ, TA> a) {
+  constexpr int W = V16<TQ>::W, R = kFusedOnceRows;
+  int q = blockIdx.x;
+  if (a.xcd_remap == 1) {
+    const int per = (a.ntiles + kXcds - 1) / kXcds;
+    q = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+  }
+  if (q >= a.ntiles) return;
+  const int row0 = a.tile_row0[q];
+  const int nrows = a.tile_nrows[q];
+  const TA* dblk = a.d + static_cast<int64_t>(a.tile_blk[q]) * a.ldd;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int64_t j = static_cast<int64_t>(threadIdx.x) * W;
+  const bool ok = j < a.n;
+  const uint32_t bytes = static_cast<uint32_t>(nrows) * static_cast<uint32_t>(a.ldc * sizeof(TQ));
+  TQ b[R][W];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    buffer_load_run<TQ, W>(a.C + static_cast<int64_t>(row0) * a.ldc, bytes,
+                               ok ? (r * static_cast<uint32_t>(a.ldc) + static_cast<uint32_t>(j)) *
+                                        static_cast<uint32_t>(sizeof(TQ))
+                                  : 0x7ffffff0u,
+                               b[r]);
+  TA dv[W];
+#pragma unroll
+  for (int e = 0; e < W; ++e) dv[e] = j + e < a.n ? dblk[j + e] : TA(0);
+  const int lr = lane & (R - 1);
+  const TA sub = a.wsub && lr < nrows ? a.wsub[row0 + lr] : TA(0);
+
+  __shared__ TA red[kFusedOnceChunks / 64][R];
+  TA s[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    s[r] = TA(0);
+#pragma unroll
+    for (int e = 0; e < W; ++e) s[r] = fma(static_cast<TA>(b[r][e]), dv[e], s[r]);
+  }
+  const TA mine = row_sum16(s, lane);
+  if ((lane & 3) == 0) red[wv][lane >> 2] = mine;
+  __syncthreads();
+  // Lane r (and r + 16, ...) sums row r over the waves, in wave order.
+  TA w = TA(0);
+  for (int v = 0; v < nw; ++v) w += red[v][lr];
+  w -= sub;
+  TA acc[W];
+#pragma unroll
+  for (int e = 0; e < W; ++e) acc[e] = TA(0);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const TA wr = lane_value(w, r);
+#pragma unroll
+    for (int e = 0; e < W; ++e) acc[e] = fma(wr, static_cast<TA>(b[r][e]), acc[e]);
+  }
+  if (j < a.ldc) store_run<TA, W>(a.part + static_cast<int64_t>(q) * a.ldp + j, acc);
+}
+
 // The x_i update, the average and the next differences after k_fused.  A
 // workgroup owns kCombineCols = 16 columns; its 16 lanes per column take every
 // sixteenth block, U blocks at a time with all their loads issued before any
@@ -1794,11 +1874,15 @@ int fused_cpt(int64_t ldc, int elem_bytes) {
   return 0;
 }
 
+template <typename TQ, typename TA>
+static unsigned fused_grid(const FusedArgs<TQ, TA>& a) {
+  return a.xcd_remap == 1 ? static_cast<unsigned>((a.ntiles + kXcds - 1) / kXcds * kXcds)
+                          : static_cast<unsigned>(a.ntiles);
+}
+
 template <typename TQ, typename TA, int CPT, int G>
 static hipError_t fused_launch(const FusedArgs<TQ, TA>& a, hipStream_t s) {
-  const unsigned grid = a.xcd_remap == 1
-                            ? static_cast<unsigned>((a.ntiles + kXcds - 1) / kXcds * kXcds)
-                            : static_cast<unsigned>(a.ntiles);
+  const unsigned grid = fused_grid(a);
   if (grid == 0) return hipSuccess;
   APC_LAUNCH((k_fused<TQ, TA, CPT, G>), dim3(grid), dim3(kThreads), 0, s, a);
   return hipGetLastError();
@@ -1835,6 +1919,18 @@ static hipError_t fused_g(const FusedArgs<TQ, TA>& a, int g, hipStream_t s) {
 
 template <typename TQ, typename TA>
 static hipError_t fused_impl(const FusedArgs<TQ, TA>& a, int g, hipStream_t s) {
+  // Not for an FP32 factor with FP64 sums: 16 rows' sums at eight registers
+  // per chunk spill.
+  if constexpr (sizeof(TQ) == sizeof(TA)) {
+    const int64_t chunks = a.ldc * static_cast<int64_t>(sizeof(TQ)) / 16;
+    if (a.once && chunks <= kFusedOnceChunks) {
+      const unsigned grid = fused_grid(a);
+      if (grid == 0) return hipSuccess;
+      const unsigned threads = static_cast<unsigned>((chunks + 63) / 64 * 64);
+      APC_LAUNCH((k_fused_once<TQ, TA>), dim3(grid), dim3(threads), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   switch (fused_cpt(a.ldc, sizeof(TQ))) {
     case 1: return fused_g<TQ, TA, 1>(a, g, s);
     case 2: return fused_g<TQ, TA, 2>(a, g, s);

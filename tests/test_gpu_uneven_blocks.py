@@ -40,3 +40,31 @@ def test_trajectory(m, lo, hi, n, prec, tol):
     dev = np.linalg.norm(got - ref) / np.linalg.norm(xs)
     print(f"{prec} m={m} n={n}: dev {dev:.2e}", flush=True)
     assert dev <= tol
+
+
+# Rows of one 16-byte chunk and one wave; either side of a wave's width; the widest rows
+# whose tiles are held whole, and one column more.
+@pytest.mark.parametrize("prec,tol,n", [("f64", 1e-10, n) for n in (1, 127, 130, 2048, 2049)] +
+                         [("f32", 1e-5, n) for n in (3, 255, 258, 4096, 4097)])
+def test_tiles_held_whole(n, prec, tol):
+    """20 updates on blocks of 1 to 65 rows (tiles of 16 and remainders), against
+    the oracle's."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    p = [min(h, n) for h in (1, 65, 17, 15, 32)]
+    while sum(p) < n:
+        p.append(min(65, n))
+    off = np.concatenate([[0], np.cumsum(p)]).astype(np.int64)
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((off[-1], n)) / np.sqrt(n)
+    xs = rng.standard_normal((n, 1))
+    B = A @ xs
+    g, e = 1.2, 1.1
+    ref = O.apc_run(A, B, off, T=20, gamma=g, eta=e, keep_traj=True)["traj"][20]
+    plan = apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), off, prec,
+                    gamma=g, eta=e)
+    plan.iterate_timed(20)
+    dev = np.linalg.norm(plan.xbar().cpu().numpy().reshape(n, 1) - ref) / np.linalg.norm(xs)
+    print(f"{prec} n={n} N={off[-1]}: dev {dev:.2e}", flush=True)
+    assert dev <= tol
