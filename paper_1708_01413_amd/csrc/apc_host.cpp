@@ -2569,7 +2569,7 @@ struct apc_batch_s {
   int32_t* item_start = nullptr;
   double* partial = nullptr;
   double* relres = nullptr;
-  int32_t gridA = 1024, gridB = 1024, gridV = 1024;
+  int32_t gridA = 1024, gridB = 1024, gridV = 1024, gridW = 1;
   float tuned_us = 0.f;
   std::vector<int32_t> h_active;
   std::map<std::pair<int32_t, int32_t>, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
@@ -2864,7 +2864,7 @@ apc_status batch_update(apc_batch_s* B) {
   }
   if (B->fused) {
     HIP_TRY(launch_batch_fused(B->gridA, B->sys, B->itemsF, B->nF, B->active, B->stream));
-    HIP_TRY(launch_batch_fused_combine(B->gridV, B->sys, B->itemsW, B->nW, B->active, B->stream));
+    HIP_TRY(launch_batch_fused_combine(B->gridW, B->sys, B->itemsW, B->nW, B->active, B->stream));
     return APC_OK;
   }
   HIP_TRY(launch_batch_pass_a(0, B->gridA, B->sys, B->itemsA, B->nA, B->active, B->stream));
@@ -2999,11 +2999,13 @@ apc_status apc_batch_create(apc_batch* out, const apc_plan* plans, int32_t count
   }
   HIP_TRY(hipMemcpyAsync(B->active, B->h_active.data(), count * 4, hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(B->item_start, it.start.data(), it.start.size() * 4, hipMemcpyHostToDevice, st));
+  // One workgroup per combine item.
+  B->gridW = std::max(1, B->nW);
   // Persistent grid: time the pass over the factors for a few workgroup
   // counts and use the fastest for every pass, unless the environment fixes it.
   if (const char* e = std::getenv("APC_BATCH_GRID")) {
     const int g = std::max(1, std::atoi(e));
-    B->gridA = B->gridB = B->gridV = g;
+    B->gridA = B->gridB = B->gridV = B->gridW = g;
   } else {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIP_TRY(hipEventCreate(&e0));

@@ -68,3 +68,31 @@ def test_tiles_held_whole(n, prec, tol):
     dev = np.linalg.norm(plan.xbar().cpu().numpy().reshape(n, 1) - ref) / np.linalg.norm(xs)
     print(f"{prec} n={n} N={off[-1]}: dev {dev:.2e}", flush=True)
     assert dev <= tol
+
+
+def test_batch_combine():
+    """One batch of systems with one row tile per block (fewer, exactly and more blocks than
+    stay in registers; columns around a workgroup's 64) and with several: 20 updates."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    g, e = 1.2, 1.1
+    plans, refs = [], []
+    for s, (p, n) in enumerate([([1], 1), ([21, 22, 22], 65), ([4] * 15 + [3], 63),
+                                ([9] * 16 + [1], 130), ([20] * 39 + [7], 700),
+                                ([600, 1, 257] + [5] * 15, 640)]):
+        off = np.concatenate([[0], np.cumsum(p)]).astype(np.int64)
+        rng = np.random.default_rng(s)
+        A = rng.standard_normal((off[-1], n)) / np.sqrt(n)
+        xs = rng.standard_normal(n)
+        refs.append((O.apc_run(A, (A @ xs)[:, None], off, T=20, gamma=g, eta=e)["xbar"][:, 0],
+                     np.linalg.norm(xs)))
+        plans.append(apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(A @ xs).cuda(), off,
+                              "f32", gamma=g, eta=e))
+    batch = apc.Batch(plans)
+    batch.iterate(20)
+    for plan, (ref, xn) in zip(plans, refs):
+        dev = np.linalg.norm(plan.xbar().cpu().numpy() - ref) / xn
+        print(f"m={plan.m} n={plan.n}: dev {dev:.2e}", flush=True)
+        assert dev <= 1e-5
+    batch.close()
