@@ -780,7 +780,9 @@ def main():
         avg_f = float(np.sum(pa_ms)) / launches
         avg_c = float(np.sum(av_ms)) / launches
         dom_bytes, dom_ms = bytes_f, avg_f
-        dom_label = f"k_fused<{ptype}, {ptype}, {chunks_per_thread(n, sq)}, {grp}>"
+        # Non-temporal loads of a factor larger than the last-level cache.
+        nt = "true" if N * (-(-n // 64) * 64) * sq > 256 << 20 else "false"
+        dom_label = f"k_fused<{ptype}, {ptype}, {chunks_per_thread(n, sq)}, {grp}, {nt}>"
         dom_fn = "k_fused"
         iteration = {
             "form": "single pass over C per update, then the x_i update + average launch",

@@ -539,6 +539,20 @@ apc_status pass_b(apc_plan_s* P, int i0, int i1, int col) {
   return APC_OK;
 }
 
+// Which single-pass kernel and loads a pass over the plan's tiles takes.  A
+// factor of at most 256 MiB, the size of the last-level cache, stays there
+// between passes with plain loads: per launch, non-temporal -> plain, FP32
+// 26.9 -> 22.5 us at 8192 x 4096 (134 MB), 37.6 -> 30.7 at 8192 x 6000
+// (197 MB), 56.4 -> 53.6 at 8192 x 8192 (268 MB, 256 MiB); FP64 37.3 -> 31.3 at
+// 6181 x 4096 (203 MB), 44.8 -> 42.8 at 8192 x 4096 (268 MB).  Above it plain
+// loads lose: 51.2 -> 53.3 at 12000 x 6005 in FP32 (288 MB), 83 -> 92 at
+// 16384 x 8192 (537 MB).
+template <typename Args>
+void fused_route(const apc_plan_s* P, Args* a) {
+  a->once = P->fused_once;
+  a->cached = P->N * a->ldc * static_cast<int64_t>(sizeof *a->C) <= kLlcBytes;
+}
+
 // Both halves of eq. (2a) in one pass over C (k = 1): every single-pass tile
 // writes its part of Q_i w_i, w = C_i d_i formed row by row on the way.
 apc_status fused_pass(apc_plan_s* P) {
@@ -548,13 +562,13 @@ apc_status fused_pass(apc_plan_s* P) {
     FusedArgs<float, float> a{P->at<float>(L.C32), L.ldc, P->n, P->tf(0), P->tf(1), P->tf(2),
                               P->ntiles_f, P->at<float>(L.dv), P->state_ld(),
                               P->at<float>(L.fpart), L.ldc, remap};
-    a.once = P->fused_once;
+    fused_route(P, &a);
     HIP_TRY(launch_fused_f32(a, P->fused_g, P->stream));
   } else {
     FusedArgs<double, double> a{P->C64(), L.ldc, P->n, P->tf(0), P->tf(1), P->tf(2),
                                 P->ntiles_f, P->at<double>(L.dv), P->state_ld(),
                                 P->at<double>(L.fpart), L.ldc, remap};
-    a.once = P->fused_once;
+    fused_route(P, &a);
     HIP_TRY(launch_fused_f64(a, P->fused_g, P->stream));
   }
   return APC_OK;
@@ -632,7 +646,7 @@ apc_status orthogonality_defect(apc_plan_s* P, const double* C, double* defect, 
     for (int app = 0; app < 2; ++app) {
       FusedArgs<double, double> a{C, L.ldc, P->n, P->tf(0), P->tf(1), P->tf(2), P->ntiles_f,
                                   app == 0 ? zd : U, app == 0 ? 0 : L.ldc, part, L.ldc, remap};
-      a.once = P->fused_once;
+      fused_route(P, &a);
       HIP_TRY(launch_fused_f64(a, g, st));
       HIP_TRY(launch_block_sum(part, L.ldc, P->tf(3), P->m, L.ldc, app == 0 ? U : V, L.ldc, st));
     }
@@ -1206,7 +1220,7 @@ apc_status normal_matvec(apc_plan_s* P, const NormalOp& op, const double* v, dou
       if (!v32_ready) HIP_TRY(launch_cast_f32(v, v32, L.ldc, P->stream));
       FusedArgs<float, float> a{static_cast<const float*>(op.C), L.ldc, P->n, P->tf(0), P->tf(1),
                                 P->tf(2), P->ntiles_f, v32, 0, part32, L.ldc, remap};
-      a.once = P->fused_once;
+      fused_route(P, &a);
       HIP_TRY(launch_fused_f32(a, P->fused_g, P->stream));
       if (defer) {
         *defer = DeferredSum{part32, true, L.ldc, P->ntiles_f, op.scale};
@@ -1217,7 +1231,7 @@ apc_status normal_matvec(apc_plan_s* P, const NormalOp& op, const double* v, dou
     } else {
       FusedArgs<double, double> a{static_cast<const double*>(op.C), L.ldc, P->n, P->tf(0),
                                   P->tf(1), P->tf(2), P->ntiles_f, v, 0, part, L.ldc, remap};
-      a.once = P->fused_once;
+      fused_route(P, &a);
       HIP_TRY(launch_fused_f64(a, cpt64 >= 16 ? 1 : 2, P->stream));
     }
     if (defer) {
@@ -3280,13 +3294,13 @@ apc_status hbm_update(apc_hbm_s* H) {
       FusedArgs<float, double> a{static_cast<const float*>(H->C), L.ldc, P->n, P->tf(0),
                                  P->tf(1), P->tf(2), P->ntiles_f, H->x, 0, part, L.ldc, remap,
                                  H->d};
-      a.once = P->fused_once;
+      fused_route(P, &a);
       HIP_TRY(launch_fused_f32x64(a, 1, P->stream));
     } else {
       FusedArgs<double, double> a{static_cast<const double*>(H->C), L.ldc, P->n, P->tf(0),
                                   P->tf(1), P->tf(2), P->ntiles_f, H->x, 0, part, L.ldc, remap,
                                   H->d};
-      a.once = P->fused_once;
+      fused_route(P, &a);
       HIP_TRY(launch_fused_f64(a, cpt64 >= 16 ? 1 : 2, P->stream));
     }
     HIP_TRY(launch_fused_sum(part, L.ldc, P->ntiles_f, L.ldc, 1.0, H->Y, P->stream));

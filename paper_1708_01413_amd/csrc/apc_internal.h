@@ -332,8 +332,10 @@ struct FusedArgs {
   int64_t ldp;
   int32_t xcd_remap;          // 1: give each XCD a contiguous range of tiles
   const TA* wsub = nullptr;   // optional: w_r = C[r][:] . d_blk - wsub[r] (global row r)
+  bool cached = false;        // C fits the last-level cache: plain loads, not non-temporal
   bool once = false;          // no tile has more than kFusedOnceRows rows: k_fused_once may run
 };
+constexpr int64_t kLlcBytes = int64_t{256} << 20;
 constexpr int kFusedOnceRows = 16;      // rows and 16-byte chunks per row of a tile held whole
 constexpr int kFusedOnceChunks = 1024;
 // cpt for a row width: the smallest of 1, 2, 4, 8, 16 that covers it (0 when

@@ -418,7 +418,7 @@ __device__ inline void store_run(T* p, const T (&v)[W]) {
 // group's dot products are reduced across the workgroup (a wave sum each, then
 // the four wave values through LDS), the next group's loads are in flight; the
 // LDS slot alternates between groups, so one barrier per group is enough.
-template <typename TQ, typename TA, int CPT, int G>
+template <typename TQ, typename TA, int CPT, int G, bool NT>
 __global__ __launch_bounds__(kThreads) void k_fused(FusedArgs<TQ, TA> a) {
   constexpr int W = V16<TQ>::W;
   int q = blockIdx.x;
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kThreads) void k_fused(FusedArgs<TQ, TA> a) {
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         if (row_ok && ok[c]) {
-          V16<TQ>::template load<true>(base + static_cast<int64_t>(r0 + r) * a.ldc + c * kThreads * W,
+          V16<TQ>::template load<NT>(base + static_cast<int64_t>(r0 + r) * a.ldc + c * kThreads * W,
                                        b[r][c]);
         } else {
 #pragma unroll
@@ -1884,7 +1884,10 @@ template <typename TQ, typename TA, int CPT, int G>
 static hipError_t fused_launch(const FusedArgs<TQ, TA>& a, hipStream_t s) {
   const unsigned grid = fused_grid(a);
   if (grid == 0) return hipSuccess;
-  APC_LAUNCH((k_fused<TQ, TA, CPT, G>), dim3(grid), dim3(kThreads), 0, s, a);
+  if (a.cached)
+    APC_LAUNCH((k_fused<TQ, TA, CPT, G, false>), dim3(grid), dim3(kThreads), 0, s, a);
+  else
+    APC_LAUNCH((k_fused<TQ, TA, CPT, G, true>), dim3(grid), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
