@@ -85,6 +85,7 @@ struct Tiles {
   std::vector<int64_t> toff;                     // triangular-product row tiles before block i (m+1)
   std::vector<int32_t> f_row0, f_nrows, f_blk;  // single-pass row tiles (k = 1)
   std::vector<int32_t> f_first;                 // first single-pass tile of every block (m+1)
+  std::vector<int32_t> f_wg;                    // first tile of every workgroup (even split only)
 };
 
 constexpr int kFusedMinRows = 16;  // the workspace holds single-pass tiles of this height or more
@@ -102,15 +103,50 @@ void build_fused_tiles(const int64_t* off, int32_t m, int rows_per_tile, Tiles* 
   }
 }
 
+// Even split: every one of nwg workgroups takes N / nwg consecutive rows, one
+// tile per block that they touch.  A cut within a thirty-second of a
+// workgroup's rows of a block's start moves there.
+void build_even_tiles(const int64_t* off, int32_t m, int32_t nwg, Tiles* T) {
+  T->f_row0.clear();
+  T->f_nrows.clear();
+  T->f_blk.clear();
+  T->f_first.assign(1, 0);
+  T->f_wg.clear();
+  const int64_t N = off[m], snap = N / nwg / 32;
+  int32_t i = 0;
+  int64_t r = 0;
+  for (int32_t q = 0; q < nwg; ++q) {
+    T->f_wg.push_back(static_cast<int32_t>(T->f_row0.size()));
+    int64_t end = N * (q + 1) / nwg;
+    const int64_t* at = std::lower_bound(off, off + m + 1, end);  // off[m] = N >= end
+    if (*at - end <= snap) end = *at;
+    else if (end - at[-1] <= snap) end = at[-1];
+    while (r < end) {
+      const int64_t stop = std::min(end, off[i + 1]);
+      T->f_row0.push_back(static_cast<int32_t>(r));
+      T->f_nrows.push_back(static_cast<int32_t>(stop - r));
+      T->f_blk.push_back(i);
+      r = stop;
+      if (r == off[i + 1]) {
+        T->f_first.push_back(static_cast<int32_t>(T->f_row0.size()));
+        ++i;
+      }
+    }
+  }
+  T->f_wg.push_back(static_cast<int32_t>(T->f_row0.size()));
+}
+
 // Default single-pass shape: two rows per register group (one at the widest
 // rows, where two spill), and tiles of 64 rows, fewer when that leaves under
-// about one workgroup per CU.  At 16384 x 8192 in FP32, 64 rows and groups of
+// about one workgroup per CU, two where a thread has two 16-byte chunks of a
+// row or fewer (FP32 19.6 -> 12.6 us at 16384 x 1000 with 32 rows, 13.9 -> 11.7
+// at 8192 x 2000 with 16; wider rows measured the same or slower).  At 16384 x 8192 in FP32, 64 rows and groups of
 // two measured best (85.5 us per launch against 88-145 us for 16-128 rows and
 // groups of one to four).
 void fused_shape(int64_t N, int elem, int cpt, int32_t* rows, int32_t* g) {
   *g = fused_shape_ok(elem, elem, cpt, 2) ? 2 : 1;
   int32_t r = 64;
-  while (r > kFusedMinRows && N / r < 256) r /= 2;
+  while (r > kFusedMinRows && N / r < (cpt <= 2 ? 512 : 256)) r /= 2;
   *rows = r;
 }
 
@@ -440,6 +476,7 @@ struct apc_plan_s {
   int32_t passa_nt = 1;                // k = 1 pass A: non-temporal loads of C
   bool fused = false;                  // k = 1: both halves of eq. (2a) in one pass over C
   int32_t fused_rows = 0, fused_g = 0, ntiles_f = 0;
+  int32_t fused_nwg = 0;               // > 0: workgroups of the even split (build_even_tiles)
   bool fused_once = false;             // tiles short enough for k_fused_once
   int64_t ntiles_tr = 0;               // triangular-product row tiles over all blocks
   int32_t fused_tpb = 0;               // > 0: every block has this many single-pass tiles
@@ -549,6 +586,10 @@ apc_status pass_b(apc_plan_s* P, int i0, int i1, int col) {
 // 16384 x 8192 (537 MB).
 template <typename Args>
 void fused_route(const apc_plan_s* P, Args* a) {
+  if (P->fused_nwg > 0) {
+    a->wg_first = P->tf(3) + P->m + 1;
+    a->nwg = P->fused_nwg;
+  }
   a->once = P->fused_once;
   a->cached = P->N * a->ldc * static_cast<int64_t>(sizeof *a->C) <= kLlcBytes;
 }
@@ -1502,6 +1543,7 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
     tf.insert(tf.end(), T.f_nrows.begin(), T.f_nrows.end());
     tf.insert(tf.end(), T.f_blk.begin(), T.f_blk.end());
     tf.insert(tf.end(), T.f_first.begin(), T.f_first.end());
+    tf.insert(tf.end(), T.f_wg.begin(), T.f_wg.end());
     HIP_TRY(hipMemcpyAsync(P->at<int32_t>(L.tiles_f), tf.data(), tf.size() * 4, hipMemcpyHostToDevice, st));
   }
   HIP_TRY(hipMemcpyAsync(P->at<int32_t>(L.tiles_t), T.t.data(), T.t.size() * 4, hipMemcpyHostToDevice, st));
@@ -1812,6 +1854,41 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
   // adjoint's scratch.
   HIP_TRY(noalloc_scratch_init(dev));
 
+  // Tiles of fused_rows rows end where blocks end: uneven blocks leave short
+  // tiles, and a few tiles more than CUs leave most CUs idle while some take a
+  // second one.  Where the fullest CU would have over 1.05 of the mean rows, the
+  // rows are split evenly over one workgroup per CU instead -- with rows of 16
+  // chunks per thread (one workgroup per CU) always: an FP64 update 143 -> 99 us
+  // at 8192 x 8192 with 64 blocks of 32 to 256 rows, 138 -> 118 at 12000 x 6005
+  // with 137, 206 -> 139 at 16384 x 5000 with 200 even ones, 245 -> 165 at
+  // 16384 x 7236 with 85.  With 8 chunks two workgroups run per CU and a change
+  // of block costs about a row's time, so only with up to a third as many
+  // blocks as CUs: FP32 62.4 -> 58.6 at 8192 x 8192, 105.5 -> 95.8 at 16384 x
+  // 7236, but 64.4 -> 71.4 at 12000 x 6005.  Narrower rows lose (FP32 24.6 ->
+  // 31.2 at 10000 x 2200 with 100 blocks).
+  int cus = 0;
+  HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const int fused_c = fused ? cpt : cpt32;
+  if (fused_rows > kFusedMinRows && std::getenv("APC_FUSED_ROWS") == nullptr && cus > 0 &&
+      (fused_c >= 16 ? m <= 2 * cus : fused_c == 8 && 3 * m <= cus)) {
+    const int64_t tiles = static_cast<int64_t>(T.f_row0.size());
+    const int64_t fullest = (tiles + cus - 1) / cus * fused_rows;
+    if (20 * fullest * cus > 21 * N) {
+      Tiles E;
+      build_even_tiles(off, m, cus, &E);
+      // The lists and partial rows have to fit the slices of the 16-row tiles.
+      const int64_t nt = static_cast<int64_t>(E.f_row0.size());
+      if (3 * nt + cus + 1 <= 3 * static_cast<int64_t>(L.ntiles_fmax)) {
+        T.f_row0 = E.f_row0;
+        T.f_nrows = E.f_nrows;
+        T.f_blk = E.f_blk;
+        T.f_first = E.f_first;
+        T.f_wg = E.f_wg;
+        fused_rows = static_cast<int32_t>((N + cus - 1) / cus);
+      }
+    }
+  }
+
   apc_plan_s* P = new (std::nothrow) apc_plan_s();
   if (!P) return fail(APC_EINVAL, "out of host memory");
   P->device = dev;
@@ -1845,6 +1922,7 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
   P->fused_once = fused_rows > 0 && fused_rows <= kFusedOnceRows &&
                   std::getenv("APC_FUSED_G") == nullptr;
   P->ntiles_f = static_cast<int32_t>(T.f_row0.size());
+  P->fused_nwg = T.f_wg.empty() ? 0 : static_cast<int32_t>(T.f_wg.size()) - 1;
   P->ntiles_tr = T.toff.back();
   {
     // At eight or more 16-byte chunks per thread, two-row register groups

@@ -332,6 +332,8 @@ struct FusedArgs {
   int64_t ldp;
   int32_t xcd_remap;          // 1: give each XCD a contiguous range of tiles
   const TA* wsub = nullptr;   // optional: w_r = C[r][:] . d_blk - wsub[r] (global row r)
+  const int32_t* wg_first = nullptr;  // optional, nwg + 1: workgroup q takes tiles wg_first[q] ..
+  int32_t nwg = 0;            // wg_first[q + 1] - 1 in turn (without it, tile q)
   bool cached = false;        // C fits the last-level cache: plain loads, not non-temporal
   bool once = false;          // no tile has more than kFusedOnceRows rows: k_fused_once may run
 };

@@ -417,100 +417,108 @@ __device__ inline void store_run(T* p, const T (&v)[W]) {
 // w_r C[r][:] stay in its registers.  Rows go in groups of G.  While one
 // group's dot products are reduced across the workgroup (a wave sum each, then
 // the four wave values through LDS), the next group's loads are in flight; the
-// LDS slot alternates between groups, so one barrier per group is enough.
+// LDS slot alternates between groups, so one barrier per group is enough.  With
+// wg_first a workgroup takes several tiles in turn, consecutive rows across
+// block boundaries.
 template <typename TQ, typename TA, int CPT, int G, bool NT>
 __global__ __launch_bounds__(kThreads) void k_fused(FusedArgs<TQ, TA> a) {
   constexpr int W = V16<TQ>::W;
-  int q = blockIdx.x;
+  const int nwg = a.wg_first ? a.nwg : a.ntiles;
+  int wg = blockIdx.x;
   if (a.xcd_remap == 1) {
-    const int per = (a.ntiles + kXcds - 1) / kXcds;
-    q = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    const int per = (nwg + kXcds - 1) / kXcds;
+    wg = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
   }
-  if (q >= a.ntiles) return;
-  const int row0 = a.tile_row0[q];
-  const int nrows = a.tile_nrows[q];
-  const TA* dblk = a.d + static_cast<int64_t>(a.tile_blk[q]) * a.ldd;
+  if (wg >= nwg) return;
+  __shared__ TA red[2][kThreads / 64][G];
+  int q = a.wg_first ? a.wg_first[wg] : wg;
+  const int q1 = a.wg_first ? a.wg_first[wg + 1] : wg + 1;
+  for (; q < q1; ++q) {
+    // (Scalars: behind the stores of a tile before, the compiler takes them for vectors.)
+    const int row0 = __builtin_amdgcn_readfirstlane(a.tile_row0[q]);
+    const int nrows = __builtin_amdgcn_readfirstlane(a.tile_nrows[q]);
+    const TA* dblk = a.d + static_cast<int64_t>(__builtin_amdgcn_readfirstlane(a.tile_blk[q])) * a.ldd;
 
-  // A chunk takes part when it starts before column n; C is zero from n to
-  // ldc (a multiple of W), so the chunk's loads stay inside the row.
-  bool ok[CPT];
-  TA dv[CPT][W], acc[CPT][W];
+    // A chunk takes part when it starts before column n; C is zero from n to
+    // ldc (a multiple of W), so the chunk's loads stay inside the row.
+    bool ok[CPT];
+    TA dv[CPT][W], acc[CPT][W];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int64_t j = static_cast<int64_t>(threadIdx.x + c * kThreads) * W;
-    ok[c] = j < a.n;
+    for (int c = 0; c < CPT; ++c) {
+      const int64_t j = static_cast<int64_t>(threadIdx.x + c * kThreads) * W;
+      ok[c] = j < a.n;
 #pragma unroll
-    for (int e = 0; e < W; ++e) {
-      dv[c][e] = j + e < a.n ? dblk[j + e] : TA(0);
-      acc[c][e] = TA(0);
-    }
-  }
-
-  const TQ* base = a.C + static_cast<int64_t>(row0) * a.ldc + threadIdx.x * W;
-  auto load = [&](TQ (&b)[G][CPT][W], int r0) {
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const bool row_ok = r0 + r < nrows;
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        if (row_ok && ok[c]) {
-          V16<TQ>::template load<NT>(base + static_cast<int64_t>(r0 + r) * a.ldc + c * kThreads * W,
-                                       b[r][c]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < W; ++e) b[r][c][e] = TQ(0);
-        }
+      for (int e = 0; e < W; ++e) {
+        dv[c][e] = j + e < a.n ? dblk[j + e] : TA(0);
+        acc[c][e] = TA(0);
       }
     }
-  };
 
-  __shared__ TA red[2][kThreads / 64][G];
-  const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
-  // Rows past the tile were loaded as zeros, so their w is 0 and they add nothing.
-  auto step = [&](const TQ (&b)[G][CPT][W], int r0, int slot) {
-    TA sum[G];
+    const TQ* base = a.C + static_cast<int64_t>(row0) * a.ldc + threadIdx.x * W;
+    auto load = [&](TQ (&b)[G][CPT][W], int r0) {
 #pragma unroll
-    for (int r = 0; r < G; ++r) {
-      sum[r] = TA(0);
+      for (int r = 0; r < G; ++r) {
+        const bool row_ok = r0 + r < nrows;
 #pragma unroll
-      for (int c = 0; c < CPT; ++c)
+        for (int c = 0; c < CPT; ++c) {
+          if (row_ok && ok[c]) {
+            V16<TQ>::template load<NT>(base + static_cast<int64_t>(r0 + r) * a.ldc + c * kThreads * W,
+                                         b[r][c]);
+          } else {
 #pragma unroll
-        for (int e = 0; e < W; ++e) sum[r] = fma(static_cast<TA>(b[r][c][e]), dv[c][e], sum[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const TA v = wave_sum_dpp(sum[r]);
-      if (lane == 0) red[slot][wv][r] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      TA w = (red[slot][0][r] + red[slot][1][r]) + (red[slot][2][r] + red[slot][3][r]);
-      if (a.wsub && r0 + r < nrows) w -= a.wsub[row0 + r0 + r];
-#pragma unroll
-      for (int c = 0; c < CPT; ++c)
-#pragma unroll
-        for (int e = 0; e < W; ++e) acc[c][e] = fma(w, static_cast<TA>(b[r][c][e]), acc[c][e]);
-    }
-  };
+            for (int e = 0; e < W; ++e) b[r][c][e] = TQ(0);
+          }
+        }
+      }
+    };
 
-  TQ b0[G][CPT][W], b1[G][CPT][W];
-  load(b0, 0);
-  for (int r0 = 0; r0 < nrows; r0 += 2 * G) {
-    load(b1, r0 + G);
-    step(b0, r0, 0);
-    load(b0, r0 + 2 * G);
-    step(b1, r0 + G, 1);
+    const int lane = threadIdx.x & 63;
+    const int wv = threadIdx.x >> 6;
+    // Rows past the tile were loaded as zeros, so their w is 0 and they add nothing.
+    auto step = [&](const TQ (&b)[G][CPT][W], int r0, int slot) {
+      TA sum[G];
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        sum[r] = TA(0);
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+#pragma unroll
+          for (int e = 0; e < W; ++e) sum[r] = fma(static_cast<TA>(b[r][c][e]), dv[c][e], sum[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        const TA v = wave_sum_dpp(sum[r]);
+        if (lane == 0) red[slot][wv][r] = v;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        TA w = (red[slot][0][r] + red[slot][1][r]) + (red[slot][2][r] + red[slot][3][r]);
+        if (a.wsub && r0 + r < nrows) w -= a.wsub[row0 + r0 + r];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+#pragma unroll
+          for (int e = 0; e < W; ++e) acc[c][e] = fma(w, static_cast<TA>(b[r][c][e]), acc[c][e]);
+      }
+    };
+
+    TQ b0[G][CPT][W], b1[G][CPT][W];
+    load(b0, 0);
+    for (int r0 = 0; r0 < nrows; r0 += 2 * G) {
+      load(b1, r0 + G);
+      step(b0, r0, 0);
+      load(b0, r0 + 2 * G);
+      step(b1, r0 + G, 1);
+    }
+
+    // Every chunk inside the padded row is written (zeros past n), so a partial
+    // row is defined on all of [0, ldc).
+    TA* out = a.part + static_cast<int64_t>(q) * a.ldp + threadIdx.x * W;
+#pragma unroll
+    for (int c = 0; c < CPT; ++c)
+      if (static_cast<int64_t>(threadIdx.x + c * kThreads) * W < a.ldc)
+        store_run<TA, W>(out + c * kThreads * W, acc[c]);
   }
-
-  // Every chunk inside the padded row is written (zeros past n), so a partial
-  // row is defined on all of [0, ldc).
-  TA* out = a.part + static_cast<int64_t>(q) * a.ldp + threadIdx.x * W;
-#pragma unroll
-  for (int c = 0; c < CPT; ++c)
-    if (static_cast<int64_t>(threadIdx.x + c * kThreads) * W < a.ldc)
-      store_run<TA, W>(out + c * kThreads * W, acc[c]);
 }
 
 // 16 bytes at byte offset off of a buffer of the given size; past it, zeros.
@@ -1876,8 +1884,8 @@ int fused_cpt(int64_t ldc, int elem_bytes) {
 
 template <typename TQ, typename TA>
 static unsigned fused_grid(const FusedArgs<TQ, TA>& a) {
-  return a.xcd_remap == 1 ? static_cast<unsigned>((a.ntiles + kXcds - 1) / kXcds * kXcds)
-                          : static_cast<unsigned>(a.ntiles);
+  const int nwg = a.wg_first ? a.nwg : a.ntiles;
+  return static_cast<unsigned>(a.xcd_remap == 1 ? (nwg + kXcds - 1) / kXcds * kXcds : nwg);
 }
 
 template <typename TQ, typename TA, int CPT, int G>
@@ -2001,11 +2009,13 @@ static hipError_t fused_combine_impl(const FusedCombineArgs<TD>& a, hipStream_t 
     case 4: APC_LAUNCH((k_fused_combine<TD, 4>), grid, dim3(256), 0, s, a); break;
     case 8: APC_LAUNCH((k_fused_combine<TD, 8>), grid, dim3(256), 0, s, a); break;
     default: {
-      // Staged up to what one workgroup's LDS holds without a larger limit
-      // (the kernel's static part is 2.2 KB): 479 FP64 or 957 FP32 tiles.
+      // Staged up to what a CU's 160 KB of LDS hold (the kernel's static part is
+      // 2.2 KB): about 1200 FP64 or 2400 FP32 tiles.  Past 64 KB one workgroup
+      // runs per CU, still the faster one: 20.6 -> 12.4 us at 16384 x 1000 with
+      // 1024 FP32 tiles, 39 -> 32 at 16384 x 7236 with 1100 FP64 tiles.
       const size_t lds = static_cast<size_t>(a.ntiles) * kCombineCols * sizeof(TD) +
                          (static_cast<size_t>(a.m) + 1) * 4;
-      if (lds <= 60 * 1024)
+      if (lds <= 150 * 1024)
         APC_LAUNCH((k_fused_combine_staged<TD>), grid, dim3(256), lds, s, a);
       else
         APC_LAUNCH((k_fused_combine<TD, 0>), grid, dim3(256), 0, s, a);

@@ -96,3 +96,33 @@ def test_batch_combine():
         print(f"m={plan.m} n={plan.n}: dev {dev:.2e}", flush=True)
         assert dev <= 1e-5
     batch.close()
+
+
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-10), ("f32", 1e-5)])
+@pytest.mark.parametrize("m,lo,hi,n", [(70, 3, 250, 4100), (4, 1000, 1100, 4100),
+                                       (300, 20, 36, 4100)])
+def test_rows_split_evenly(m, lo, hi, n, prec, tol):
+    """Tall systems whose workgroups take consecutive rows across block boundaries (a few
+    blocks per workgroup or workgroups per block): 12 updates."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    off = _blocks(m, min(lo, n), min(hi, n), m)
+    while off[-1] < 8192:
+        off = np.append(off, off[-1] + min(min(hi, n), 8250 - off[-1]))
+    rng = np.random.default_rng(m)
+    A = rng.standard_normal((off[-1], n)) / np.sqrt(n)
+    xs = rng.standard_normal((n, 1))
+    B = A @ xs
+    g, e = 1.2, 1.1
+    ref = O.apc_run(A, B, off, T=12, gamma=g, eta=e, keep_traj=True)["traj"][12]
+    plan = apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), off, prec,
+                    gamma=g, eta=e)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if prec == "f64" or 3 * m <= cus:
+        assert plan.single_pass_shape()["rows_per_wg"] == -(-int(off[-1]) // cus)
+    plan.iterate_timed(12)
+    dev = np.linalg.norm(plan.xbar().cpu().numpy().reshape(n, 1) - ref) / np.linalg.norm(xs)
+    print(f"{prec} m={len(off) - 1} N={off[-1]} n={n} {plan.single_pass_shape()}: dev {dev:.2e}",
+          flush=True)
+    assert dev <= tol
