@@ -255,7 +255,7 @@ __device__ __attribute__((always_inline)) inline void fused_item(const BatchSys&
   else if (S.ldc <= 512) batch_tile_pass<2, INFLIGHT>(S, row0, nrows, blk, red);
   else batch_tile_pass<4, INFLIGHT>(S, row0, nrows, blk, red);
   __syncthreads();
-  const gptr<float> out = to_global(S.part) + static_cast<int64_t>(t) * S.ldc;
+  float* out = S.part + static_cast<int64_t>(t) * S.ldc;
   for (int64_t j = threadIdx.x; j < S.ldc; j += 256)
     out[j] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
   __syncthreads();
@@ -272,9 +272,8 @@ __device__ __attribute__((always_inline)) inline void fused_item(const BatchSys&
 // row, (rows - 1) | block << 8): the tile's partial row, for rows up to
 // kBatchFusedCols wide.  The item carries the tile so that its rows' loads
 // wait only for the item and the system's descriptor.
-__global__ __launch_bounds__(256) void k_batch_fused(const BatchSys* __restrict__ sys,
-                                                     const int4* __restrict__ items, int32_t nitems,
-                                                     const int32_t* __restrict__ active) {
+__global__ __launch_bounds__(256) void k_batch_fused(const BatchSys* sys, const int4* items,
+                                                     int32_t nitems, const int32_t* active) {
   __shared__ float red[4][kBatchFusedCols];
   for (int32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int4 w = items[it];
