@@ -3363,7 +3363,7 @@ apc_status hbm_update(apc_hbm_s* H) {
   const int32_t nt = P->tile_start[P->m];
   const bool f32 = P->prec == APC_F32;
   // Single pass (the plan's tiles): every tile's partial of sum_r (C_r x - d_r) C_r,
-  // their sum (the gradient), then the heavy-ball step.
+  // then their sum (the gradient) and the heavy-ball step in one launch.
   const int cpt32 = fused_cpt(L.ldc, 4), cpt64 = fused_cpt(L.ldc, 8);
   if (P->fused && (f32 ? fused_shape_ok(4, 8, cpt32, 1) : cpt64 > 0)) {
     double* part = P->at<double>(L.fpart);
@@ -3381,8 +3381,8 @@ apc_status hbm_update(apc_hbm_s* H) {
       fused_route(P, &a);
       HIP_TRY(launch_fused_f64(a, cpt64 >= 16 ? 1 : 2, P->stream));
     }
-    HIP_TRY(launch_fused_sum(part, L.ldc, P->ntiles_f, L.ldc, 1.0, H->Y, P->stream));
-    HIP_TRY(launch_hbm_step(H->Y, L.ldc, 1, P->n, H->alpha, H->beta, H->x, H->z, P->stream));
+    HIP_TRY(launch_fused_hbm(part, L.ldc, P->ntiles_f, P->n, H->alpha, H->beta, H->x, H->z,
+                             P->stream));
     return APC_OK;
   }
   if (f32) {

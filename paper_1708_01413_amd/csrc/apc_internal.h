@@ -762,6 +762,9 @@ hipError_t launch_pad_cast(int f32, const double* A, int64_t lda, int64_t N, int
 // Heavy-ball step: g = sum_i Y_i (block order), z <- beta z + g, x <- x - alpha z.
 hipError_t launch_hbm_step(const double* Y, int64_t ldy, int32_t m, int64_t n, double alpha,
                            double beta, double* x, double* z, hipStream_t s);
+// The same over a single pass's ntiles partial rows (stride ldp).
+hipError_t launch_fused_hbm(const double* part, int64_t ldp, int32_t ntiles, int64_t n,
+                            double alpha, double beta, double* x, double* z, hipStream_t s);
 hipError_t launch_fill_u32(unsigned* p, int64_t count, unsigned v, hipStream_t s);
 hipError_t launch_copy_strided(const double* src, int64_t lds, double* dst, int64_t ldd,
                                int64_t rows, int64_t cols, hipStream_t s);

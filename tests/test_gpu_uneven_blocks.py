@@ -126,3 +126,26 @@ def test_rows_split_evenly(m, lo, hi, n, prec, tol):
     print(f"{prec} m={len(off) - 1} N={off[-1]} n={n} {plan.single_pass_shape()}: dev {dev:.2e}",
           flush=True)
     assert dev <= tol
+
+
+@pytest.mark.parametrize("m,n", [(1, 17), (259, 170), (600, 33)])
+def test_heavy_ball_over_many_tiles(m, n):
+    """15 heavy-ball steps over one, just over 256 and over 512 row tiles, FP64, against the
+    oracle's."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    off = _blocks(m, 1, 2, m) if m > 1 else np.array([0, n], dtype=np.int64)
+    rng = np.random.default_rng(m)
+    A = rng.standard_normal((off[-1], n)) / np.sqrt(n)
+    xs = rng.standard_normal((n, 1))
+    B = A @ xs
+    ref = O.dhbm_run(A, B, off, 15, preconditioned=True, alpha=0.9 / m, beta=0.3,
+                     keep_traj=True)["traj"][15, :, 0]
+    plan = apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(B[:, 0]).cuda(), off, "f64",
+                    gamma=1.0, eta=1.0)
+    h = apc.HeavyBall(plan, 1, alpha=0.9 / m, beta=0.3)
+    h.iterate(15)
+    dev = np.linalg.norm(h.x().cpu().numpy() - ref) / np.linalg.norm(xs)
+    print(f"m={m} n={n}: dev {dev:.2e}", flush=True)
+    assert dev <= 1e-10
