@@ -139,7 +139,11 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
  * (x_i += gamma (x_bar - x_i - Q_i w_i)), then the average;
  * k-RHS form: pass A (W = C y), its split sum, pass B (Z = C^T W) and the
  * elementwise step y <- (1-gamma) y + gamma x_bar,
- * x_bar <- eta (x_bar(0) + y - Z/m) + (1 - eta) x_bar.  Returns at once. */
+ * x_bar <- eta (x_bar(0) + y - Z/m) + (1 - eta) x_bar (small systems: the split
+ * sum and the step inside the passes' launches).  The FP32 form's products for
+ * more than 16 right-hand sides run on the bf16 matrix cores, every FP32 value
+ * split exactly into three bf16 parts and six of the nine products summed in
+ * FP32; an infinity there gives NaN.  Returns at once. */
 apc_status apc_iterate(apc_plan p, int32_t T);
 
 /* As apc_iterate, replayed from a captured HIP graph: the first call for a
@@ -246,8 +250,12 @@ apc_status apc_get_setup(apc_plan p, int32_t* qr_passes, double* qr_defect);
  * residual): rows of the streamed operand per workgroup, split-K factor, and
  * the measured time per launch when it was chosen by timing (0 when fixed by
  * APC_TN_TUNE=0 / APC_TN_RT / APC_TN_SPLIT).  Shapes are timed once per
- * problem shape and process.  which = 4: the single-pass k = 1 update, rows
- * per workgroup and rows per register group (in *splits), *tuned_us = 0.
+ * problem shape and process.  A shape of 16 or 32 rows per workgroup is the
+ * kernel whose waves split K and that applies its epilogue itself.  which = 4:
+ * the single-pass k = 1 update, rows per workgroup (the mean where the rows are
+ * split evenly over the workgroups) and rows per register group (in *splits; of
+ * the looping kernel: tiles of 16 rows of up to 16 KiB are held whole),
+ * *tuned_us = 0.
  * which = 5: the single-launch k = 1 update of apc_iterate, the block rows and
  * columns one workgroup holds (in *splits), *tuned_us = 0.
  * Host pointers, any may be NULL.  APC_EUNSUPPORTED for which 0..3 on a k = 1
@@ -339,8 +347,8 @@ apc_status apc_backward_noalloc(apc_plan p, const double* dXbar, int64_t ldd, in
  *   - k = 1, APC_F32, per-block form;
  *   - the k-RHS (y, x_bar) form with FP32 products (k > 1 or APC_REDUCED_FORM,
  *     k <= 128), with or without FP64 anchor updates.
- * Every launch is a persistent grid of a fixed number of workgroups looping
- * over a work list that covers all systems; items of inactive systems are
+ * Every launch but the single-pass update's second (one workgroup per item) is a
+ * persistent grid of a fixed number of workgroups looping over a work list that covers all systems; items of inactive systems are
  * skipped.  Per update:
  *   - k = 1 plans only, single pass (every row at most 1024 wide): one launch
  *     of (system, row tile) items that form each tile's partial row of
@@ -404,7 +412,7 @@ apc_status apc_batch_solve(apc_batch b, double rtol, int32_t max_iters, int32_t 
  * measured time of the pass over the factors when the grid was chosen by
  * timing.  A batch whose plans all update in one pass over their factor (rows
  * up to 1024 wide) does too: *items_a then counts its row tiles, *items_b is
- * 0 and *items_avg counts the 32-column items of the update + average launch.
+ * 0 and *items_avg counts the 64-column items of the update + average launch.
  * With k-RHS plans: the items of an ordinary update's first (pass A),
  * third (pass B) and second (split sums) launches.  Host pointers. */
 apc_status apc_batch_get_launch(apc_batch b, int32_t* grid, int32_t* items_a, int32_t* items_b,
@@ -425,7 +433,8 @@ void apc_batch_destroy(apc_batch b);
  * C_i^T (C_i x - d_i) = Q_i (Q_i^T x - c_i) is the same.  One update is a row
  * pass (w_r = C_r . x - d_r, FP64 accumulation), a block pass
  * (sum over the block's rows of w_r C_r, per block) and an elementwise step that
- * adds the blocks in a fixed order; the factor or the copy of A is streamed in
+ * adds the blocks in a fixed order (where the plan updates in one pass: one
+ * launch for both products, one for the sum of its row tiles and the step); the factor or the copy of A is streamed in
  * the plan's precision (APC_F32: FP32), vectors and arithmetic are FP64.
  * Start (not fixed by the paper): x(0) = the plan's x_bar(0) (Alg. 1
  * initialisation), z(0) = 0, so both methods start where APC starts.  Needs a
