@@ -614,11 +614,15 @@ __global__ __launch_bounds__(kFusedOnceChunks) void k_fused_once(FusedArgs<TQ, T
 constexpr int kCombineCols = 16;
 // Sixteen FP32 entries are half a cache line, and workgroups b and b + 8 run on
 // the same XCD: neighbouring column groups go there, so that one L2 serves
-// both halves (at 16384 x 8192 in FP32 27.5 -> 19.1 MB of traffic, 5.2 -> 4.8 us).
-// Of every 16 workgroups, XCD x takes groups 2x and 2x + 1.
-__device__ inline int64_t combine_group() {
+// both halves (at 16384 x 8192 with 64 blocks 27.5 -> 19.1 MB of traffic, 5.2 ->
+// 4.8 us).  Of every 16 workgroups, XCD x takes groups 2x and 2x + 1.  With more
+// blocks than stay in registers x is read again and outweighs the partial rows,
+// and the plain order is the faster one (11.2 against 13.8 us at 16384 x 6616
+// with 303); FP64 pieces are whole lines.
+template <typename TD>
+__device__ inline int64_t combine_group(int32_t m) {
   const int b = static_cast<int>(blockIdx.x);
-  return (b & ~15) + 2 * (b & 7) + ((b >> 3) & 1);
+  return sizeof(TD) == 4 && m <= 128 ? (b & ~15) + 2 * (b & 7) + ((b >> 3) & 1) : b;
 }
 template <typename TD, int TPB>
 __global__ __launch_bounds__(256) void k_fused_combine(FusedCombineArgs<TD> a) {
@@ -628,7 +632,7 @@ __global__ __launch_bounds__(256) void k_fused_combine(FusedCombineArgs<TD> a) {
   __shared__ double xb[CL];
   const int lane = threadIdx.x % CL;
   const int bl = threadIdx.x / CL;
-  const int64_t j = combine_group() * CL + lane;
+  const int64_t j = combine_group<TD>(a.m) * CL + lane;
   const TD* pp = a.part;
   double* x = a.x;
   double s = 0.0;
@@ -734,7 +738,7 @@ __global__ __launch_bounds__(256) void k_fused_combine_staged(FusedCombineArgs<T
   __shared__ double xb[CL];
   const int lane = threadIdx.x % CL;
   const int bl = threadIdx.x / CL;
-  const int64_t j = combine_group() * CL + lane;
+  const int64_t j = combine_group<TD>(a.m) * CL + lane;
   const bool ok = j < a.n;
   const int64_t jc = ok ? j : a.n - 1;
   double* x = a.x;
