@@ -72,14 +72,18 @@ __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f64x4& c, doubl
 }
 
 // FP32 operands on the bf16 matrix cores.  An FP32 value is the exact sum of
-// three bf16 values: h = its upper half (truncated), m = the remainder rounded
-// to bf16, l = what is left (at most 8 significant bits, so exact).  A product
-// is then h h' + h m' + m h' + m m' + h l' + l h' in FP32 accumulation; the
-// three left out (m l', l m', l l') are together below 2^-21 of it with random
-// signs, small against the rounding of the FP32 sums they would be added to.
-// Infinities and NaN give NaN.  The FP32 matrix instructions run at 1/16 of
-// the bf16 rate, so six products take 3/8 of their time; errors against 64
-// bits measured 0.3-0.85 of theirs (fewer roundings per sum).  With 16 right-
+// three bf16 values: h and m are the value and the remainder rounded to bf16, l
+// is what is left (at most 7 significant bits, so exact).  A product is then
+// h h' + h m' + m h' + m m' + h l' + l h' in FP32 accumulation; the three left
+// out (m l', l m', l l') are together below 2^-24 of it, which is what rounding
+// a product to FP32 may cost: over 4 million random pairs 2^-24.2 at most and
+// 2^-27.5 rms.  (h truncated instead leaves an m twice as long, of the value's
+// sign: 2^-22.2 and 2^-25.5, and rows of few entries then err by up to 1.6 FP32
+// roundings in one direction.)
+// Infinities, NaN and what rounds to a bf16 infinity (from 2^128 - 2^119 on)
+// give NaN.  The FP32 matrix instructions run at 1/16 of the bf16 rate, so six
+// products take 3/8 of their time; the errors of long sums against 64 bits
+// measured 0.3-0.85 of theirs (fewer roundings per sum).  With 16 right-
 // hand sides a pass is bound by reading M, not by its products, and the FP32
 // instructions stay (T = float): splitting cost 4-15 % there (5120^2: 18.1
 // against 17.3 us).
@@ -89,14 +93,13 @@ struct Split3 {
 typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 __device__ inline void split_pair(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
-  const unsigned u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
-  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the two upper halves
-  const float r0 = x0 - __uint_as_float(u0 & 0xffff0000u);
-  const float r1 = x1 - __uint_as_float(u1 & 0xffff0000u);
+  h = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2v{x0, x1}, bf16x2v));
+  const float r0 = x0 - __uint_as_float(h << 16);
+  const float r1 = x1 - __uint_as_float(h & 0xffff0000u);
   m = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2v{r0, r1}, bf16x2v));
   const float s0 = r0 - __uint_as_float(m << 16);
   const float s1 = r1 - __uint_as_float(m & 0xffff0000u);
-  l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
+  l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);  // upper halves
 }
 __device__ inline Split3 split8(const u32x4& a, const u32x4& b) {
   const f32x4 av = __builtin_bit_cast(f32x4, a), bv = __builtin_bit_cast(f32x4, b);

@@ -80,3 +80,49 @@ def test_mixed_batch_with_two_column_groups(k):
         print(f"k={k} n={S.n}: dev {dev:.2e}", flush=True)
         assert dev <= 1e-5
     batch.close()
+
+
+def _worst_split_angles(count):
+    """Angles whose cosine and sine, as FP32, have large middle and low thirds of one sign."""
+    rng = np.random.default_rng(1)
+
+    def worst(v):
+        bits = int(np.float32(v).view(np.uint32))
+        return 200 <= (bits >> 8 & 255) <= 254 and 96 <= (bits & 255) <= 126
+
+    out = []
+    while len(out) < count:
+        t = rng.uniform(0.3, 1.27)
+        if worst(math.cos(t)) and worst(math.sin(t)):
+            out.append(t)
+    return out
+
+
+def test_products_of_sparse_rows():
+    """Rows of two entries (2 x 2 rotations, a block per row), gamma = eta = 1: x_bar(1) =
+    2 x0 - X x0 with x0 = x / m, so X x0 = 2 x0 - x_bar(1) is two FP32 contractions of two
+    products each.  Their roundings have either sign, so the mean of the n k = 1536
+    relative errors against 64 bits of the FP32 inputs is below 3 u / sqrt(n k) = 0.08 u
+    (a third of it for a uniform rounding error); 0.5 u is six of that.  Entries whose
+    middle and low thirds are large and of one sign make the parts that a product leaves
+    out add up instead: a split by truncation has a mean of -1.6 u."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    n, k = 64, 24
+    A = np.zeros((n, n))
+    for i, t in enumerate(_worst_split_angles(4) * 8):
+        c, s = math.cos(t), math.sin(t)
+        A[2 * i:2 * i + 2, 2 * i:2 * i + 2] = [[c, s], [-s, c]]
+    rng = np.random.default_rng(2)
+    x = ((rng.integers(128, 256, (n, k)) << 16) | (rng.integers(200, 255, (n, k)) << 8) |
+         rng.integers(96, 127, (n, k))) / 2.0 ** 23
+    plan = apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(A @ x).cuda(),
+                    np.arange(n + 1), "f32", gamma=1.0, eta=1.0, anchor_every=0)
+    plan.iterate(1)
+    z = n * (2 * x / n - plan.xbar().cpu().numpy())
+    C = A.astype(np.float32).astype(np.float64)
+    ref = C.T @ (C @ x) / n
+    rel = (z - ref) / ref / U
+    print(f"relative error in u: mean {rel.mean():.3f} rms {np.sqrt((rel ** 2).mean()):.3f} "
+          f"max {abs(rel).max():.2f}", flush=True)
+    assert abs(rel.mean()) <= 0.5
