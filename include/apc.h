@@ -142,8 +142,12 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
  * x_bar <- eta (x_bar(0) + y - Z/m) + (1 - eta) x_bar (small systems: the split
  * sum and the step inside the passes' launches).  The FP32 form's products for
  * more than 16 right-hand sides run on the bf16 matrix cores, every FP32 value
- * split exactly into three bf16 parts and six of the nine products summed in
- * FP32; an infinity there gives NaN.  Returns at once. */
+ * split into three bf16 parts that add up to it and six of the nine products
+ * summed in FP32 (what is left out is below 2^-24 of a product).  The parts need
+ * values above 2^-110: a right-hand side (and a cotangent of apc_backward) whose
+ * largest transformed entry is outside 2^-64 .. 2^65 is iterated times a power
+ * of two, which changes no rounding.  An infinity there gives NaN.  Returns at
+ * once. */
 apc_status apc_iterate(apc_plan p, int32_t T);
 
 /* As apc_iterate, replayed from a captured HIP graph: the first call for a

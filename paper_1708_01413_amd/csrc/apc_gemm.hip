@@ -59,8 +59,8 @@ namespace apc {
 namespace {
 
 inline bool quad_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
-inline bool update_args_ok(const TnUpdateArgs& a) {
-  return a.n % 4 == 0 && a.ldx % 4 == 0 && a.ldq % 4 == 0 && quad_ok(a.x0) && quad_ok(a.y) &&
+inline bool update_args_ok(int type, const TnUpdateArgs& a) {
+  return (type != kTnF32x3 || a.qs) && a.n % 4 == 0 && a.ldx % 4 == 0 && a.ldq % 4 == 0 && quad_ok(a.x0) && quad_ok(a.y) &&
          quad_ok(a.xb) && quad_ok(a.yq) && (!a.yref || (quad_ok(a.yref) && quad_ok(a.uref)));
 }
 
@@ -209,18 +209,20 @@ __global__ __launch_bounds__(64 * kKsWaves) void k_tn_ks(TnArgs a, TnKsEpilogue 
                 ej = static_cast<int64_t>(rt) * 16 + 4 * eg;
   UpdateState us;
   AdjointState as;
+  double zs = 1.0;
   if constexpr (EPI == kKsOperand) asm volatile("" ::"s"(ep.out), "s"(ep.ldo));
   if constexpr (EPI == kKsUpdate) {
     // The arguments used after the products are read here too: read there,
     // each would wait for a cold line of the argument buffer.
     asm volatile("" ::"s"(ep.upd.yq), "s"(ep.upd.ldq), "s"(ep.upd.gamma), "s"(ep.upd.eta),
                  "s"(ep.upd.inv_m), "s"(ep.upd.y));
-    update_load<true>(ep.upd, ec, ej, us);  // (threads past the first repeat their entries)
+    if constexpr (Op::kSplit) zs = ep.upd.zs[ec];
+    update_load<TQ, true>(ep.upd, ec, ej, us);  // (threads past the first repeat their entries)
   }
   if constexpr (EPI == kKsAdjoint) {
     asm volatile("" ::"s"(ep.adj.bq), "s"(ep.adj.ldq), "s"(ep.adj.gamma), "s"(ep.adj.eta),
                  "s"(ep.adj.inv_m), "s"(ep.adj.red));
-    adjoint_load(ep.adj, ec, ej, as);
+    adjoint_load<TQ>(ep.adj, ec, ej, as);
   }
 
   u32x4 mr[D][4], vr[D][NCT][VP];
@@ -311,7 +313,8 @@ __global__ __launch_bounds__(64 * kKsWaves) void k_tn_ks(TnArgs a, TnKsEpilogue 
       store_operand4(static_cast<TQ*>(ep.out), ep.ldo, ec, ej, o);
     }
   } else if constexpr (EPI == kKsUpdate) {
-    if (eth) update_quad<TQ>(ep.upd, ec, ej, us, zd);
+    const double zu[4] = {zd[0] * zs, zd[1] * zs, zd[2] * zs, zd[3] * zs};
+    if (eth) update_quad<TQ>(ep.upd, ec, ej, us, zu);
   } else {
     // dL/dgamma and dL/deta: wave sums, then the waves' in order.
     double sg = 0.0, se = 0.0;
@@ -384,16 +387,17 @@ __global__ __launch_bounds__(256) void k_tn_anchor_vec(const double* y, const do
 // restored, rows of n entries (stride n).
 template <typename TQ>
 __global__ __launch_bounds__(256) void k_tn_prep(const double* y, const double* xb, int64_t count,
-                                                 int64_t n, double gamma, TQ* yq) {
+                                                 int64_t n, double gamma, const double* qs, TQ* yq) {
   for (int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x); e < count;
        e += 4 * static_cast<int64_t>(gridDim.x) * blockDim.x) {
     double yv[4], xv[4];
     load4(y + e, yv);
     load4(xb + e, xv);
+    const int64_t c = e / n;
+    const double f = TnOperand<TQ>::kSplit ? qs[c] : 1.0;
     TQ q[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = cvt<TQ>((1.0 - gamma) * yv[u] + gamma * xv[u]);
-    const int64_t c = e / n;
+    for (int u = 0; u < 4; ++u) q[u] = cvt_scaled<TQ>((1.0 - gamma) * yv[u] + gamma * xv[u], f);
     store_operand4(yq, n, c, e - c * n, q);
   }
 }
@@ -409,6 +413,44 @@ __global__ __launch_bounds__(256) void k_tn_operand(const double* src, int64_t l
     TQ q[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) q[u] = j + u < cols ? cvt<TQ>(src[c * lds + j + u]) : cvt<TQ>(0.0);
+    store_operand4(dst, ldd, c, j, q);
+  }
+}
+
+// The same with the rows' scales (see launch_tn_operand), a workgroup per row:
+// its largest magnitude first, so that no launch of its own is needed for it.
+template <typename TQ>
+__global__ __launch_bounds__(1024) void k_tn_operand_scale(const double* src, int64_t lds, int64_t cols,
+                                                           TQ* dst, int64_t ldd, double* scale) {
+  const int64_t c = blockIdx.x;
+  const double* row = src + c * lds;
+  double big = 0.0;
+  for (int64_t j = threadIdx.x; j < cols; j += 1024) big = fmax(big, fabs(row[j]));  // (NaN: ignored)
+  __shared__ double red[16];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = big;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) big = fmax(big, red[w]);
+  // Zero and infinite rows keep 1.  (Exponents past 1000 would leave no
+  // normal reciprocal.)
+  double f = 1.0, inv = 1.0;
+  if (big > 0.0 && big < INFINITY) {
+    const int e = max(-1000, min(1000, ilogb(big)));
+    if (e < -64 || e > 64) {
+      f = ldexp(1.0, -e);
+      inv = ldexp(1.0, e);
+    }
+  }
+  if (threadIdx.x == 0) {
+    scale[c] = f;
+    scale[gridDim.x + c] = inv;
+  }
+  for (int64_t j = 4 * threadIdx.x; j < ldd; j += 4096) {
+    TQ q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = j + u < cols ? cvt_scaled<TQ>(row[j + u], f) : cvt<TQ>(0.0);
     store_operand4(dst, ldd, c, j, q);
   }
 }
@@ -434,7 +476,7 @@ __global__ __launch_bounds__(256) void k_tn_adjoint(TnAdjointArgs a) {
       for (int q = 0; q < 4; ++q) zs[q] += t[q];
     }
     AdjointState s;
-    adjoint_load(a, c, j, s);
+    adjoint_load<TQ>(a, c, j, s);
     const double z[4] = {static_cast<double>(zs[0]), static_cast<double>(zs[1]),
                          static_cast<double>(zs[2]), static_cast<double>(zs[3])};
     adjoint_quad<TQ>(a, c, j, s, z, sg, se);
@@ -715,7 +757,8 @@ hipError_t launch_tn_ks_operand(int type, int nct, const TnArgs& a, void* out, i
 
 hipError_t launch_tn_ks_update(int type, int nct, const TnArgs& a, int type_q, const TnUpdateArgs& u,
                                hipStream_t s) {
-  if (!tn_ks_ok(type, nct, a) || !update_args_ok(u) || u.n != a.rows || u.kp != a.kp)
+  if (!tn_ks_ok(type, nct, a) || !update_args_ok(type_q, u) || u.n != a.rows || u.kp != a.kp ||
+      (type == kTnF32x3 && !u.zs))
     return hipErrorInvalidValue;
   TnKsEpilogue ep{};
   ep.upd = u;
@@ -750,6 +793,7 @@ hipError_t launch_tn_ks_update(int type, int nct, const TnArgs& a, int type_q, c
 hipError_t launch_tn_ks_adjoint(int type, int nct, const TnArgs& a, const TnAdjointArgs& d,
                                 hipStream_t s) {
   if (!tn_ks_ok(type, nct, a) || d.n != a.rows || d.kp != a.kp || d.ldx % 4 ||
+      (type == kTnF32x3 && (!d.qs || !d.zs)) ||
       (a.rows / 16) * (a.kp / (16 * nct)) > kTnAdjointBlocks)
     return hipErrorInvalidValue;
   TnKsEpilogue ep{};
@@ -783,7 +827,7 @@ hipError_t launch_tn_sum_cast(int type, const void* part, int32_t nsplit, int32_
 }
 
 hipError_t launch_tn_update(int type, int part_f64, const TnUpdateArgs& a, hipStream_t s) {
-  if (!update_args_ok(a) || a.ldp % 4 || !quad_ok(a.part)) return hipErrorInvalidValue;
+  if (!update_args_ok(type, a) || a.ldp % 4 || !quad_ok(a.part)) return hipErrorInvalidValue;
   const unsigned g = grid_stride_blocks(static_cast<int64_t>(a.kp) * a.n / 4);
 #define APC_UPDATE(P, TQ) APC_LAUNCH((k_tn_update4<P, TQ>), dim3(g), dim3(256), 0, s, a)
   if (part_f64) {
@@ -813,36 +857,47 @@ hipError_t launch_tn_anchor_vec(const double* y, const double* xb, int64_t count
 }
 
 hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, int64_t n,
-                          double gamma, void* yq, hipStream_t s) {
-  if (n % tn_step_elems(type) || count % n || !quad_ok(y) || !quad_ok(xb) || !quad_ok(yq))
+                          double gamma, const double* qs, void* yq, hipStream_t s) {
+  if (n % tn_step_elems(type) || (type == kTnF32x3 && !qs) || count % n || !quad_ok(y) || !quad_ok(xb) || !quad_ok(yq))
     return hipErrorInvalidValue;
   const unsigned g = grid_stride_blocks(count / 4);
   switch (type) {
-    case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<double*>(yq)); break;
-    case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<float*>(yq)); break;
-    case kTnF32x3: k_tn_prep<F32x3><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<F32x3*>(yq)); break;
-    case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, n, gamma, static_cast<__bf16*>(yq)); break;
+    case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<double*>(yq)); break;
+    case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<float*>(yq)); break;
+    case kTnF32x3: k_tn_prep<F32x3><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<F32x3*>(yq)); break;
+    case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<__bf16*>(yq)); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
+template <typename TQ>
+static hipError_t tn_operand(const double* src, int64_t lds, int64_t rows, int64_t cols, TQ* dst,
+                             int64_t ldd, double* scale, hipStream_t s) {
+  if (scale)
+    k_tn_operand_scale<TQ><<<static_cast<unsigned>(rows), 1024, 0, s>>>(src, lds, cols, dst, ldd, scale);
+  else if constexpr (TnOperand<TQ>::kSplit)
+    return hipErrorInvalidValue;
+  else
+    k_tn_operand<TQ><<<grid_stride_blocks(rows * ldd / 4), 256, 0, s>>>(src, lds, rows, cols, dst, ldd);
+  return hipGetLastError();
+}
+
 hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t rows, int64_t cols,
-                             void* dst, int64_t ldd, hipStream_t s) {
-  if (ldd % tn_step_elems(type) || cols > ldd || !quad_ok(dst)) return hipErrorInvalidValue;
-  const unsigned g = grid_stride_blocks(rows * ldd / 4);
+                             void* dst, int64_t ldd, double* scale, hipStream_t s) {
+  if (ldd % tn_step_elems(type) || cols > ldd || rows < 1 || !quad_ok(dst)) return hipErrorInvalidValue;
   switch (type) {
-    case kTnF64: k_tn_operand<double><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<double*>(dst), ldd); break;
-    case kTnF32: k_tn_operand<float><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<float*>(dst), ldd); break;
-    case kTnF32x3: k_tn_operand<F32x3><<<g, 256, 0, s>>>(src, lds, rows, cols, static_cast<F32x3*>(dst), ldd); break;
+    case kTnF64: return tn_operand(src, lds, rows, cols, static_cast<double*>(dst), ldd, scale, s);
+    case kTnF32: return tn_operand(src, lds, rows, cols, static_cast<float*>(dst), ldd, scale, s);
+    case kTnF32x3: return tn_operand(src, lds, rows, cols, static_cast<F32x3*>(dst), ldd, scale, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 int tn_adjoint_blocks() { return kTnAdjointBlocks; }
 
 hipError_t launch_tn_adjoint(int type, const TnAdjointArgs& a, hipStream_t s) {
+  if (type == kTnF32x3 && (!a.qs || !a.zs)) return hipErrorInvalidValue;
   switch (type) {
     case kTnF64: k_tn_adjoint<double, double><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;
     case kTnF32: k_tn_adjoint<float, float><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;

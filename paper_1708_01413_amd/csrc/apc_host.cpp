@@ -70,7 +70,7 @@ struct Layout {
   size_t tiles_f = 0, fpart = 0, v32 = 0;
   // k-RHS path: rows/K padding of its operands (N and n rounded up to kTnPad)
   int64_t Np = 0, np = 0;
-  size_t Cq, CqT, C64T, C32T, Apad, yq, Wq, tnpart, x0, ys, c64p, Xs, Rb, cw, Linv2, ssq;
+  size_t Cq, CqT, C64T, C32T, Apad, yq, Wq, tnpart, x0, ys, c64p, vs, Xs, Rb, cw, Linv2, ssq;
   size_t C64p, yref, uref, W64;  // FP64 anchor of the FP32 / bf16 k-RHS iteration
   size_t C64a, C64b, C32, x, xbar, dv, w, ca, cb, Y, vtmp, V, h, alpha, beta, G, Linv, flags, scal, partial, tiles_a, tiles_g, tiles_t, doff, goff, total;
   size_t toff, tpart;  // triangular product's row-tile sums (setup)
@@ -293,6 +293,9 @@ Layout make_layout(int64_t N, int64_t n, const int64_t* off, int32_t m, int32_t 
   L.uref = take(anc ? kp * L.np * d : 0);
   L.W64 = take(anc ? kp * L.Np * d : 0);
   if (!own_wq) L.Wq = L.W64;
+  // Row scales of the split operands (launch_tn_operand): the iteration's, the
+  // reverse sweep's.
+  L.vs = take(gemm ? 4 * kp * d : 0);
   L.Rb = take(gemm ? kp * N * d : 0);
   L.cw = take(bf ? kp * N * d : 0);
   L.ssq = take(sumsq_parts() * d);
@@ -828,10 +831,13 @@ TnUpdateArgs update_args(const apc_plan_s* P, const TnChoice& ch, int mode) {
   // The start zeroes y_ref and u_ref whenever they exist (with both zero an
   // update is the same as an unanchored one).
   const bool anc = P->prec != APC_F64 && (P->anchor_every > 0 || mode == 1);
+  const int z_type = mode == 0 ? P->tq : mode == 1 ? x0_type(P) : kTnF64;
   return TnUpdateArgs{P->ws + L.tnpart, ch.nsplit, P->kp, L.np, L.np, P->at<double>(L.x0),
                       P->at<double>(L.ys), P->xbar(), L.np, P->ws + L.yq, L.np, P->gamma, P->eta,
                       1.0 / P->m, mode, anc ? P->at<double>(L.yref) : nullptr,
-                      anc ? P->at<double>(L.uref) : nullptr};
+                      anc ? P->at<double>(L.uref) : nullptr,
+                      P->tq == kTnF32x3 ? P->at<double>(L.vs) : nullptr,
+                      z_type == kTnF32x3 ? P->at<double>(L.vs) + P->kp : nullptr};
 }
 
 // One update of the (y, x_bar) form.  In the FP32 and bf16 iterations every
@@ -928,7 +934,8 @@ apc_status update_gemm(apc_plan_s* P, hipEvent_t* ev, int* kinds, int* nev) {
 apc_status start_gemm(apc_plan_s* P, const double* c_rhs) {
   const Layout& L = P->L;
   const int t = x0_type(P);
-  HIP_TRY(launch_tn_operand(t, c_rhs, P->N, P->kp, P->N, P->ws + L.c64p, L.Np, P->stream));
+  double* scale = t == kTnF32x3 || P->tq == kTnF32x3 ? P->at<double>(L.vs) : nullptr;
+  HIP_TRY(launch_tn_operand(t, c_rhs, P->N, P->kp, P->N, P->ws + L.c64p, L.Np, scale, P->stream));
   ST_TRY(pass_b_update(P, t, P->tnX0, x0_args(P), 1));
   P->since_start = 0;
   return APC_OK;
@@ -2489,8 +2496,8 @@ apc_status restore_state(apc_plan_s* P, const double* y, const double* xb) {
   const Layout& L = P->L;
   ST_TRY(copy_state(P, P->at<double>(L.ys), P->xbar(), y, xb));
   HIP_TRY(launch_tn_prep(P->tq, P->at<double>(L.ys), P->xbar(),
-                         static_cast<int64_t>(P->kp) * L.np, L.np, P->gamma, P->ws + L.yq,
-                         P->stream));
+                         static_cast<int64_t>(P->kp) * L.np, L.np, P->gamma, P->at<double>(L.vs),
+                         P->ws + L.yq, P->stream));
   P->since_start = 0;
   return APC_OK;
 }
@@ -2554,7 +2561,9 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(g0), 2 * cnt, 0u, st));
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(red), 4 * tn_adjoint_blocks(), 0u, st));
   HIP_TRY(launch_tn_pack(dXbar, ldd, P->n, P->k, 1, bh, L.np, P->kp, st));
-  HIP_TRY(launch_tn_prep(P->tq, a, bh, cnt, L.np, 1.0, bq, st));  // bq = TQ(bh)
+  const bool split = P->tq == kTnF32x3;
+  double* bs = P->at<double>(L.vs) + 2 * P->kp;
+  HIP_TRY(launch_tn_operand(P->tq, bh, L.np, P->kp, L.np, bq, L.np, split ? bs : nullptr, st));
 
   void* part = P->ws + L.tnpart;
   for (int64_t sgi = nck - 1; sgi >= 0; --sgi) {
@@ -2574,7 +2583,8 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
       const double* s_t = seg(t - t0);
       const double* s_n = seg(t - t0 + 1);
       TnAdjointArgs ad{part, P->tnB.nsplit, P->kp, L.np, L.np, a, bh, g0, s_t, s_t + cnt,
-                       s_n + cnt, L.np, bq, L.np, P->gamma, P->eta, 1.0 / P->m, red};
+                       s_n + cnt, L.np, bq, L.np, P->gamma, P->eta, 1.0 / P->m, red,
+                       split ? bs : nullptr, split ? bs + P->kp : nullptr};
       // One launch when the shape holds whole sums and its workgroups fit the
       // sums' slots.
       const TnChoice& cb = P->tnB;

@@ -80,8 +80,10 @@ __device__ inline void mma_piece(const u32x4& a, const u32x4& b, f64x4& c, doubl
 // 2^-27.5 rms.  (h truncated instead leaves an m twice as long, of the value's
 // sign: 2^-22.2 and 2^-25.5, and rows of few entries then err by up to 1.6 FP32
 // roundings in one direction.)
-// Infinities, NaN and what rounds to a bf16 infinity (from 2^128 - 2^119 on)
-// give NaN.  The FP32 matrix instructions run at 1/16 of the bf16 rate, so six
+// Exact from 2^-110 on, below which l falls under bf16's range (2^-112: off by
+// 4e-7, 2^-120 by 6e-5): the rows of an operand far from 1 are stored scaled
+// (launch_tn_operand).  Infinities, NaN and what rounds to a bf16 infinity
+// (from 2^128 - 2^119 on) give NaN.  The FP32 matrix instructions run at 1/16 of the bf16 rate, so six
 // products take 3/8 of their time; the errors of long sums against 64 bits
 // measured 0.3-0.85 of theirs (fewer roundings per sum).  With 16 right-
 // hand sides a pass is bound by reading M, not by its products, and the FP32
@@ -474,6 +476,13 @@ __device__ inline F32x3 cvt<F32x3>(double v) { return F32x3(static_cast<float>(v
 template <>
 __device__ inline __bf16 cvt<__bf16>(double v) { return static_cast<__bf16>(static_cast<float>(v)); }
 
+// The same, times the row's scale where the operand has one.
+template <typename T>
+__device__ inline T cvt_scaled(double v, double qs) {
+  if constexpr (TnOperand<T>::kSplit) return cvt<T>(v * qs);
+  else return cvt<T>(v);
+}
+
 template <typename P>
 __device__ inline double split_sum(const P* part, int32_t nsplit, int64_t split_stride, int64_t idx) {
   P s = part[idx];
@@ -562,13 +571,15 @@ __device__ inline void sum_cast4(const P* part, int32_t nsplit, int64_t ldp, int
 // contraction can load it before its products.
 struct UpdateState {
   double xb[4], x0[4], y[4], yr[4], ur[4];  // y: y_ref in an anchor update
+  double qs;
 };
 // kAll: load every field without a branch (absent anchors read y instead, and
 // are not used), so that the loads can stay in flight.
-template <bool kAll>
+template <typename TQ, bool kAll>
 __device__ inline void update_load(const TnUpdateArgs& a, int64_t c, int64_t j, UpdateState& s) {
   const int64_t i = c * a.ldx + j;
   const double* y = a.mode == 2 ? a.yref : a.y;
+  if constexpr (TnOperand<TQ>::kSplit) s.qs = a.qs[c];
   load4(a.xb + i, s.xb);
   load4(a.x0 + i, s.x0);
   load4(y + i, s.y);
@@ -589,7 +600,7 @@ __device__ inline void update_quad(const TnUpdateArgs& a, int64_t c, int64_t j, 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       x0[q] = z[q] * a.inv_m;
-      qv[q] = cvt<TQ>(g * x0[q]);
+      qv[q] = cvt_scaled<TQ>(g * x0[q], s.qs);
     }
     store4(a.x0 + i, x0);
     store4(a.xb + i, x0);
@@ -617,7 +628,7 @@ __device__ inline void update_quad(const TnUpdateArgs& a, int64_t c, int64_t j, 
     const double xn = eta * (s.x0[q] + y1 - u) + ome * s.xb[q];
     yo[q] = y1;
     xo[q] = xn;
-    qv[q] = cvt<TQ>(omg * y1 + g * xn - ref);
+    qv[q] = cvt_scaled<TQ>(omg * y1 + g * xn - ref, s.qs);
   }
   if (a.mode == 2) store4(a.uref + i, uo);
   store4(a.y + i, yo);
@@ -640,9 +651,10 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
     for (int q = 0; q < 4; ++q) zs[q] += t[q];
   }
   UpdateState s;
-  update_load<false>(a, c, j, s);
-  const double z[4] = {static_cast<double>(zs[0]), static_cast<double>(zs[1]),
-                       static_cast<double>(zs[2]), static_cast<double>(zs[3])};
+  update_load<TQ, false>(a, c, j, s);
+  const double f = sizeof(P) == 4 && a.zs ? a.zs[c] : 1.0;
+  const double z[4] = {static_cast<double>(zs[0]) * f, static_cast<double>(zs[1]) * f,
+                       static_cast<double>(zs[2]) * f, static_cast<double>(zs[3]) * f};
   update_quad<TQ>(a, c, j, s, z);
 }
 
@@ -651,9 +663,15 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
 // of the dL/dgamma and dL/deta sums.
 struct AdjointState {
   double a[4], bh[4], g0[4], y[4], xb[4], xn[4];
+  double qs, zs;
 };
+template <typename TQ>
 __device__ inline void adjoint_load(const TnAdjointArgs& a, int64_t c, int64_t j, AdjointState& s) {
   const int64_t i = c * a.ldx + j;
+  if constexpr (TnOperand<TQ>::kSplit) {
+    s.qs = a.qs[c];
+    s.zs = a.zs[c];
+  }
   load4(a.a + i, s.a);
   load4(a.bh + i, s.bh);
   load4(a.g0 + i, s.g0);
@@ -668,7 +686,8 @@ __device__ inline void adjoint_quad(const TnAdjointArgs& a, int64_t c, int64_t j
   TQ qv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const double xbh = z[q] * a.inv_m;  // X b
+    const double zq = TnOperand<TQ>::kSplit ? z[q] * s.zs : z[q];
+    const double xbh = zq * a.inv_m;  // X b
     const double bh = s.bh[q];
     const double at = s.a[q] + a.eta * (bh - xbh);
     sg += at * (s.xb[q] - s.y[q]);
@@ -676,7 +695,7 @@ __device__ inline void adjoint_quad(const TnAdjointArgs& a, int64_t c, int64_t j
     s.g0[q] += a.eta * bh;
     s.a[q] = (1.0 - a.gamma) * at;
     s.bh[q] = (1.0 - a.eta) * bh + a.gamma * at;
-    qv[q] = cvt<TQ>(s.bh[q]);
+    qv[q] = cvt_scaled<TQ>(s.bh[q], s.qs);
   }
   store4(a.g0 + i, s.g0);
   store4(a.a + i, s.a);

@@ -126,3 +126,64 @@ def test_products_of_sparse_rows():
     print(f"relative error in u: mean {rel.mean():.3f} rms {np.sqrt((rel ** 2).mean()):.3f} "
           f"max {abs(rel).max():.2f}", flush=True)
     assert abs(rel.mean()) <= 0.5
+
+
+@pytest.mark.parametrize("ks", ["0", "1", "2"])
+@pytest.mark.parametrize("exps", [(-36, -36), (-45, -45), (38, 38), (60, 60), (-60, 60)])
+def test_one_fp32_update_far_from_one(exps, ks, monkeypatch):
+    """Right-hand sides of 1e-60 to 1e60 (the last: every column of its own, one of them
+    zero), each column to the bound of test_one_fp32_update.  A power of two changes no
+    rounding, so the bound does not depend on the scale; the third parts of unscaled
+    entries fall out of bf16's range below 1e-33."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    k = 24
+    S = synth.gaussian_system(200, 200, 5, k=k, seed=8, scale=1 / math.sqrt(200), shift=2.0)
+    S.B *= 10.0 ** np.linspace(*exps, k)
+    if exps[0] != exps[1]:
+        S.B[:, 5] = 0.0
+    monkeypatch.setenv("APC_TN_KS", ks)
+    g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+    x0, ref = _one_update(S, g, e)
+    plan = apc.Plan(torch.from_numpy(S.A).cuda(), torch.from_numpy(S.B).cuda(), S.off, "f32",
+                    gamma=g, eta=e, anchor_every=0)
+    plan.iterate(1)
+    got = plan.xbar().cpu().numpy()
+    Xy = x0 + g * x0 - (ref - (1 - e) * x0) / e
+    for c in range(k):
+        norm = np.linalg.norm(ref[:, c])
+        tol = 2 * U * (4 + math.sqrt(256)) * e * np.linalg.norm(Xy[:, c])
+        dev = np.linalg.norm(got[:, c] - ref[:, c])
+        assert dev <= tol, f"column {c}: dev {dev:.2e} tol {tol:.2e} of {norm:.2e}"
+    # The next right-hand sides get scales of their own.
+    plan.restart(torch.from_numpy(S.B / 10.0 ** np.linspace(*exps, k)).cuda())
+    plan.iterate(1)
+    back = plan.xbar().cpu().numpy() * 10.0 ** np.linspace(*exps, k)
+    assert np.all(np.linalg.norm(back - ref, axis=0) <=
+                  2 * U * (4 + math.sqrt(256)) * e * np.linalg.norm(Xy, axis=0))
+
+
+@pytest.mark.parametrize("ks", ["0", "1", "2"])
+@pytest.mark.parametrize("k", [12, 24])
+def test_fp32_adjoint(k, ks, monkeypatch):
+    """The FP32 reverse step, by itself and inside the contraction's launch, 16 and more
+    right-hand sides, dL/dB, dL/dgamma and dL/deta to 1e-5 of the oracle's; with more than 16
+    also for right-hand sides of 1e36 and cotangents of 1e-36."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    S = synth.gaussian_system(300, 200, 5, k=k, seed=4, scale=1 / math.sqrt(200), shift=2.0)
+    g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+    dx = np.random.default_rng(1).standard_normal((S.n, k))
+    rB, rg, re = O.apc_adjoint(S.A, S.B, S.off, 9, g, e, dx)
+    monkeypatch.setenv("APC_TN_KS", ks)
+    for f in (1.0, 1e36) if k > 16 else (1.0,):
+        plan = apc.Plan(torch.from_numpy(S.A).cuda(), torch.from_numpy(S.B * f).cuda(), S.off,
+                        "f32", gamma=g, eta=e)
+        if ks == "1":
+            assert plan.launch_shapes()["pass_b"]["rows_per_wg"] == 16
+        dB, dg, de = plan.backward(torch.from_numpy(dx / f).cuda(), 9, 4)
+        dev = np.linalg.norm(dB.cpu().numpy() * f - rB) / np.linalg.norm(rB)
+        print(f"k={k} ks={ks} scale={f}: dB {dev:.2e} dgamma {abs(dg - rg) / abs(rg):.2e} "
+              f"deta {abs(de - re) / abs(re):.2e}", flush=True)
+        assert dev <= 1e-5
+        assert abs(dg - rg) <= 1e-5 * abs(rg) and abs(de - re) <= 1e-5 * abs(re)
