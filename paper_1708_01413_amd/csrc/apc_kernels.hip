@@ -585,10 +585,20 @@ __global__ __launch_bounds__(kFusedOnceChunks) void k_fused_once(FusedArgs<TQ, T
   const TA mine = row_sum16(s, lane);
   if ((lane & 3) == 0) red[wv][lane >> 2] = mine;
   __syncthreads();
-  // Lane r (and r + 16, ...) sums row r over the waves, in wave order.
-  TA w = TA(0);
-  for (int v = 0; v < nw; ++v) w += red[v][lr];
-  w -= sub;
+  // Row lr over the waves, pairwise (one after another, sixteen waves' sums took
+  // up to 15 roundings of the largest): lane group g adds waves g, g + 4, g + 8
+  // and g + 12, then the four groups add theirs.
+  static_assert(kFusedOnceChunks == 1024 && R == 16, "four waves per group of 16 lanes");
+  TA part4[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int v = (lane >> 4) + 4 * u;
+    part4[u] = red[v][lr];
+    if (v >= nw) part4[u] = TA(0);
+  }
+  TA w = (part4[0] + part4[1]) + (part4[2] + part4[3]);
+  w = swap_add16(w, w);
+  w = swap_add32(w, w) - sub;
   TA acc[W];
 #pragma unroll
   for (int e = 0; e < W; ++e) acc[e] = TA(0);

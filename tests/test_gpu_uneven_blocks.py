@@ -149,3 +149,35 @@ def test_heavy_ball_over_many_tiles(m, n):
     dev = np.linalg.norm(h.x().cpu().numpy() - ref) / np.linalg.norm(xs)
     print(f"m={m} n={n}: dev {dev:.2e}", flush=True)
     assert dev <= 1e-10
+
+
+@pytest.mark.parametrize("n", [4096, 3300])
+def test_wave_sums_of_whole_tiles(n):
+    """One row product over 16 and 13 waves' columns, one entry per wave: a large product
+    and then ones just below half a unit of its last place.  Added pairwise the product of
+    the row is off by at most a rounding per product, four per sum and one of what is read
+    back (6 u); added one after another every small one is lost (0.99 u each)."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    u = 2.0 ** -24
+    at = np.arange(0, n, 256)
+    a = np.zeros(n)
+    a[at] = 1 / np.sqrt(len(at))
+    # Block 0 is this row, with b = 0; the others are unit rows, so x_bar(0) = x / m.
+    off = np.concatenate([[0], np.minimum(1 + np.arange(0, n, 64), n), [n + 1]]).astype(np.int64)
+    m = len(off) - 1
+    x = np.zeros(n)
+    x[at] = m
+    x[at[1:]] *= 0.99 * u
+    A = np.concatenate([a[None], np.eye(n)])
+    plan = apc.Plan(torch.from_numpy(A).cuda(), torch.from_numpy(np.concatenate([[0.0], x])).cuda(),
+                    off, "f32", gamma=1.0, eta=1.0)
+    d = plan.xbar().cpu().numpy()
+    plan.iterate(1)
+    # x_0(1) = x_bar(0) - C_0 w with w = C_0 . x_bar(0).
+    C = a.astype(np.float32).astype(np.float64)
+    w = (d - plan.local().cpu().numpy()[0].reshape(-1))[at] / C[at]
+    ref = C @ d.astype(np.float32).astype(np.float64)
+    print(f"n={n} {plan.single_pass_shape()}: w off by {(w / ref - 1) / u} u", flush=True)
+    assert np.all(np.abs(w - ref) <= 6 * u * ref)
