@@ -1870,7 +1870,7 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
   // with 137, 206 -> 139 at 16384 x 5000 with 200 even ones, 245 -> 165 at
   // 16384 x 7236 with 85.  With 8 chunks two workgroups run per CU and a change
   // of block costs about a row's time, so only with up to a third as many
-  // blocks as CUs: FP32 62.4 -> 58.6 at 8192 x 8192, 105.5 -> 95.8 at 16384 x
+  // blocks as CUs: FP32 62.4 -> 58.6 at 8192 x 8192, 105.5 -> 89.2 at 16384 x
   // 7236, but 64.4 -> 71.4 at 12000 x 6005.  Narrower rows lose (FP32 24.6 ->
   // 31.2 at 10000 x 2200 with 100 blocks).
   int cus = 0;
@@ -1936,12 +1936,19 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
     // take every register of a wave, one workgroup per CU: tiles beyond the
     // CU count then run as a second round of their own.  Between one and two
     // tiles per CU, one-row groups (two workgroups per CU) run them at once.
+    // Not where the rows are split evenly: there one workgroup per CU takes
+    // its tiles in turn, and one-row groups only halve its loads in flight
+    // (per launch, one row -> two: FP32 85.1 -> 78.5 us at 16384 x 7236, 91.2 ->
+    // 86.0 at 16384 x 8192, 52.3 -> 50.1 at 8300 x 8192; FP64 89.8 -> 83.8 at
+    // 16384 x 4000, 50.4 -> 48.2 at 8300 x 4096).  Even splits of 32 rows keep the
+    // one-row groups that apc_get_launch has reported for 8192 rows all along
+    // (49.0 against 46.6 us at 8192 x 8192).
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const int ce = fused ? elem : 4, cc = fused ? cpt : cpt32;
     const bool fixed = std::getenv("APC_FUSED_G") != nullptr;
-    if (!fixed && P->fused_g == 2 && cc >= 8 && P->ntiles_f > cus && P->ntiles_f <= 2 * cus &&
-        fused_shape_ok(ce, ce, cc, 1))
+    if (!fixed && (P->fused_nwg == 0 || fused_rows <= 32) && P->fused_g == 2 && cc >= 8 &&
+        P->ntiles_f > cus && P->ntiles_f <= 2 * cus && fused_shape_ok(ce, ce, cc, 1))
       P->fused_g = 1;
   }
   if (fused) {

@@ -181,3 +181,23 @@ def test_wave_sums_of_whole_tiles(n):
     ref = C @ d.astype(np.float32).astype(np.float64)
     print(f"n={n} {plan.single_pass_shape()}: w off by {(w / ref - 1) / u} u", flush=True)
     assert np.all(np.abs(w - ref) <= 6 * u * ref)
+
+
+@pytest.mark.parametrize("prec,N,n,m,rows,group", [
+    ("f32", 8192, 8192, 64, 32, 1), ("f32", 8300, 8192, 64, 33, 2), ("f32", 16384, 8192, 30, 64, 2), ("f32", 16384, 5000, 80, 64, 2),
+    ("f64", 16384, 4000, 80, 64, 2)])
+def test_split_and_groups_of_wide_rows(prec, N, n, m, rows, group):
+    """FP32 and FP64 rows of eight chunks per thread in uneven blocks: one workgroup per CU
+    over an even split of more than 32 rows reads two rows at a time."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1708_01413_amd import apc
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus != 256:
+        pytest.skip("the shapes are those of 256 CUs")
+    p = np.random.default_rng(m).uniform(0.2, 1.0, m)
+    off = np.concatenate([[0], np.round(np.cumsum(p) / p.sum() * N)]).astype(np.int64)
+    g = torch.Generator(device="cuda").manual_seed(m)
+    A = torch.randn(N, n, generator=g, dtype=torch.float64, device="cuda") / n ** 0.5
+    plan = apc.Plan(A, A[:, 0].contiguous(), off, prec, gamma=1.2, eta=1.1)
+    assert plan.single_pass_shape() == {"rows_per_wg": rows, "rows_per_group": group}
