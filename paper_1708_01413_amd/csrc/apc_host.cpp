@@ -1863,16 +1863,25 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
 
   // Tiles of fused_rows rows end where blocks end: uneven blocks leave short
   // tiles, and a few tiles more than CUs leave most CUs idle while some take a
-  // second one.  Where the fullest CU would have over 1.05 of the mean rows, the
-  // rows are split evenly over one workgroup per CU instead -- with rows of 16
-  // chunks per thread (one workgroup per CU) always: an FP64 update 143 -> 99 us
-  // at 8192 x 8192 with 64 blocks of 32 to 256 rows, 138 -> 118 at 12000 x 6005
-  // with 137, 206 -> 139 at 16384 x 5000 with 200 even ones, 245 -> 165 at
-  // 16384 x 7236 with 85.  With 8 chunks two workgroups run per CU and a change
-  // of block costs about a row's time, so only with up to a third as many
-  // blocks as CUs: FP32 62.4 -> 58.6 at 8192 x 8192, 105.5 -> 89.2 at 16384 x
-  // 7236, but 64.4 -> 71.4 at 12000 x 6005.  Narrower rows lose (FP32 24.6 ->
-  // 31.2 at 10000 x 2200 with 100 blocks).
+  // second one.  The rows can be split evenly over one workgroup per CU instead.
+  // With rows of 16 chunks per thread (one workgroup per CU either way) that
+  // pays wherever the fullest CU would have over 1.05 of the mean rows: an FP64
+  // update 143 -> 99 us at 8192 x 8192 with 64 blocks of 32 to 256 rows, 138 ->
+  // 118 at 12000 x 6005 with 137, 206 -> 139 at 16384 x 5000 with 200 even ones,
+  // 245 -> 165 at 16384 x 7236 with 85; a pass 118 -> 98 at 14000 x 5000.  With 8
+  // chunks two workgroups of plain tiles share a CU, and a change of block inside
+  // a workgroup costs about a row's time: only with up to a third as many blocks
+  // as CUs (FP32 pass 56.2 -> 58.7 at 8250 x 8192 with 110), and
+  //   rows that fill over 7 of the 8 chunks as above: FP32 50.8 -> 49.0 at
+  //   8192 x 8192, 100.5 -> 85.9 at 16384 x 8192, 47.2 -> 44.6 at 9000 x 7236,
+  //   84.9 -> 80.9 at 15000 x 8192 (but 69.2 -> 72.1 at 12000 x 8192 with 80);
+  //   narrower ones, whose plain tiles keep as many loads in flight, where the
+  //   fullest CU has nearly twice the mean.  Tiles of 64 rows: 71 -> 61 at
+  //   16384 x 5000 (2.0), 72 -> 66 at 18000 x 5000 (1.82), but 83.6 -> 85.6 at
+  //   20000 x 6005 (1.64), 78 -> 86 at 24000 x 5000 (1.37), FP64 82 -> 99 at 26000
+  //   x 2500 (1.26).  Of 32: 28.5 -> 28.1 at 8250 x 4200 (1.99), but 29.9 -> 32.3 at
+  //   8300 x 5000 with 80 blocks (1.97), 32.0 -> 34.9 at 10000 x 5000 (1.64).
+  // Narrower rows lose (FP32 18.0 -> 23.0 at 10000 x 2200 with 100 blocks).
   int cus = 0;
   HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const int fused_c = fused ? cpt : cpt32;
@@ -1880,7 +1889,9 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
       (fused_c >= 16 ? m <= 2 * cus : fused_c == 8 && 3 * m <= cus)) {
     const int64_t tiles = static_cast<int64_t>(T.f_row0.size());
     const int64_t fullest = (tiles + cus - 1) / cus * fused_rows;
-    if (20 * fullest * cus > 21 * N) {
+    const bool wide = L.ldc * (fused ? elem : 4) > 7 * 256 * 16;  // over seven chunks of 256 threads
+    const int64_t percent = wide ? 105 : fused_rows == 64 ? 180 : 198;
+    if (100 * fullest * cus > percent * N) {
       Tiles E;
       build_even_tiles(off, m, cus, &E);
       // The lists and partial rows have to fit the slices of the 16-row tiles.

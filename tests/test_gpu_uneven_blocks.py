@@ -185,10 +185,14 @@ def test_wave_sums_of_whole_tiles(n):
 
 @pytest.mark.parametrize("prec,N,n,m,rows,group", [
     ("f32", 8192, 8192, 64, 32, 1), ("f32", 8300, 8192, 64, 33, 2), ("f32", 16384, 8192, 30, 64, 2), ("f32", 16384, 5000, 80, 64, 2),
-    ("f64", 16384, 4000, 80, 64, 2)])
+    ("f64", 16384, 4000, 80, 64, 2), ("f32", 14000, 5000, 40, 32, 1), ("f32", 20000, 5000, 60, 64, 1),
+    ("f64", 26000, 2500, 60, 64, 1)])
 def test_split_and_groups_of_wide_rows(prec, N, n, m, rows, group):
     """FP32 and FP64 rows of eight chunks per thread in uneven blocks: one workgroup per CU
-    over an even split of more than 32 rows reads two rows at a time."""
+    over an even split of more than 32 rows reads two rows at a time; plain tiles (rows per
+    workgroup 32 or 64) of between one and two per CU one row, two workgroups per CU.
+    Rows that do not fill their chunks keep the plain tiles unless the fullest CU had
+    nearly twice the mean."""
     import torch
     assert torch.cuda.is_available()
     from paper_1708_01413_amd import apc
