@@ -963,7 +963,8 @@ struct TnScrub {
   int type;
   TnChoice choice;
 };
-apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
+// fuses: the contraction's epilogue is one that k_tn_ks applies itself.
+apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* out,
                    const TnScrub* scrub = nullptr) {
   struct Key {
     int type;
@@ -1013,13 +1014,16 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
     return APC_OK;
   }
   static std::mutex mu;
-  static std::map<Key, TnChoice> cache;
+  struct Entry {
+    TnChoice best[2];  // [1]: counting the launch of an epilogue that k_tn_ks applies
+  };
+  static std::map<Key, Entry> cache;
   const Key key{type, base.rows, base.K, base.kp};
   {
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
     if (it != cache.end()) {
-      *out = it->second;
+      *out = it->second.best[fuses];
       return APC_OK;
     }
   }
@@ -1064,10 +1068,13 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
         cand.push_back(c);
       }
   }
-  // It saves the epilogue's launch, which takes at least this long (4.1-5.5 us
-  // for the smallest operands).
+  // Where the epilogue is one of its own it saves that launch, which takes at
+  // least this long (4.1-5.5 us for the smallest operands).  The state that an
+  // epilogue reads and writes is the same on both sides, and left out on both.
+  // Where a launch follows either way (the residual) it saves nothing, so both
+  // choices are kept from one round of timing.
   constexpr float kEpilogueMs = 4.0e-3f;
-  TnChoice best;
+  Entry entry;
   int plain_nsplit = 1;
   {
     // Each timed launch takes a pair of events recorded from its own dispatch.
@@ -1081,8 +1088,8 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
       if (!scrub) return hipSuccess;
       return launch_choice(scrub->type, scrub->choice, scrub->args, P->stream);
     };
-    float best_ms = 0.f, plain_ms = 0.f;
-    bool have = false, have_plain = false;
+    float best_ms[2] = {}, plain_ms = 0.f;
+    bool have[2] = {}, have_plain = false;
     for (const TnChoice& c : cand) {
       TnArgs a = base;
       a.nsplit = c.nsplit;
@@ -1114,12 +1121,13 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
         return fail(APC_EHIP, "tuning launch failed: %s", hipGetErrorString(err));
       }
       ms /= static_cast<float>(kReps);
-      const float cost = ms + (c.ks ? 0.f : kEpilogueMs);
-      if (!have || cost < best_ms) {
-        best = c;
-        best_ms = cost;
-        best.us = ms * 1e3f;
-        have = true;
+      for (int f = 0; f < 2; ++f) {
+        const float cost = ms + (f && !c.ks ? kEpilogueMs : 0.f);
+        if (have[f] && cost >= best_ms[f]) continue;
+        entry.best[f] = c;
+        entry.best[f].us = ms * 1e3f;
+        best_ms[f] = cost;
+        have[f] = true;
       }
       if (!c.ks && (!have_plain || ms < plain_ms)) {
         plain_ms = ms;
@@ -1128,11 +1136,11 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, TnChoice* out,
       }
     }
     destroy();
-    best.plain_nsplit = plain_nsplit;
+    for (TnChoice& c : entry.best) c.plain_nsplit = plain_nsplit;
   }
   std::lock_guard<std::mutex> lk(mu);
-  cache[key] = best;
-  *out = best;
+  cache[key] = entry;
+  *out = entry.best[fuses];
   return APC_OK;
 }
 
@@ -1732,12 +1740,13 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
       TnScrub sb{tn_args(P->ws + L.CqT, L.Np, L.np, P->ws + L.Wq, L.Np, P->kp, L.Np, dflt, P->tq,
                          P->ws + L.tnpart, L.np),
                  P->tq, dflt};
-      ST_TRY(tn_tune(P, P->tq, pass_a_args(P), &P->tnA, &sb));
+      ST_TRY(tn_tune(P, P->tq, pass_a_args(P), true, &P->tnA, &sb));
       const TnScrub sa{pass_a_args(P), P->tq, P->tnA};
-      ST_TRY(tn_tune(P, P->tq, pass_b_args(P), &P->tnB, &sa));
+      ST_TRY(tn_tune(P, P->tq, pass_b_args(P), true, &P->tnB, &sa));
     }
-    ST_TRY(tn_tune(P, x0_type(P), x0_args(P), &P->tnX0));
-    ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()), &P->tnR));
+    ST_TRY(tn_tune(P, x0_type(P), x0_args(P), true, &P->tnX0));
+    // (Anchor updates run in this shape too, more often than residuals are formed.)
+    ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()), P->anchor_every > 0, &P->tnR));
   } else {
     // Alg. 1 initialisation: x_i(0) = Q_i c_i (minimum-norm local solutions),
     // x_bar(0) = (1/m) sum_i x_i(0).  The matrix-core triangular product left
