@@ -1,6 +1,7 @@
 """The contraction whose waves split K and that applies its epilogue itself (forced with
-APC_TN_KS, 16 or 32 right-hand sides per workgroup): every epilogue and element type, on
-sizes with one row tile, with fewer steps of K than waves and with ragged ends."""
+APC_TN_KS, 16 or 32 right-hand sides per workgroup): its epilogues and element types (the
+FP32 reverse step in test_gpu_fp32_products.py), on sizes with one row tile, with fewer
+steps of K than waves and with ragged ends."""
 
 import math
 

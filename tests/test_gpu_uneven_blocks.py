@@ -1,5 +1,5 @@
 """Single right-hand side with blocks of different heights: the combine that stages every
-partial row in LDS, and the one without for more tiles than LDS holds."""
+partial row in LDS, tiles held whole, rows split evenly, the batch's combine."""
 
 import numpy as np
 import pytest
@@ -15,8 +15,8 @@ def _blocks(m, lo, hi, seed):
     return np.concatenate([[0], np.cumsum(p)]).astype(np.int64)
 
 
-# m, smallest and largest block, n: one tile per block and two; a ragged last column group;
-# more blocks than the sums kept in registers; FP64 tiles past what LDS holds (FP32 within).
+# m, smallest and largest block, n: up to three tiles of 16 rows per block; a ragged last
+# column group; more blocks than the sums kept in registers; one tile per block.
 @pytest.mark.parametrize("prec,tol", [("f64", 1e-10), ("f32", 1e-5)])
 @pytest.mark.parametrize("m,lo,hi,n", [(3, 1, 40, 41), (17, 5, 33, 257), (131, 1, 20, 513),
                                        (500, 1, 3, 170)])
