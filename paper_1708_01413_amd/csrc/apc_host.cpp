@@ -1199,6 +1199,7 @@ apc_status advance(apc_plan_s* P, int32_t T) {
   return APC_OK;
 }
 
+// (k-RHS plans: at most; a contraction that applies its epilogue saves one.)
 int launches_per_update(const apc_plan_s* P) {
   if (P->gemm) return 4;
   if (P->fused) return 2;
@@ -1944,8 +1945,9 @@ apc_status apc_setup(apc_plan* out, const double* A, int64_t lda, const double* 
   P->fused = fused;
   P->fused_rows = fused_rows;
   P->fused_g = fused_g;
-  // Tiles of 16 rows (fewer than 8192 rows in all): whole in registers where
-  // rows are narrow enough, unless the looping kernel's groups are asked for.
+  // Tiles of 16 rows (fewer than 8192 rows in all, 16384 where a thread has two
+  // chunks of a row or fewer): whole in registers where rows are narrow enough,
+  // unless the looping kernel's groups are asked for.
   P->fused_once = fused_rows > 0 && fused_rows <= kFusedOnceRows &&
                   std::getenv("APC_FUSED_G") == nullptr;
   P->ntiles_f = static_cast<int32_t>(T.f_row0.size());
