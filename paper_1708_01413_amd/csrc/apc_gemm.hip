@@ -419,13 +419,22 @@ __global__ __launch_bounds__(256) void k_tn_operand(const double* src, int64_t l
 
 // The same with the rows' scales (see launch_tn_operand), a workgroup per row:
 // its largest magnitude first, so that no launch of its own is needed for it.
+// Once per start; bound by what one CU reads of its row twice (7.8 us for 64 rows
+// of 8192, 13.0 for 128 of 16384, with single loads 9.0 and 16.8; k_tn_operand
+// over all CUs 4.0 and 8.4, plus a launch and a pass for the magnitudes).
 template <typename TQ>
 __global__ __launch_bounds__(1024) void k_tn_operand_scale(const double* src, int64_t lds, int64_t cols,
                                                            TQ* dst, int64_t ldd, double* scale) {
   const int64_t c = blockIdx.x;
   const double* row = src + c * lds;
   double big = 0.0;
-  for (int64_t j = threadIdx.x; j < cols; j += 1024) big = fmax(big, fabs(row[j]));  // (NaN: ignored)
+  for (int64_t j = threadIdx.x; j < cols; j += 8 * 1024) {
+    double v[8];  // (eight loads in flight)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = row[min(j + 1024 * u, cols - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) big = fmax(big, fabs(v[u]));  // (NaN: ignored)
+  }
   __shared__ double red[16];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o));
@@ -447,11 +456,20 @@ __global__ __launch_bounds__(1024) void k_tn_operand_scale(const double* src, in
     scale[c] = f;
     scale[gridDim.x + c] = inv;
   }
-  for (int64_t j = 4 * threadIdx.x; j < ldd; j += 4096) {
-    TQ q[4];
+  for (int64_t j = 4 * threadIdx.x; j < ldd; j += 2 * 4096) {
+    double v[2][4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = j + u < cols ? cvt_scaled<TQ>(row[j + u], f) : cvt<TQ>(0.0);
-    store_operand4(dst, ldd, c, j, q);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[h][u] = row[min(j + 4096 * h + u, cols - 1)];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t jh = j + 4096 * h;
+      TQ q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q[u] = jh + u < cols ? cvt_scaled<TQ>(v[h][u], f) : cvt<TQ>(0.0);
+      if (jh < ldd) store_operand4(dst, ldd, c, jh, q);
+    }
   }
 }
 
