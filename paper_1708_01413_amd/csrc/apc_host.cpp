@@ -963,8 +963,15 @@ struct TnScrub {
   int type;
   TnChoice choice;
 };
-// fuses: the contraction's epilogue is one that k_tn_ks applies itself.
-apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* out,
+// use: the epilogue that the contraction is timed with, and whether it is the one
+// that follows (else the choice counts the bare contraction: the residual's own
+// launch follows whichever kernel runs).
+struct TnUse {
+  void* out;   // the operand W, or null: the (y, x_bar) update of the given mode
+  int mode;
+  bool follows;
+};
+apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnChoice* out,
                    const TnScrub* scrub = nullptr) {
   struct Key {
     int type;
@@ -1015,7 +1022,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
   }
   static std::mutex mu;
   struct Entry {
-    TnChoice best[2];  // [1]: counting the launch of an epilogue that k_tn_ks applies
+    TnChoice best[2];  // of the bare contraction, with its epilogue
   };
   static std::map<Key, Entry> cache;
   const Key key{type, base.rows, base.K, base.kp};
@@ -1023,7 +1030,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
     if (it != cache.end()) {
-      *out = it->second.best[fuses];
+      *out = it->second.best[use.follows];
       return APC_OK;
     }
   }
@@ -1068,25 +1075,64 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
         cand.push_back(c);
       }
   }
-  // Where the epilogue is one of its own it saves that launch, which takes at
-  // least this long (4.1-5.5 us for the smallest operands).  The state that an
-  // epilogue reads and writes is the same on both sides, and left out on both.
-  // Where a launch follows either way (the residual) it saves nothing, so both
-  // choices are kept from one round of timing.
-  constexpr float kEpilogueMs = 4.0e-3f;
+  // Every candidate is timed as it would run: k_tn and then the launch of its
+  // epilogue, k_tn_ks with its epilogue in place; and bare.  Between two
+  // launches the GPU is idle for about this long (an update of 4096^2, k = 16 in
+  // two launches takes 2.0 us more than its kernels).  Counting a flat 4 us for
+  // the epilogue's launch instead, processes differed in their choice there
+  // (25.9 and 30.0 ms per call of 200 updates and their adjoint).
+  constexpr float kGapMs = 1.0e-3f;
+  // The epilogue reads and writes the plan's state, which the start will set.
+  {
+    const int64_t words = 2 * static_cast<int64_t>(P->kp) * P->L.np;
+    const bool anc = P->prec != APC_F64;
+    HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.x0), words, 0u, P->stream));
+    HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.ys), words, 0u, P->stream));
+    if (anc) HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.yref), words, 0u, P->stream));
+    if (anc) HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.uref), words, 0u, P->stream));
+    HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.vs), 8 * static_cast<int64_t>(P->kp), 0u, P->stream));
+  }
   Entry entry;
   int plain_nsplit = 1;
   {
-    // Each timed launch takes a pair of events recorded from its own dispatch.
+    // Each timed launch takes a pair of events recorded from its own dispatch:
+    // the bare contraction, its epilogue (k_tn), the two in one (k_tn_ks).
     constexpr int kReps = 3;
-    hipEvent_t ev[2 * kReps] = {};
+    hipEvent_t ev[4 * kReps] = {};
     for (hipEvent_t& e : ev) HIP_TRY(hipEventCreate(&e));
     auto destroy = [&]() {
       for (hipEvent_t& e : ev) (void)hipEventDestroy(e);
     };
-    auto run_scrub = [&]() -> hipError_t {
-      if (!scrub) return hipSuccess;
-      return launch_choice(scrub->type, scrub->choice, scrub->args, P->stream);
+    auto timed = [&](hipEvent_t* pair, auto&& launch) -> hipError_t {
+      if (pair) pending_timing() = TimedLaunch{pair[0], pair[1]};
+      const hipError_t err = launch();
+      if (err == hipSuccess && pending_timing().start) {  // not taken (never expected)
+        pending_timing() = TimedLaunch{};
+        return hipErrorInvalidValue;
+      }
+      return err;
+    };
+    auto scrubbed = [&](hipEvent_t* pair, auto&& launch) -> hipError_t {
+      if (scrub) {
+        const hipError_t err = launch_choice(scrub->type, scrub->choice, scrub->args, P->stream);
+        if (err != hipSuccess) return err;
+      }
+      return timed(pair, launch);
+    };
+    auto run = [&](const TnChoice& c, const TnArgs& a, hipEvent_t* pairs) -> hipError_t {
+      hipError_t err = scrubbed(pairs, [&] { return launch_choice(type, c, a, P->stream); });
+      if (err != hipSuccess) return err;
+      const TnUpdateArgs u = update_args(P, c, use.mode);
+      auto epilogue = [&] {
+        if (!use.out)
+          return c.ks ? launch_tn_ks_update(type, c.ks, a, P->tq, u, P->stream)
+                      : launch_tn_update(P->tq, type == kTnF64, u, P->stream);
+        return c.ks ? launch_tn_ks_operand(type, c.ks, a, use.out, a.rows, P->stream)
+                    : launch_tn_sum_cast(type, a.part, c.nsplit, a.kp, a.rows, a.rows, use.out,
+                                         a.rows, P->stream);
+      };
+      hipEvent_t* second = pairs ? pairs + 2 : nullptr;
+      return c.ks ? scrubbed(second, epilogue) : timed(second, epilogue);
     };
     float best_ms[2] = {}, plain_ms = 0.f;
     bool have[2] = {}, have_plain = false;
@@ -1096,41 +1142,32 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
       a.nt = c.nt;
       a.waves = c.waves;
       a.klen = round_up((a.K + c.nsplit - 1) / c.nsplit, tn_step_elems(type));
-      hipError_t err = run_scrub();
-      if (err == hipSuccess) err = launch_choice(type, c, a, P->stream);  // warm-up
+      hipError_t err = run(c, a, nullptr);  // warm-up
+      for (int r = 0; err == hipSuccess && r < kReps; ++r) err = run(c, a, ev + 4 * r);
+      float bare = 0.f, second = 0.f;
+      if (err == hipSuccess) err = hipEventSynchronize(ev[4 * kReps - 1]);
       for (int r = 0; err == hipSuccess && r < kReps; ++r) {
-        err = run_scrub();
-        if (err != hipSuccess) break;
-        pending_timing() = TimedLaunch{ev[2 * r], ev[2 * r + 1]};
-        err = launch_choice(type, c, a, P->stream);
-        if (pending_timing().start) {  // not taken: record back to back (never expected)
-          pending_timing() = TimedLaunch{};
-          err = hipErrorInvalidValue;
-        }
-      }
-      float ms = 0.f;
-      if (err == hipSuccess) err = hipEventSynchronize(ev[2 * kReps - 1]);
-      for (int r = 0; err == hipSuccess && r < kReps; ++r) {
-        float t = 0.f;
-        err = hipEventElapsedTime(&t, ev[2 * r], ev[2 * r + 1]);
-        ms += t;
+        float t = 0.f, t2 = 0.f;
+        err = hipEventElapsedTime(&t, ev[4 * r], ev[4 * r + 1]);
+        if (err == hipSuccess) err = hipEventElapsedTime(&t2, ev[4 * r + 2], ev[4 * r + 3]);
+        bare += t / kReps;
+        second += t2 / kReps;
       }
       if (err != hipSuccess) {
         pending_timing() = TimedLaunch{};
         destroy();
         return fail(APC_EHIP, "tuning launch failed: %s", hipGetErrorString(err));
       }
-      ms /= static_cast<float>(kReps);
+      const float cost[2] = {bare, c.ks ? second : bare + kGapMs + second};
       for (int f = 0; f < 2; ++f) {
-        const float cost = ms + (f && !c.ks ? kEpilogueMs : 0.f);
-        if (have[f] && cost >= best_ms[f]) continue;
+        if (have[f] && cost[f] >= best_ms[f]) continue;
         entry.best[f] = c;
-        entry.best[f].us = ms * 1e3f;
-        best_ms[f] = cost;
+        entry.best[f].us = (f && c.ks ? second : bare) * 1e3f;
+        best_ms[f] = cost[f];
         have[f] = true;
       }
-      if (!c.ks && (!have_plain || ms < plain_ms)) {
-        plain_ms = ms;
+      if (!c.ks && (!have_plain || bare < plain_ms)) {
+        plain_ms = bare;
         plain_nsplit = c.nsplit;
         have_plain = true;
       }
@@ -1140,7 +1177,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
   }
   std::lock_guard<std::mutex> lk(mu);
   cache[key] = entry;
-  *out = entry.best[fuses];
+  *out = entry.best[use.follows];
   return APC_OK;
 }
 
@@ -1741,13 +1778,14 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
       TnScrub sb{tn_args(P->ws + L.CqT, L.Np, L.np, P->ws + L.Wq, L.Np, P->kp, L.Np, dflt, P->tq,
                          P->ws + L.tnpart, L.np),
                  P->tq, dflt};
-      ST_TRY(tn_tune(P, P->tq, pass_a_args(P), true, &P->tnA, &sb));
+      ST_TRY(tn_tune(P, P->tq, pass_a_args(P), TnUse{P->ws + L.Wq, 0, true}, &P->tnA, &sb));
       const TnScrub sa{pass_a_args(P), P->tq, P->tnA};
-      ST_TRY(tn_tune(P, P->tq, pass_b_args(P), true, &P->tnB, &sa));
+      ST_TRY(tn_tune(P, P->tq, pass_b_args(P), TnUse{nullptr, 0, true}, &P->tnB, &sa));
     }
-    ST_TRY(tn_tune(P, x0_type(P), x0_args(P), true, &P->tnX0));
+    ST_TRY(tn_tune(P, x0_type(P), x0_args(P), TnUse{nullptr, 1, true}, &P->tnX0));
     // (Anchor updates run in this shape too, more often than residuals are formed.)
-    ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()), P->anchor_every > 0, &P->tnR));
+    ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()),
+                   TnUse{P->ws + (P->tq == kTnF64 ? L.Wq : L.W64), 0, P->anchor_every > 0}, &P->tnR));
   } else {
     // Alg. 1 initialisation: x_i(0) = Q_i c_i (minimum-norm local solutions),
     // x_bar(0) = (1/m) sum_i x_i(0).  The matrix-core triangular product left
