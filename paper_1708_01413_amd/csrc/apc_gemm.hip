@@ -60,7 +60,7 @@ namespace {
 
 inline bool quad_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 inline bool update_args_ok(int type, const TnUpdateArgs& a) {
-  return (type != kTnF32x3 || a.qs) && a.n % 4 == 0 && a.ldx % 4 == 0 && a.ldq % 4 == 0 && quad_ok(a.x0) && quad_ok(a.y) &&
+  return (type != kTnF32x3 || a.scale) && a.n % 4 == 0 && a.ldx % 4 == 0 && a.ldq % 4 == 0 && quad_ok(a.x0) && quad_ok(a.y) &&
          quad_ok(a.xb) && quad_ok(a.yq) && (!a.yref || (quad_ok(a.yref) && quad_ok(a.uref)));
 }
 
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64 * kKsWaves) void k_tn_ks(TnArgs a, TnKsEpilogue 
     // each would wait for a cold line of the argument buffer.
     asm volatile("" ::"s"(ep.upd.yq), "s"(ep.upd.ldq), "s"(ep.upd.gamma), "s"(ep.upd.eta),
                  "s"(ep.upd.inv_m), "s"(ep.upd.y));
-    if constexpr (Op::kSplit) zs = ep.upd.zs[ec];
+    if constexpr (Op::kSplit) zs = ep.upd.scale[ec].y;
     update_load<TQ, true>(ep.upd, ec, ej, us);  // (threads past the first repeat their entries)
   }
   if constexpr (EPI == kKsAdjoint) {
@@ -387,14 +387,14 @@ __global__ __launch_bounds__(256) void k_tn_anchor_vec(const double* y, const do
 // restored, rows of n entries (stride n).
 template <typename TQ>
 __global__ __launch_bounds__(256) void k_tn_prep(const double* y, const double* xb, int64_t count,
-                                                 int64_t n, double gamma, const double* qs, TQ* yq) {
+                                                 int64_t n, double gamma, const double2* scale, TQ* yq) {
   for (int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x); e < count;
        e += 4 * static_cast<int64_t>(gridDim.x) * blockDim.x) {
     double yv[4], xv[4];
     load4(y + e, yv);
     load4(xb + e, xv);
     const int64_t c = e / n;
-    const double f = TnOperand<TQ>::kSplit ? qs[c] : 1.0;
+    const double f = TnOperand<TQ>::kSplit ? scale[c].x : 1.0;
     TQ q[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) q[u] = cvt_scaled<TQ>((1.0 - gamma) * yv[u] + gamma * xv[u], f);
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(256) void k_tn_operand(const double* src, int64_t l
 // over all CUs 4.0 and 8.4, plus a launch and a pass for the magnitudes).
 template <typename TQ>
 __global__ __launch_bounds__(1024) void k_tn_operand_scale(const double* src, int64_t lds, int64_t cols,
-                                                           TQ* dst, int64_t ldd, double* scale) {
+                                                           TQ* dst, int64_t ldd, double2* scale) {
   const int64_t c = blockIdx.x;
   const double* row = src + c * lds;
   double big = 0.0;
@@ -452,10 +452,7 @@ __global__ __launch_bounds__(1024) void k_tn_operand_scale(const double* src, in
       inv = ldexp(1.0, e);
     }
   }
-  if (threadIdx.x == 0) {
-    scale[c] = f;
-    scale[gridDim.x + c] = inv;
-  }
+  if (threadIdx.x == 0) scale[c] = make_double2(f, inv);
   for (int64_t j = 4 * threadIdx.x; j < ldd; j += 2 * 4096) {
     double v[2][4];
 #pragma unroll
@@ -776,7 +773,7 @@ hipError_t launch_tn_ks_operand(int type, int nct, const TnArgs& a, void* out, i
 hipError_t launch_tn_ks_update(int type, int nct, const TnArgs& a, int type_q, const TnUpdateArgs& u,
                                hipStream_t s) {
   if (!tn_ks_ok(type, nct, a) || !update_args_ok(type_q, u) || u.n != a.rows || u.kp != a.kp ||
-      (type == kTnF32x3 && !u.zs))
+      (type == kTnF32x3 && !u.scale))
     return hipErrorInvalidValue;
   TnKsEpilogue ep{};
   ep.upd = u;
@@ -811,7 +808,7 @@ hipError_t launch_tn_ks_update(int type, int nct, const TnArgs& a, int type_q, c
 hipError_t launch_tn_ks_adjoint(int type, int nct, const TnArgs& a, const TnAdjointArgs& d,
                                 hipStream_t s) {
   if (!tn_ks_ok(type, nct, a) || d.n != a.rows || d.kp != a.kp || d.ldx % 4 ||
-      (type == kTnF32x3 && (!d.qs || !d.zs)) ||
+      (type == kTnF32x3 && !d.scale) ||
       (a.rows / 16) * (a.kp / (16 * nct)) > kTnAdjointBlocks)
     return hipErrorInvalidValue;
   TnKsEpilogue ep{};
@@ -875,15 +872,15 @@ hipError_t launch_tn_anchor_vec(const double* y, const double* xb, int64_t count
 }
 
 hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, int64_t n,
-                          double gamma, const double* qs, void* yq, hipStream_t s) {
-  if (n % tn_step_elems(type) || (type == kTnF32x3 && !qs) || count % n || !quad_ok(y) || !quad_ok(xb) || !quad_ok(yq))
+                          double gamma, const double2* scale, void* yq, hipStream_t s) {
+  if (n % tn_step_elems(type) || (type == kTnF32x3 && !scale) || count % n || !quad_ok(y) || !quad_ok(xb) || !quad_ok(yq))
     return hipErrorInvalidValue;
   const unsigned g = grid_stride_blocks(count / 4);
   switch (type) {
-    case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<double*>(yq)); break;
-    case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<float*>(yq)); break;
-    case kTnF32x3: k_tn_prep<F32x3><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<F32x3*>(yq)); break;
-    case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, n, gamma, qs, static_cast<__bf16*>(yq)); break;
+    case kTnF64: k_tn_prep<double><<<g, 256, 0, s>>>(y, xb, count, n, gamma, scale, static_cast<double*>(yq)); break;
+    case kTnF32: k_tn_prep<float><<<g, 256, 0, s>>>(y, xb, count, n, gamma, scale, static_cast<float*>(yq)); break;
+    case kTnF32x3: k_tn_prep<F32x3><<<g, 256, 0, s>>>(y, xb, count, n, gamma, scale, static_cast<F32x3*>(yq)); break;
+    case kTnBF16: k_tn_prep<__bf16><<<g, 256, 0, s>>>(y, xb, count, n, gamma, scale, static_cast<__bf16*>(yq)); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -891,7 +888,7 @@ hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t c
 
 template <typename TQ>
 static hipError_t tn_operand(const double* src, int64_t lds, int64_t rows, int64_t cols, TQ* dst,
-                             int64_t ldd, double* scale, hipStream_t s) {
+                             int64_t ldd, double2* scale, hipStream_t s) {
   if (scale)
     k_tn_operand_scale<TQ><<<static_cast<unsigned>(rows), 1024, 0, s>>>(src, lds, cols, dst, ldd, scale);
   else if constexpr (TnOperand<TQ>::kSplit)
@@ -902,7 +899,7 @@ static hipError_t tn_operand(const double* src, int64_t lds, int64_t rows, int64
 }
 
 hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t rows, int64_t cols,
-                             void* dst, int64_t ldd, double* scale, hipStream_t s) {
+                             void* dst, int64_t ldd, double2* scale, hipStream_t s) {
   if (ldd % tn_step_elems(type) || cols > ldd || rows < 1 || !quad_ok(dst)) return hipErrorInvalidValue;
   switch (type) {
     case kTnF64: return tn_operand(src, lds, rows, cols, static_cast<double*>(dst), ldd, scale, s);
@@ -915,7 +912,7 @@ hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t r
 int tn_adjoint_blocks() { return kTnAdjointBlocks; }
 
 hipError_t launch_tn_adjoint(int type, const TnAdjointArgs& a, hipStream_t s) {
-  if (type == kTnF32x3 && (!a.qs || !a.zs)) return hipErrorInvalidValue;
+  if (type == kTnF32x3 && !a.scale) return hipErrorInvalidValue;
   switch (type) {
     case kTnF64: k_tn_adjoint<double, double><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;
     case kTnF32: k_tn_adjoint<float, float><<<kTnAdjointBlocks, 256, 0, s>>>(a); break;

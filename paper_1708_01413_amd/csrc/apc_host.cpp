@@ -836,8 +836,7 @@ TnUpdateArgs update_args(const apc_plan_s* P, const TnChoice& ch, int mode) {
                       P->at<double>(L.ys), P->xbar(), L.np, P->ws + L.yq, L.np, P->gamma, P->eta,
                       1.0 / P->m, mode, anc ? P->at<double>(L.yref) : nullptr,
                       anc ? P->at<double>(L.uref) : nullptr,
-                      P->tq == kTnF32x3 ? P->at<double>(L.vs) : nullptr,
-                      z_type == kTnF32x3 ? P->at<double>(L.vs) + P->kp : nullptr};
+                      P->tq == kTnF32x3 || z_type == kTnF32x3 ? P->at<double2>(L.vs) : nullptr};
 }
 
 // One update of the (y, x_bar) form.  In the FP32 and bf16 iterations every
@@ -934,7 +933,7 @@ apc_status update_gemm(apc_plan_s* P, hipEvent_t* ev, int* kinds, int* nev) {
 apc_status start_gemm(apc_plan_s* P, const double* c_rhs) {
   const Layout& L = P->L;
   const int t = x0_type(P);
-  double* scale = t == kTnF32x3 || P->tq == kTnF32x3 ? P->at<double>(L.vs) : nullptr;
+  double2* scale = t == kTnF32x3 || P->tq == kTnF32x3 ? P->at<double2>(L.vs) : nullptr;
   HIP_TRY(launch_tn_operand(t, c_rhs, P->N, P->kp, P->N, P->ws + L.c64p, L.Np, scale, P->stream));
   ST_TRY(pass_b_update(P, t, P->tnX0, x0_args(P), 1));
   P->since_start = 0;
@@ -2563,7 +2562,7 @@ apc_status restore_state(apc_plan_s* P, const double* y, const double* xb) {
   const Layout& L = P->L;
   ST_TRY(copy_state(P, P->at<double>(L.ys), P->xbar(), y, xb));
   HIP_TRY(launch_tn_prep(P->tq, P->at<double>(L.ys), P->xbar(),
-                         static_cast<int64_t>(P->kp) * L.np, L.np, P->gamma, P->at<double>(L.vs),
+                         static_cast<int64_t>(P->kp) * L.np, L.np, P->gamma, P->at<double2>(L.vs),
                          P->ws + L.yq, P->stream));
   P->since_start = 0;
   return APC_OK;
@@ -2628,9 +2627,8 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(g0), 2 * cnt, 0u, st));
   HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(red), 4 * tn_adjoint_blocks(), 0u, st));
   HIP_TRY(launch_tn_pack(dXbar, ldd, P->n, P->k, 1, bh, L.np, P->kp, st));
-  const bool split = P->tq == kTnF32x3;
-  double* bs = P->at<double>(L.vs) + 2 * P->kp;
-  HIP_TRY(launch_tn_operand(P->tq, bh, L.np, P->kp, L.np, bq, L.np, split ? bs : nullptr, st));
+  double2* bs = P->tq == kTnF32x3 ? P->at<double2>(L.vs) + P->kp : nullptr;
+  HIP_TRY(launch_tn_operand(P->tq, bh, L.np, P->kp, L.np, bq, L.np, bs, st));
 
   void* part = P->ws + L.tnpart;
   for (int64_t sgi = nck - 1; sgi >= 0; --sgi) {
@@ -2651,7 +2649,7 @@ apc_status apc_backward(apc_plan p, const double* dXbar, int64_t ldd, int32_t T,
       const double* s_n = seg(t - t0 + 1);
       TnAdjointArgs ad{part, P->tnB.nsplit, P->kp, L.np, L.np, a, bh, g0, s_t, s_t + cnt,
                        s_n + cnt, L.np, bq, L.np, P->gamma, P->eta, 1.0 / P->m, red,
-                       split ? bs : nullptr, split ? bs + P->kp : nullptr};
+                       bs};
       // One launch when the shape holds whole sums and its workgroups fit the
       // sums' slots.
       const TnChoice& cb = P->tnB;

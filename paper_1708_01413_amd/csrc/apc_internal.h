@@ -501,26 +501,26 @@ struct TnUpdateArgs {
   int32_t mode;
   double* yref;
   double* uref;
-  const double* qs;  // kp: yq's rows are stored times qs[c] (kTnF32x3; others null: 1)
-  const double* zs;  // kp: z's rows come times 1 / zs[c] (null: 1)
+  const double2* scale;  // kp: a kTnF32x3 yq's rows are stored times x, such a contraction's
+                         // sums z taken times y (null where neither is one)
 };
 // y_ref[e] = (1 - gamma) y[e] + gamma x_bar[e], e < count.
 hipError_t launch_tn_anchor_vec(const double* y, const double* xb, int64_t count, double gamma,
                                 double* yref, hipStream_t s);
 hipError_t launch_tn_update(int type, int part_f64, const TnUpdateArgs& a, hipStream_t s);
 // yq = TQ((1 - gamma) y + gamma x_bar), count entries in rows of n (the pass-A
-// operand for a restored state), kTnF32x3 times qs[row].
+// operand for a restored state), kTnF32x3 times scale[row].x.
 hipError_t launch_tn_prep(int type, const double* y, const double* xb, int64_t count, int64_t n,
-                          double gamma, const double* qs, void* yq, hipStream_t s);
+                          double gamma, const double2* scale, void* yq, hipStream_t s);
 // dst = the V operand (rows of ldd entries, not bf16) of src (FP64,
-// rows x cols, stride lds), zero past cols.  scale (optional, 2 rows): a power
+// rows x cols, stride lds), zero past cols.  scale (optional, rows): a power
 // of two per row and its reciprocal, 1 unless the row's largest magnitude is
 // outside 2^-64 .. 2^65, then what brings that to 1 .. 2; a kTnF32x3 operand is
 // stored times the first.  Its scale, set by the start (or the reverse sweep's),
 // is kept for the vectors that follow: exact, and they stay in the range where
 // an FP32 value is the sum of its three parts (Split3).
 hipError_t launch_tn_operand(int type, const double* src, int64_t lds, int64_t rows, int64_t cols,
-                             void* dst, int64_t ldd, double* scale, hipStream_t s);
+                             void* dst, int64_t ldd, double2* scale, hipStream_t s);
 // Bytes of a V operand of `rows` rows of ld entries.
 inline int64_t tn_operand_bytes(int type, int64_t rows, int64_t ld) {
   return rows * ld * (type == kTnF64 ? 8 : type == kTnF32x3 ? 6 : type == kTnF32 ? 4 : 2);
@@ -552,8 +552,7 @@ struct TnAdjointArgs {
   double eta;
   double inv_m;
   double* red;
-  const double* qs;  // bq's and z's scales, as TnUpdateArgs'
-  const double* zs;
+  const double2* scale;  // as TnUpdateArgs'
 };
 constexpr int kTnAdjointBlocks = 512;
 int tn_adjoint_blocks();

@@ -571,7 +571,7 @@ __device__ inline void sum_cast4(const P* part, int32_t nsplit, int64_t ldp, int
 // contraction can load it before its products.
 struct UpdateState {
   double xb[4], x0[4], y[4], yr[4], ur[4];  // y: y_ref in an anchor update
-  double qs;
+  double2 scale;
 };
 // kAll: load every field without a branch (absent anchors read y instead, and
 // are not used), so that the loads can stay in flight.
@@ -579,7 +579,7 @@ template <typename TQ, bool kAll>
 __device__ inline void update_load(const TnUpdateArgs& a, int64_t c, int64_t j, UpdateState& s) {
   const int64_t i = c * a.ldx + j;
   const double* y = a.mode == 2 ? a.yref : a.y;
-  if constexpr (TnOperand<TQ>::kSplit) s.qs = a.qs[c];
+  if constexpr (TnOperand<TQ>::kSplit) s.scale = a.scale[c];
   load4(a.xb + i, s.xb);
   load4(a.x0 + i, s.x0);
   load4(y + i, s.y);
@@ -600,7 +600,7 @@ __device__ inline void update_quad(const TnUpdateArgs& a, int64_t c, int64_t j, 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       x0[q] = z[q] * a.inv_m;
-      qv[q] = cvt_scaled<TQ>(g * x0[q], s.qs);
+      qv[q] = cvt_scaled<TQ>(g * x0[q], s.scale.x);
     }
     store4(a.x0 + i, x0);
     store4(a.xb + i, x0);
@@ -628,7 +628,7 @@ __device__ inline void update_quad(const TnUpdateArgs& a, int64_t c, int64_t j, 
     const double xn = eta * (s.x0[q] + y1 - u) + ome * s.xb[q];
     yo[q] = y1;
     xo[q] = xn;
-    qv[q] = cvt_scaled<TQ>(omg * y1 + g * xn - ref, s.qs);
+    qv[q] = cvt_scaled<TQ>(omg * y1 + g * xn - ref, s.scale.x);
   }
   if (a.mode == 2) store4(a.uref + i, uo);
   store4(a.y + i, yo);
@@ -652,7 +652,7 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
   }
   UpdateState s;
   update_load<TQ, false>(a, c, j, s);
-  const double f = sizeof(P) == 4 && a.zs ? a.zs[c] : 1.0;
+  const double f = sizeof(P) == 4 && a.scale ? a.scale[c].y : 1.0;
   const double z[4] = {static_cast<double>(zs[0]) * f, static_cast<double>(zs[1]) * f,
                        static_cast<double>(zs[2]) * f, static_cast<double>(zs[3]) * f};
   update_quad<TQ>(a, c, j, s, z);
@@ -663,15 +663,12 @@ __device__ inline void update4(const TnUpdateArgs& a, int64_t e) {
 // of the dL/dgamma and dL/deta sums.
 struct AdjointState {
   double a[4], bh[4], g0[4], y[4], xb[4], xn[4];
-  double qs, zs;
+  double2 scale;
 };
 template <typename TQ>
 __device__ inline void adjoint_load(const TnAdjointArgs& a, int64_t c, int64_t j, AdjointState& s) {
   const int64_t i = c * a.ldx + j;
-  if constexpr (TnOperand<TQ>::kSplit) {
-    s.qs = a.qs[c];
-    s.zs = a.zs[c];
-  }
+  if constexpr (TnOperand<TQ>::kSplit) s.scale = a.scale[c];
   load4(a.a + i, s.a);
   load4(a.bh + i, s.bh);
   load4(a.g0 + i, s.g0);
@@ -686,7 +683,7 @@ __device__ inline void adjoint_quad(const TnAdjointArgs& a, int64_t c, int64_t j
   TQ qv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const double zq = TnOperand<TQ>::kSplit ? z[q] * s.zs : z[q];
+    const double zq = TnOperand<TQ>::kSplit ? z[q] * s.scale.y : z[q];
     const double xbh = zq * a.inv_m;  // X b
     const double bh = s.bh[q];
     const double at = s.a[q] + a.eta * (bh - xbh);
@@ -695,7 +692,7 @@ __device__ inline void adjoint_quad(const TnAdjointArgs& a, int64_t c, int64_t j
     s.g0[q] += a.eta * bh;
     s.a[q] = (1.0 - a.gamma) * at;
     s.bh[q] = (1.0 - a.eta) * bh + a.gamma * at;
-    qv[q] = cvt_scaled<TQ>(s.bh[q], s.qs);
+    qv[q] = cvt_scaled<TQ>(s.bh[q], s.scale.x);
   }
   store4(a.g0 + i, s.g0);
   store4(a.a + i, s.a);
