@@ -255,7 +255,7 @@ apc_status apc_get_setup(apc_plan p, int32_t* qr_passes, double* qr_defect);
  * the measured time per launch when it was chosen by timing (0 when fixed by
  * APC_TN_TUNE=0 / APC_TN_RT / APC_TN_SPLIT).  Shapes are timed once per
  * problem shape and process.  A shape of 16 rows per workgroup is the
- * kernel whose waves split K and that applies its epilogue itself (timed with it).  which = 4:
+ * kernel whose waves split K and that applies its epilogue itself.  which = 4:
  * the single-pass k = 1 update, rows per workgroup (the mean where the rows are
  * split evenly over the workgroups) and rows per register group (in *splits; of
  * the looping kernel: tiles of 16 rows of up to 16 KiB are held whole),

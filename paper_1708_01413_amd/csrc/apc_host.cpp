@@ -486,6 +486,7 @@ struct apc_plan_s {
   bool resident = false;               // k = 1 FP64: T updates in one launch (k_resident)
   int32_t res_rpw = 0, res_cpl = 0, res_stride = 1;
   uint32_t res_spin = 1u << 22;        // polls of one exchanged word before it gives up
+  const double* tune_rhs = nullptr;    // set while setup tunes: c for tune_start
   int32_t qr_passes = 2;               // CholeskyQR passes setup took (1: see setup_impl)
   double qr_defect = NAN;              // estimated ||Q_i^T Q_i - I|| after the first pass
   double* pinned = nullptr;            // pinned host staging (Lanczos coefficients, setup readbacks)
@@ -949,6 +950,23 @@ apc_status gemm_residual(apc_plan_s* P, const double* X, double* R) {
   return APC_OK;
 }
 
+// Once per setup that has to time anything: the start, in a default shape (the
+// real one follows in the tuned shape and sets all of the state again), so that
+// the operands hold what an update multiplies (zeros draw less power).  gamma and
+// eta may not be known yet.
+apc_status tune_start(apc_plan_s* P) {
+  if (!P->tune_rhs) return APC_OK;
+  const double* c = P->tune_rhs;
+  P->tune_rhs = nullptr;
+  const TnChoice keep = P->tnX0;
+  P->tnX0 = TnChoice{};
+  P->tnX0.rt = 1;
+  P->tnX0.nsplit = 4;
+  const apc_status st = start_gemm(P, c);
+  P->tnX0 = keep;
+  return st;
+}
+
 // Chooses the launch shape of one contraction by timing the candidates on the
 // plan's operands (the partial buffer is scratch here).  Shapes are cached per
 // (type, rows, K, kp) for the life of the process, so repeated plans of one
@@ -962,16 +980,11 @@ struct TnScrub {
   int type;
   TnChoice choice;
 };
-// use: the epilogue that the contraction is timed with, and whether it is the one
-// that follows (else the choice counts the bare contraction: the residual's own
-// launch follows whichever kernel runs).
-struct TnUse {
-  void* out;   // the operand W, or null: the (y, x_bar) update of the given mode
-  int mode;
-  bool follows;
-};
-apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnChoice* out,
-                   const TnScrub* scrub = nullptr) {
+// fuses: the contraction's epilogue is one that k_tn_ks applies itself.
+// top (optional): the fastest few as well, for tn_tune_update.
+constexpr size_t kTuneTop = 4;
+apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* out,
+                   const TnScrub* scrub = nullptr, std::vector<TnChoice>* top = nullptr) {
   struct Key {
     int type;
     int64_t rows, K;
@@ -1017,11 +1030,13 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnCho
           base.rows % (128 * c.rt) == 0)
         c.waves = 8;
     *out = c;
+    if (top) top->assign(1, c);
     return APC_OK;
   }
   static std::mutex mu;
   struct Entry {
-    TnChoice best[2];  // of the bare contraction, with its epilogue
+    TnChoice best[2];  // [1]: counting the launch of an epilogue that k_tn_ks applies
+    std::vector<TnChoice> top;
   };
   static std::map<Key, Entry> cache;
   const Key key{type, base.rows, base.K, base.kp};
@@ -1029,7 +1044,8 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnCho
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
     if (it != cache.end()) {
-      *out = it->second.best[use.follows];
+      *out = it->second.best[fuses];
+      if (top) *top = it->second.top;
       return APC_OK;
     }
   }
@@ -1074,64 +1090,27 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnCho
         cand.push_back(c);
       }
   }
-  // Every candidate is timed as it would run: k_tn and then the launch of its
-  // epilogue, k_tn_ks with its epilogue in place; and bare.  Between two
-  // launches the GPU is idle for about this long (an update of 4096^2, k = 16 in
-  // two launches takes 2.0 us more than its kernels).  Counting a flat 4 us for
-  // the epilogue's launch instead, processes differed in their choice there
-  // (25.9 and 30.0 ms per call of 200 updates and their adjoint).
-  constexpr float kGapMs = 1.0e-3f;
-  // The epilogue reads and writes the plan's state, which the start will set.
-  {
-    const int64_t words = 2 * static_cast<int64_t>(P->kp) * P->L.np;
-    const bool anc = P->prec != APC_F64;
-    HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.x0), words, 0u, P->stream));
-    HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.ys), words, 0u, P->stream));
-    if (anc) HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.yref), words, 0u, P->stream));
-    if (anc) HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.uref), words, 0u, P->stream));
-    HIP_TRY(launch_fill_u32(P->at<unsigned>(P->L.vs), 8 * static_cast<int64_t>(P->kp), 0u, P->stream));
-  }
+  // Where the epilogue is one of its own it saves that launch, which takes at
+  // least this long (4.1-5.5 us for the smallest operands); where a launch
+  // follows either way (the residual) it saves nothing.  Both choices are kept
+  // from one round of timing.  What an update's passes really take is left to
+  // tn_tune_update.
+  constexpr float kEpilogueMs = 4.0e-3f;
+  ST_TRY(tune_start(P));
   Entry entry;
+  std::vector<std::pair<float, TnChoice>> ranked;
   int plain_nsplit = 1;
   {
-    // Each timed launch takes a pair of events recorded from its own dispatch:
-    // the bare contraction, its epilogue (k_tn), the two in one (k_tn_ks).
+    // Each timed launch takes a pair of events recorded from its own dispatch.
     constexpr int kReps = 3;
-    hipEvent_t ev[4 * kReps] = {};
+    hipEvent_t ev[2 * kReps] = {};
     for (hipEvent_t& e : ev) HIP_TRY(hipEventCreate(&e));
     auto destroy = [&]() {
       for (hipEvent_t& e : ev) (void)hipEventDestroy(e);
     };
-    auto timed = [&](hipEvent_t* pair, auto&& launch) -> hipError_t {
-      if (pair) pending_timing() = TimedLaunch{pair[0], pair[1]};
-      const hipError_t err = launch();
-      if (err == hipSuccess && pending_timing().start) {  // not taken (never expected)
-        pending_timing() = TimedLaunch{};
-        return hipErrorInvalidValue;
-      }
-      return err;
-    };
-    auto scrubbed = [&](hipEvent_t* pair, auto&& launch) -> hipError_t {
-      if (scrub) {
-        const hipError_t err = launch_choice(scrub->type, scrub->choice, scrub->args, P->stream);
-        if (err != hipSuccess) return err;
-      }
-      return timed(pair, launch);
-    };
-    auto run = [&](const TnChoice& c, const TnArgs& a, hipEvent_t* pairs) -> hipError_t {
-      hipError_t err = scrubbed(pairs, [&] { return launch_choice(type, c, a, P->stream); });
-      if (err != hipSuccess) return err;
-      const TnUpdateArgs u = update_args(P, c, use.mode);
-      auto epilogue = [&] {
-        if (!use.out)
-          return c.ks ? launch_tn_ks_update(type, c.ks, a, P->tq, u, P->stream)
-                      : launch_tn_update(P->tq, type == kTnF64, u, P->stream);
-        return c.ks ? launch_tn_ks_operand(type, c.ks, a, use.out, a.rows, P->stream)
-                    : launch_tn_sum_cast(type, a.part, c.nsplit, a.kp, a.rows, a.rows, use.out,
-                                         a.rows, P->stream);
-      };
-      hipEvent_t* second = pairs ? pairs + 2 : nullptr;
-      return c.ks ? scrubbed(second, epilogue) : timed(second, epilogue);
+    auto run_scrub = [&]() -> hipError_t {
+      if (!scrub) return hipSuccess;
+      return launch_choice(scrub->type, scrub->choice, scrub->args, P->stream);
     };
     float best_ms[2] = {}, plain_ms = 0.f;
     bool have[2] = {}, have_plain = false;
@@ -1141,32 +1120,53 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnCho
       a.nt = c.nt;
       a.waves = c.waves;
       a.klen = round_up((a.K + c.nsplit - 1) / c.nsplit, tn_step_elems(type));
-      hipError_t err = run(c, a, nullptr);  // warm-up
-      for (int r = 0; err == hipSuccess && r < kReps; ++r) err = run(c, a, ev + 4 * r);
-      float bare = 0.f, second = 0.f;
-      if (err == hipSuccess) err = hipEventSynchronize(ev[4 * kReps - 1]);
+      // Long passes: one whose warm-up is far behind is not timed again (a wait, so
+      // not for short ones, which an idle GPU would run slower after it).
+      const bool peek = !c.ks && have_plain && plain_ms > 0.1f;
+      hipError_t err = run_scrub();
+      if (err == hipSuccess && peek) pending_timing() = TimedLaunch{ev[0], ev[1]};
+      if (err == hipSuccess) err = launch_choice(type, c, a, P->stream);  // warm-up
+      if (err == hipSuccess && peek) {
+        float t = 0.f;
+        err = hipEventSynchronize(ev[1]);
+        if (err == hipSuccess) err = hipEventElapsedTime(&t, ev[0], ev[1]);
+        if (err == hipSuccess && t > 1.5f * plain_ms) continue;
+      }
       for (int r = 0; err == hipSuccess && r < kReps; ++r) {
-        float t = 0.f, t2 = 0.f;
-        err = hipEventElapsedTime(&t, ev[4 * r], ev[4 * r + 1]);
-        if (err == hipSuccess) err = hipEventElapsedTime(&t2, ev[4 * r + 2], ev[4 * r + 3]);
-        bare += t / kReps;
-        second += t2 / kReps;
+        err = run_scrub();
+        if (err != hipSuccess) break;
+        pending_timing() = TimedLaunch{ev[2 * r], ev[2 * r + 1]};
+        err = launch_choice(type, c, a, P->stream);
+        if (pending_timing().start) {  // not taken: record back to back (never expected)
+          pending_timing() = TimedLaunch{};
+          err = hipErrorInvalidValue;
+        }
+      }
+      float ms = 0.f;
+      if (err == hipSuccess) err = hipEventSynchronize(ev[2 * kReps - 1]);
+      for (int r = 0; err == hipSuccess && r < kReps; ++r) {
+        float t = 0.f;
+        err = hipEventElapsedTime(&t, ev[2 * r], ev[2 * r + 1]);
+        ms += t;
       }
       if (err != hipSuccess) {
         pending_timing() = TimedLaunch{};
         destroy();
         return fail(APC_EHIP, "tuning launch failed: %s", hipGetErrorString(err));
       }
-      const float cost[2] = {bare, c.ks ? second : bare + kGapMs + second};
+      ms /= static_cast<float>(kReps);
+      ranked.emplace_back(ms + (c.ks ? 0.f : kEpilogueMs), c);
+      ranked.back().second.us = ms * 1e3f;
       for (int f = 0; f < 2; ++f) {
-        if (have[f] && cost[f] >= best_ms[f]) continue;
+        const float cost = ms + (f && !c.ks ? kEpilogueMs : 0.f);
+        if (have[f] && cost >= best_ms[f]) continue;
         entry.best[f] = c;
-        entry.best[f].us = (f && c.ks ? second : bare) * 1e3f;
-        best_ms[f] = cost[f];
+        entry.best[f].us = ms * 1e3f;
+        best_ms[f] = cost;
         have[f] = true;
       }
-      if (!c.ks && (!have_plain || bare < plain_ms)) {
-        plain_ms = bare;
+      if (!c.ks && (!have_plain || ms < plain_ms)) {
+        plain_ms = ms;
         plain_nsplit = c.nsplit;
         have_plain = true;
       }
@@ -1174,9 +1174,99 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, const TnUse& use, TnCho
     destroy();
     for (TnChoice& c : entry.best) c.plain_nsplit = plain_nsplit;
   }
+  std::stable_sort(ranked.begin(), ranked.end(),
+                   [](const auto& x, const auto& y) { return x.first < y.first; });
+  // The first few, and the first of either kernel.
+  auto add = [&](const TnChoice& c) {
+    entry.top.push_back(c);
+    entry.top.back().plain_nsplit = plain_nsplit;
+  };
+  for (const auto& [cost, c] : ranked) {
+    if (entry.top.size() == kTuneTop || cost > 1.3f * ranked[0].first) break;
+    add(c);
+  }
+  for (const bool ks : {false, true}) {
+    const auto of_kind = [ks](const TnChoice& c) { return (c.ks > 0) == ks; };
+    if (std::any_of(entry.top.begin(), entry.top.end(), of_kind)) continue;
+    const auto it = std::find_if(ranked.begin(), ranked.end(),
+                                 [&](const auto& x) { return of_kind(x.second); });
+    if (it != ranked.end() && it->first <= 2.f * ranked[0].first) add(it->second);
+  }
   std::lock_guard<std::mutex> lk(mu);
   cache[key] = entry;
-  *out = entry.best[use.follows];
+  *out = entry.best[fuses];
+  if (top) *top = entry.top;
+  return APC_OK;
+}
+
+// The passes' shapes by the time of whole updates.  The candidates that tn_tune
+// left in front are within a few per cent of each other there and can be a fifth
+// apart in an update, where each runs between the other pass and the epilogues
+// and on what they leave in the cache (FP32 at 3842^2, k = 17: 13.6 and 14.1 us
+// alone, 43 and 36 us per update; 6380^2, k = 32: 28.9 and 30.2, 87 and 73).  Pass
+// A's first, beside pass B's best, then pass B's.  Cached like tn_tune's.
+apc_status tn_tune_update(apc_plan_s* P, const std::vector<TnChoice>& topA,
+                          const std::vector<TnChoice>& topB) {
+  using Key = std::tuple<int, int64_t, int64_t, int32_t>;
+  static std::mutex mu;
+  static std::map<Key, std::pair<TnChoice, TnChoice>> cache;
+  if (topA.size() < 2 && topB.size() < 2) return APC_OK;
+  const Key key{P->tq, P->L.Np, P->L.np, P->kp};
+  {
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = cache.find(key);
+    if (it != cache.end()) {
+      P->tnA = it->second.first;
+      P->tnB = it->second.second;
+      return APC_OK;
+    }
+  }
+  ST_TRY(tune_start(P));
+  constexpr int kUpdates = 4, kReps = 3;
+  hipEvent_t ev[2 * kReps] = {};
+  for (hipEvent_t& e : ev) HIP_TRY(hipEventCreate(&e));
+  auto destroy = [&]() {
+    for (hipEvent_t& e : ev) (void)hipEventDestroy(e);
+  };
+  auto updates = [&]() -> apc_status {
+    for (int u = 0; u < kUpdates; ++u) {
+      ST_TRY(pass_a_w(P, P->tq, P->tnA, pass_a_args(P), P->ws + P->L.Wq));
+      ST_TRY(pass_b_update(P, P->tq, P->tnB, pass_b_args(P), 0));
+    }
+    return APC_OK;
+  };
+  auto fastest = [&](TnChoice* slot, const std::vector<TnChoice>& top) -> apc_status {
+    TnChoice best = top[0];
+    float best_ms = 0.f;
+    for (size_t i = 0; i < top.size(); ++i) {
+      *slot = top[i];
+      ST_TRY(updates());  // warm-up
+      for (int r = 0; r < kReps; ++r) {
+        HIP_TRY(hipEventRecord(ev[2 * r], P->stream));
+        ST_TRY(updates());
+        HIP_TRY(hipEventRecord(ev[2 * r + 1], P->stream));
+      }
+      HIP_TRY(hipEventSynchronize(ev[2 * kReps - 1]));
+      float ms = 0.f;
+      for (int r = 0; r < kReps; ++r) {
+        float t = 0.f;
+        HIP_TRY(hipEventElapsedTime(&t, ev[2 * r], ev[2 * r + 1]));
+        ms = r == 0 ? t : std::min(ms, t);
+      }
+      if (i == 0 || ms < best_ms) {
+        best_ms = ms;
+        best = top[i];
+      }
+    }
+    *slot = best;
+    return APC_OK;
+  };
+  apc_status st = fastest(&P->tnA, topA);
+  if (st == APC_OK) st = fastest(&P->tnB, topB);
+  destroy();
+  ST_TRY(st);
+  std::lock_guard<std::mutex> lk(mu);
+  cache[key] = {P->tnA, P->tnB};
   return APC_OK;
 }
 
@@ -1769,22 +1859,30 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
       HIP_TRY(launch_fill_u32(P->at<unsigned>(L.Xs), 2 * P->kp * np, 0u, st));
     }
     // The two passes alternate in an update: each is tuned right after the
-    // other has streamed its operand (pass B first in a default shape).
+    // other has streamed its operand (pass B first in a default shape), then
+    // both in whole updates.
+    const double gamma = P->gamma, eta = P->eta;
+    if (std::isnan(gamma) || std::isnan(eta)) P->gamma = P->eta = 1.0;  // (FP64: estimated below)
+    P->tune_rhs = ca;
     {
+      std::vector<TnChoice> top[2];
       TnChoice dflt;
       dflt.rt = 1;
       dflt.nsplit = 4;
       TnScrub sb{tn_args(P->ws + L.CqT, L.Np, L.np, P->ws + L.Wq, L.Np, P->kp, L.Np, dflt, P->tq,
                          P->ws + L.tnpart, L.np),
                  P->tq, dflt};
-      ST_TRY(tn_tune(P, P->tq, pass_a_args(P), TnUse{P->ws + L.Wq, 0, true}, &P->tnA, &sb));
+      ST_TRY(tn_tune(P, P->tq, pass_a_args(P), true, &P->tnA, &sb, &top[0]));
       const TnScrub sa{pass_a_args(P), P->tq, P->tnA};
-      ST_TRY(tn_tune(P, P->tq, pass_b_args(P), TnUse{nullptr, 0, true}, &P->tnB, &sa));
+      ST_TRY(tn_tune(P, P->tq, pass_b_args(P), true, &P->tnB, &sa, &top[1]));
+      ST_TRY(tn_tune_update(P, top[0], top[1]));
     }
-    ST_TRY(tn_tune(P, x0_type(P), x0_args(P), TnUse{nullptr, 1, true}, &P->tnX0));
+    ST_TRY(tn_tune(P, x0_type(P), x0_args(P), true, &P->tnX0));
     // (Anchor updates run in this shape too, more often than residuals are formed.)
-    ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()),
-                   TnUse{P->ws + (P->tq == kTnF64 ? L.Wq : L.W64), 0, P->anchor_every > 0}, &P->tnR));
+    ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()), P->anchor_every > 0, &P->tnR));
+    P->tune_rhs = nullptr;
+    P->gamma = gamma;
+    P->eta = eta;
   } else {
     // Alg. 1 initialisation: x_i(0) = Q_i c_i (minimum-norm local solutions),
     // x_bar(0) = (1/m) sum_i x_i(0).  The matrix-core triangular product left
