@@ -1102,7 +1102,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
   int plain_nsplit = 1;
   {
     // Each timed launch takes a pair of events recorded from its own dispatch.
-    constexpr int kReps = 3;
+    constexpr int kReps = 2;  // the lesser of them
     hipEvent_t ev[2 * kReps] = {};
     for (hipEvent_t& e : ev) HIP_TRY(hipEventCreate(&e));
     auto destroy = [&]() {
@@ -1147,14 +1147,13 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
       for (int r = 0; err == hipSuccess && r < kReps; ++r) {
         float t = 0.f;
         err = hipEventElapsedTime(&t, ev[2 * r], ev[2 * r + 1]);
-        ms += t;
+        ms = r == 0 ? t : std::min(ms, t);
       }
       if (err != hipSuccess) {
         pending_timing() = TimedLaunch{};
         destroy();
         return fail(APC_EHIP, "tuning launch failed: %s", hipGetErrorString(err));
       }
-      ms /= static_cast<float>(kReps);
       ranked.emplace_back(ms + (c.ks ? 0.f : kEpilogueMs), c);
       ranked.back().second.us = ms * 1e3f;
       for (int f = 0; f < 2; ++f) {
@@ -1176,7 +1175,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
   }
   std::stable_sort(ranked.begin(), ranked.end(),
                    [](const auto& x, const auto& y) { return x.first < y.first; });
-  // The first few, and the first of either kernel.
+  // The first few, and the first of every kernel.
   auto add = [&](const TnChoice& c) {
     entry.top.push_back(c);
     entry.top.back().plain_nsplit = plain_nsplit;
@@ -1185,8 +1184,8 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
     if (entry.top.size() == kTuneTop || cost > 1.3f * ranked[0].first) break;
     add(c);
   }
-  for (const bool ks : {false, true}) {
-    const auto of_kind = [ks](const TnChoice& c) { return (c.ks > 0) == ks; };
+  for (const int ks : {0, 1, 2}) {
+    const auto of_kind = [ks](const TnChoice& c) { return c.ks == ks; };
     if (std::any_of(entry.top.begin(), entry.top.end(), of_kind)) continue;
     const auto it = std::find_if(ranked.begin(), ranked.end(),
                                  [&](const auto& x) { return of_kind(x.second); });
