@@ -486,7 +486,6 @@ struct apc_plan_s {
   bool resident = false;               // k = 1 FP64: T updates in one launch (k_resident)
   int32_t res_rpw = 0, res_cpl = 0, res_stride = 1;
   uint32_t res_spin = 1u << 22;        // polls of one exchanged word before it gives up
-  const double* tune_rhs = nullptr;    // set while setup tunes: c for tune_start
   int32_t qr_passes = 2;               // CholeskyQR passes setup took (1: see setup_impl)
   double qr_defect = NAN;              // estimated ||Q_i^T Q_i - I|| after the first pass
   double* pinned = nullptr;            // pinned host staging (Lanczos coefficients, setup readbacks)
@@ -950,23 +949,6 @@ apc_status gemm_residual(apc_plan_s* P, const double* X, double* R) {
   return APC_OK;
 }
 
-// Once per setup that has to time anything: the start, in a default shape (the
-// real one follows in the tuned shape and sets all of the state again), so that
-// the operands hold what an update multiplies (zeros draw less power).  gamma and
-// eta may not be known yet.
-apc_status tune_start(apc_plan_s* P) {
-  if (!P->tune_rhs) return APC_OK;
-  const double* c = P->tune_rhs;
-  P->tune_rhs = nullptr;
-  const TnChoice keep = P->tnX0;
-  P->tnX0 = TnChoice{};
-  P->tnX0.rt = 1;
-  P->tnX0.nsplit = 4;
-  const apc_status st = start_gemm(P, c);
-  P->tnX0 = keep;
-  return st;
-}
-
 // Chooses the launch shape of one contraction by timing the candidates on the
 // plan's operands (the partial buffer is scratch here).  Shapes are cached per
 // (type, rows, K, kp) for the life of the process, so repeated plans of one
@@ -982,7 +964,7 @@ struct TnScrub {
 };
 // fuses: the contraction's epilogue is one that k_tn_ks applies itself.
 // top (optional): the fastest few as well, for tn_tune_update.
-constexpr size_t kTuneTop = 4;
+constexpr size_t kTuneTop = 6;
 apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* out,
                    const TnScrub* scrub = nullptr, std::vector<TnChoice>* top = nullptr) {
   struct Key {
@@ -1096,7 +1078,6 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
   // from one round of timing.  What an update's passes really take is left to
   // tn_tune_update.
   constexpr float kEpilogueMs = 4.0e-3f;
-  ST_TRY(tune_start(P));
   Entry entry;
   std::vector<std::pair<float, TnChoice>> ranked;
   int plain_nsplit = 1;
@@ -1205,7 +1186,7 @@ apc_status tn_tune(apc_plan_s* P, int type, TnArgs base, bool fuses, TnChoice* o
 // alone, 43 and 36 us per update; 6380^2, k = 32: 28.9 and 30.2, 87 and 73).  Pass
 // A's first, beside pass B's best, then pass B's.  Cached like tn_tune's.
 apc_status tn_tune_update(apc_plan_s* P, const std::vector<TnChoice>& topA,
-                          const std::vector<TnChoice>& topB) {
+                          const std::vector<TnChoice>& topB, const double* c_rhs) {
   using Key = std::tuple<int, int64_t, int64_t, int32_t>;
   static std::mutex mu;
   static std::map<Key, std::pair<TnChoice, TnChoice>> cache;
@@ -1220,49 +1201,54 @@ apc_status tn_tune_update(apc_plan_s* P, const std::vector<TnChoice>& topA,
       return APC_OK;
     }
   }
-  ST_TRY(tune_start(P));
-  constexpr int kUpdates = 4, kReps = 3;
-  hipEvent_t ev[2 * kReps] = {};
+  // The start, in a default shape, so that the operands hold what an update
+  // multiplies (zeros draw less power: tn_tune's times fall short of an update's
+  // by up to a third).  The real one follows and sets all of the state again.
+  {
+    const TnChoice keep = P->tnX0;
+    P->tnX0 = TnChoice{};
+    P->tnX0.rt = 1;
+    P->tnX0.nsplit = 4;
+    ST_TRY(start_gemm(P, c_rhs));
+    P->tnX0 = keep;
+  }
+  // Every candidate in turn, round by round (the clock falls as the chip warms,
+  // which would favour the first), the first round uncounted; a few hundred
+  // microseconds of updates at a time.
+  constexpr int kRounds = 3;
+  const int count = std::max(2, std::min(8, static_cast<int>(150.f / std::max(topA[0].us, 1.f))));
+  std::vector<hipEvent_t> ev(2 * kRounds * std::max(topA.size(), topB.size()), nullptr);
   for (hipEvent_t& e : ev) HIP_TRY(hipEventCreate(&e));
-  auto destroy = [&]() {
-    for (hipEvent_t& e : ev) (void)hipEventDestroy(e);
-  };
-  auto updates = [&]() -> apc_status {
-    for (int u = 0; u < kUpdates; ++u) {
-      ST_TRY(pass_a_w(P, P->tq, P->tnA, pass_a_args(P), P->ws + P->L.Wq));
-      ST_TRY(pass_b_update(P, P->tq, P->tnB, pass_b_args(P), 0));
-    }
-    return APC_OK;
-  };
+  // (A square system's passes have one list and take one shape.)
+  const bool square = P->L.Np == P->L.np;
   auto fastest = [&](TnChoice* slot, const std::vector<TnChoice>& top) -> apc_status {
-    TnChoice best = top[0];
-    float best_ms = 0.f;
-    for (size_t i = 0; i < top.size(); ++i) {
-      *slot = top[i];
-      ST_TRY(updates());  // warm-up
-      for (int r = 0; r < kReps; ++r) {
-        HIP_TRY(hipEventRecord(ev[2 * r], P->stream));
-        ST_TRY(updates());
-        HIP_TRY(hipEventRecord(ev[2 * r + 1], P->stream));
+    const size_t n = top.size();
+    auto set = [&](const TnChoice& c) {
+      *slot = c;
+      if (square) P->tnB = c;
+    };
+    for (size_t q = 0; q < kRounds * n; ++q) {
+      set(top[q % n]);
+      HIP_TRY(hipEventRecord(ev[2 * q], P->stream));
+      for (int u = 0; u < count; ++u) {
+        ST_TRY(pass_a_w(P, P->tq, P->tnA, pass_a_args(P), P->ws + P->L.Wq));
+        ST_TRY(pass_b_update(P, P->tq, P->tnB, pass_b_args(P), 0));
       }
-      HIP_TRY(hipEventSynchronize(ev[2 * kReps - 1]));
-      float ms = 0.f;
-      for (int r = 0; r < kReps; ++r) {
-        float t = 0.f;
-        HIP_TRY(hipEventElapsedTime(&t, ev[2 * r], ev[2 * r + 1]));
-        ms = r == 0 ? t : std::min(ms, t);
-      }
-      if (i == 0 || ms < best_ms) {
-        best_ms = ms;
-        best = top[i];
-      }
+      HIP_TRY(hipEventRecord(ev[2 * q + 1], P->stream));
     }
-    *slot = best;
+    HIP_TRY(hipEventSynchronize(ev[2 * kRounds * n - 1]));
+    std::vector<float> ms(n, 0.f);
+    for (size_t q = n; q < kRounds * n; ++q) {
+      float t = 0.f;
+      HIP_TRY(hipEventElapsedTime(&t, ev[2 * q], ev[2 * q + 1]));
+      ms[q % n] += t;
+    }
+    set(top[std::min_element(ms.begin(), ms.end()) - ms.begin()]);
     return APC_OK;
   };
   apc_status st = fastest(&P->tnA, topA);
-  if (st == APC_OK) st = fastest(&P->tnB, topB);
-  destroy();
+  if (st == APC_OK && !square) st = fastest(&P->tnB, topB);
+  for (hipEvent_t e : ev) (void)hipEventDestroy(e);
   ST_TRY(st);
   std::lock_guard<std::mutex> lk(mu);
   cache[key] = {P->tnA, P->tnB};
@@ -1862,7 +1848,6 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
     // both in whole updates.
     const double gamma = P->gamma, eta = P->eta;
     if (std::isnan(gamma) || std::isnan(eta)) P->gamma = P->eta = 1.0;  // (FP64: estimated below)
-    P->tune_rhs = ca;
     {
       std::vector<TnChoice> top[2];
       TnChoice dflt;
@@ -1874,12 +1859,11 @@ apc_status setup_impl(apc_plan_s* P, const Tiles& T) {
       ST_TRY(tn_tune(P, P->tq, pass_a_args(P), true, &P->tnA, &sb, &top[0]));
       const TnScrub sa{pass_a_args(P), P->tq, P->tnA};
       ST_TRY(tn_tune(P, P->tq, pass_b_args(P), true, &P->tnB, &sa, &top[1]));
-      ST_TRY(tn_tune_update(P, top[0], top[1]));
+      ST_TRY(tn_tune_update(P, top[0], top[1], ca));
     }
     ST_TRY(tn_tune(P, x0_type(P), x0_args(P), true, &P->tnX0));
     // (Anchor updates run in this shape too, more often than residuals are formed.)
     ST_TRY(tn_tune(P, kTnF64, resid_args(P, P->xbar()), P->anchor_every > 0, &P->tnR));
-    P->tune_rhs = nullptr;
     P->gamma = gamma;
     P->eta = eta;
   } else {
