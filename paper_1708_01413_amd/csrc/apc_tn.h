@@ -158,9 +158,10 @@ __host__ __device__ inline int64_t frag_index(int64_t r, int64_t c, int64_t rows
 }
 
 // What bounds it.  FP32, 16384^2, k = 128: 505 us per pass on the FP32 matrix
-// instructions (86 % of their rate), 343 us here (242 us on zeros: six bf16
-// products draw enough power that the clock falls to ~2 GHz; 1.07 GB of M
-// would take 165 us).  8192^2, k = 64: 75 -> 53-63 us (268 MB of M, 4.3-5.1
+// instructions (86 % of their rate), 312-343 us here, bound by power: a launch is
+// 579 thousand cycles of an XCD whatever the data, 283 us at the 2.0 GHz of a
+// cool chip and up to 375 at the 1.5 GHz that a run of them falls to (1.07 GB of
+// M would take 165 us).  8192^2, k = 64: 75 -> 53-63 us (268 MB of M, 4.3-5.1
 // TB/s).  bf16 and FP64: HBM, and the FP64 matrix rate from 64 right-hand
 // sides on.
 //
