@@ -97,3 +97,24 @@ def test_residual_takes_the_fastest_contraction(n, k):
     got = plan.xbar().cpu().numpy()
     res = np.linalg.norm(S.B - S.A @ got) / np.linalg.norm(S.B)
     assert abs(plan.residual() - res) <= 1e-9 * res + 1e-14
+
+
+@pytest.mark.parametrize("g,e", [(1.2, 1.5), (4.0, 9.0)])
+@pytest.mark.parametrize("prec,N,n,k", [("f64", 1290, 1290, 19), ("f32", 1290, 770, 37),
+                                        ("f32", 1030, 1030, 11), ("bf16_ir", 1290, 770, 70)])
+def test_first_plan_of_a_shape_equals_the_next(prec, N, n, k, g, e):
+    """The first plan of a shape in a process times updates of its own start to choose its
+    launch shapes, the next one takes that choice: the same bits after setup and after 18
+    updates, also with parameters that diverge."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    N, n = (v + 256 * (g > 2) for v in (N, n))  # (another padded shape: timed again)
+    S, A, b = _system(N, n, k, N + n + k)
+    plans = [apc.Plan(A, b, S.off, prec, gamma=g, eta=e) for _ in range(2)]
+    first, second = ([p.launch_shapes()[q] for q in ("pass_a", "pass_b")] for p in plans)
+    assert first == second
+    for T in (0, 1, 17):
+        for p in plans:
+            p.iterate(T)
+        x, y = (p.xbar() for p in plans)
+        assert torch.equal(x, y) and bool(torch.isfinite(x).all())
