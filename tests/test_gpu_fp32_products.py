@@ -187,3 +187,34 @@ def test_fp32_adjoint(k, ks, monkeypatch):
               f"deta {abs(de - re) / abs(re):.2e}", flush=True)
         assert dev <= 1e-5
         assert abs(dg - rg) <= 1e-5 * abs(rg) and abs(de - re) <= 1e-5 * abs(re)
+
+
+def test_scales_of_replayed_graphs_and_batches():
+    """A captured graph's updates and a batch's take the scales of the last restart: three
+    updates from right-hand sides of 1e-40 are those of 1 at the FP32 bar."""
+    torch = _torch()
+    from paper_1708_01413_amd import apc
+    k = 24
+    big = synth.gaussian_system(200, 200, 5, k=k, seed=8, scale=1 / math.sqrt(200), shift=2.0)
+    small = synth.gaussian_system(90, 90, 4, seed=9, scale=1 / math.sqrt(90), shift=2.0)
+    plans, stream = [], torch.cuda.Stream()
+    for S, kw in ((big, {"anchor_every": 0}), (small, {})):
+        g, e, _ = O.optimal_params(*O.spectrum(S.A, S.off))
+        plans.append(apc.Plan(torch.from_numpy(S.A).cuda(), torch.from_numpy(S.B).cuda(), S.off,
+                              "f32", gamma=g, eta=e, stream=stream, **kw))
+    plan, b = plans[0], torch.from_numpy(big.B).cuda()
+    g, e, _ = O.optimal_params(*O.spectrum(big.A, big.off))
+    ref = O.apc_run(big.A, big.B, big.off, T=3, gamma=g, eta=e)["xbar"]
+    batch = None
+    for f in (1.0, 1e-40, 1.0, 1e40):
+        for kind in ("graph", "batch"):
+            plan.restart(b * f)
+            if kind == "graph":
+                plan.iterate(3, graph=True)
+            else:
+                batch = batch or apc.Batch(plans)
+                batch.iterate(3)
+            dev = np.linalg.norm(plan.xbar().cpu().numpy() / f - ref) / np.linalg.norm(big.xstar)
+            print(f"{kind} scale {f}: dev {dev:.2e}", flush=True)
+            assert dev <= 1e-5
+    batch.close()
